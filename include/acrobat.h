@@ -197,6 +197,11 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
  * a node waits for its own two children only (flag words per node, polled with the same bound) instead of a
  * whole level waiting for the previous one, provided every workgroup of that launch is resident at once and the
  * call is not being captured into a graph (a captured call keeps one launch per level).
+ * And it covers acrobat_treelstm_forward (and its variant that allocates nothing) for H <= 512: whole trees are dealt
+ * out to groups of H / 16 workgroups that keep U on chip, and a group runs all internal levels of its trees in ONE
+ * launch, its workgroups waiting for each other between levels (max_polls < 0: up to sixteen million polls there).
+ * A captured call, and one with explicit gathers, launches the same kernel once per level instead, with the same
+ * results bit for bit.  With profiling on, the levels of the one launch are timed by clock stamps inside it.
  * Nothing else may occupy the GPU's compute units for long while such a launch runs (another stream's
  * kernels delay the workgroups that are not yet resident; the bound turns a too long delay into
  * ACROBAT_ETIMEOUT instead of a hang).  Two launches of this kind must never share the GPU - each could hold
@@ -469,7 +474,8 @@ typedef struct {
   int32_t n;     /* nodes (rows) in the batch */
   int32_t tile;  /* nodes per workgroup tile of the kernel variant that was launched */
   int32_t ksplit; /* workgroups sharing the contraction range of one tile; 0: the level was cut into equal
-                     shares, one per compute unit, whatever tile boundaries they cross */
+                     shares, one per compute unit, whatever tile boundaries they cross, or (tile 16) dealt out by
+                     whole trees to the groups of workgroups of one launch for all internal levels */
   float ms;      /* execution time of the kernel */
 } acrobat_launch_record;
 

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -18,6 +19,7 @@
 #include "persistent_kernels.h"
 #include "scheduler.h"
 #include "tdc_runtime.h"
+#include "tree_kernels.h"
 
 using namespace acrobat;
 
@@ -33,6 +35,7 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
+std::atomic<bool> g_static_counters_dirty[kMaxDevices];  // a launch that gave up may have left them non-zero
 std::mutex g_scratch_mutex;
 void* g_scratch_ptr[kMaxDevices] = {};
 
@@ -123,6 +126,9 @@ struct acrobat_ctx {
   size_t scratch_cap = 0;  // in floats
   // split-k workspace of the cell kernels (allocated at the first forward call)
   SplitKWorkspace splitk;
+  // split weights, row scales (launch_split_rows); rewritten by every call that uses them
+  unsigned char* d_split = nullptr;
+  size_t split_cap = 0;  // in bytes
   bool gather_fusion = true;  // false: explicit gather launches (ablation)
   int mvrnn_variant = 0;  // which MV-RNN level kernel (acrobat_set_tuning): 1 = streaming
   // tree generation: a zero row (previous-sibling state of a first child) and the scores on the host
@@ -134,9 +140,13 @@ struct acrobat_ctx {
   hipEvent_t tdc_order = nullptr;               // orders the second stream behind the caller's at the start of a call
   // persistent kernels: arrival counters + status word on the device, the status word's copy on the host
   bool persistent = true;           // acrobat_set_persistent
-  int32_t max_polls = 1 << 18;      // bound of every wait inside a persistent kernel
+  int32_t max_polls = 1 << 18;      // (kDefaultMaxPolls) bound of every wait inside a persistent kernel
   unsigned* d_sync = nullptr;       // [kPersistSyncWords]: the probe's flag lines | arrival counters | status
   unsigned* h_status = nullptr;     // pinned host word that a kernel raises when one of its waits runs out
+  TreeGrouping tree_groups;         // of the last tree launch; keeps its buffers
+  bool tree_sync_dirty = false;     // the same for splitk.counters and the tree launches
+  unsigned long long* d_stamps = nullptr;  // profiling: clock at the end of every group's share of a level
+  size_t stamps_cap = 0;
   bool sync_dirty = false;          // the arrival counters in d_sync may be non-zero: clear them before the next persistent recurrence
   unsigned* h_status_dev = nullptr; // the same word's address on the device side
   unsigned* d_node_flags = nullptr; // one word per arena row: the epoch of the call that last finished the node
@@ -234,6 +244,18 @@ int reserve_scratch(acrobat_ctx* ctx, size_t n_floats, hipStream_t stream) {
   return ACROBAT_OK;
 }
 
+int reserve_split(acrobat_ctx* ctx, size_t bytes, hipStream_t stream) {
+  if (bytes <= ctx->split_cap) return ACROBAT_OK;
+  if (stream_is_capturing(stream)) return fail(ctx, ACROBAT_EINVAL, "stream capture: split workspace too small, run once without capture first");
+  if (ctx->d_split) HIP_TRY(ctx, hipFree(ctx->d_split));  // waits for kernels still using it
+  ctx->d_split = nullptr;
+  ctx->split_cap = 0;
+  const size_t cap = bytes + bytes / 8;  // (the row scales grow with the batch)
+  HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&ctx->d_split), cap));
+  ctx->split_cap = cap;
+  return ACROBAT_OK;
+}
+
 // Partial-tile workspace of the k-split levels: 128 MiB.
 int reserve_splitk(acrobat_ctx* ctx, hipStream_t stream) {
   if (ctx->splitk.partial) return ACROBAT_OK;
@@ -264,9 +286,6 @@ int reserve_sync(acrobat_ctx* ctx, hipStream_t stream) {
   if (stream_is_capturing(stream)) return fail(ctx, ACROBAT_EINVAL, "stream capture: counters not allocated, run once without capture first");
   HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&ctx->d_sync), kSyncWordsPadded * sizeof(unsigned)));
   HIP_TRY(ctx, hipMemset(ctx->d_sync, 0, kSyncWordsPadded * sizeof(unsigned)));
-  HIP_TRY(ctx, hipHostMalloc(reinterpret_cast<void**>(&ctx->h_status), sizeof(unsigned), hipHostMallocDefault));
-  *ctx->h_status = 0;
-  HIP_TRY(ctx, hipHostGetDevicePointer(reinterpret_cast<void**>(&ctx->h_status_dev), ctx->h_status, 0));
   return ACROBAT_OK;
 }
 
@@ -471,11 +490,14 @@ int acrobat_create(acrobat_ctx** out, int device) {
   if (hipEventCreateWithFlags(&ctx->stage_done, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&ctx->fixed_done, hipEventDisableTiming) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&ctx->h_fixed_stage), kStaticIndexBytes, hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc(reinterpret_cast<void**>(&ctx->h_status), sizeof(unsigned), hipHostMallocDefault) != hipSuccess ||
+      hipHostGetDevicePointer(reinterpret_cast<void**>(&ctx->h_status_dev), ctx->h_status, 0) != hipSuccess ||
       static_scratch_for(device, &scratch_ptr) != hipSuccess) {
     (void)hipGetLastError();
     acrobat_destroy(ctx);
     return ACROBAT_EHIP;
   }
+  *ctx->h_status = 0;
   ctx->static_scratch = static_cast<unsigned char*>(scratch_ptr);
   if (hipDeviceGetAttribute(&ctx->n_cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) {
     acrobat_destroy(ctx);
@@ -494,6 +516,8 @@ void acrobat_destroy(acrobat_ctx* ctx) {
   if (ctx->fixed_done) (void)hipEventDestroy(ctx->fixed_done);
   if (ctx->d_idx) (void)hipFree(ctx->d_idx);
   if (ctx->d_scratch) (void)hipFree(ctx->d_scratch);
+  if (ctx->d_split) (void)hipFree(ctx->d_split);
+  if (ctx->d_stamps) (void)hipFree(ctx->d_stamps);
   if (ctx->splitk.partial) (void)hipFree(ctx->splitk.partial);
   if (ctx->splitk.counters) (void)hipFree(ctx->splitk.counters);
   if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
@@ -563,6 +587,86 @@ int acrobat_schedule_seqs(int32_t n_seq, const int32_t* len, int32_t* n_levels, 
 
 namespace {
 
+constexpr int32_t kDefaultMaxPolls = 1 << 18;
+// Tree launches wait longer before they give up: they only ever wait for workgroups that are resident or about to be,
+// and a caller may have other work on the GPU (about a microsecond per poll).
+constexpr int32_t kTreeMaxPolls = 1 << 24;
+
+// Which levels of a tree batch run on the weight-stationary kernels: leaf = groups for level 0, groups = groups the
+// trees are dealt out to for the internal levels; 0: those levels run on the level kernels.
+struct TreePlan {
+  int32_t leaf = 0, groups = 0;
+};
+
+TreePlan plan_tree(const acrobat_ctx* ctx, const TreeSchedule& s, int32_t H, int32_t D, int32_t V, bool noalloc, size_t n_iota) {
+  TreePlan p;
+  const int32_t N = s.n_nodes;
+  constexpr double kMaxBytes = 4294967296.0 - 512.0;  // rows are read through a buffer resource
+  if (!ctx->persistent || ctx->splitk.force_bm) return p;
+  // A leaf level of four or more rounds of 64-node tiles goes to the split tiles: 8 808 leaves at H = 512 take 76 us
+  // there (10 of them for splitting the weights) and 100 us on the stationary kernel, whose workgroups each convert
+  // every row for 48 columns; 1 996 leaves at H = 256 take 17.5 and 17 us.
+  const int32_t n_leaf = s.level_off[1];
+  const bool tiles = split_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ctx->splitk) && (long)((n_leaf + 63) / 64) * (H / 32) >= 1024 &&
+                     (!noalloc || ((size_t)5 * H * D + 10 * (size_t)H + n_leaf) * sizeof(float) < kStaticScratchBytes / 2);
+  if (!tiles && (double)std::max(V, N) * D * sizeof(float) < kMaxBytes) p.leaf = stationary_groups(EPI_TREE_LEAF, H, D, ctx->n_cu);
+  const int32_t n_internal = N - n_leaf;
+  if (n_internal == 0 || (double)N * H * sizeof(float) >= kMaxBytes) return p;
+  p.groups = stationary_groups(EPI_TREE_INTERNAL, H, 2 * H, ctx->n_cu);
+  // no more groups than trees of the first internal level can keep busy, and no offset table larger than the lists
+  p.groups = std::min(p.groups, std::min(s.n_trees, s.level_off[2] - s.level_off[1]));
+  p.groups = (int32_t)std::min<int64_t>(p.groups, (4 * (int64_t)N + 4096) / s.n_levels);
+  if (noalloc && (3 * (size_t)N + n_iota + (size_t)s.n_levels * p.groups + 1) * sizeof(int32_t) > kStaticIndexBytes) p.groups = 0;
+  return p;
+}
+
+// Before a launch whose workgroups wait for each other: its turn on the GPU, and zero arrival counters.
+int order_and_clean(acrobat_ctx* ctx, const StationaryArgs& sa, bool noalloc, hipStream_t stream) {
+  HIP_TRY(ctx, order_waiting_launch(ctx->device, stream));
+  const bool dirty = noalloc ? g_static_counters_dirty[ctx->device].exchange(false) : ctx->tree_sync_dirty;
+  if (dirty) HIP_TRY(ctx, launch_fill_u32(sa.counters, 0u, kTreeMaxGroups * kTreeCounterStride, stream));
+  if (!noalloc) ctx->tree_sync_dirty = false;
+  return ACROBAT_OK;
+}
+
+int reserve_stamps(acrobat_ctx* ctx, size_t n, hipStream_t stream, unsigned long long** out) {
+  if (n > ctx->stamps_cap) {
+    if (ctx->d_stamps) HIP_TRY(ctx, hipFree(ctx->d_stamps));
+    ctx->d_stamps = nullptr;
+    ctx->stamps_cap = 0;
+    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&ctx->d_stamps), n * sizeof(unsigned long long)));
+    ctx->stamps_cap = n;
+  }
+  HIP_TRY(ctx, launch_fill_u32(reinterpret_cast<unsigned*>(ctx->d_stamps), 0u, (int)(2 * n), stream));
+  *out = ctx->d_stamps;
+  return ACROBAT_OK;
+}
+
+// Profiling: the record of the one launch for all internal levels becomes one record per level.  A level ends when the
+// last group is through with it (clock stamps of the launch); the first level also gets what came before it.
+int level_records(acrobat_ctx* ctx, const TreeSchedule& s, int32_t groups) {
+  std::vector<unsigned long long> t((size_t)s.n_levels * groups);
+  HIP_TRY(ctx, hipMemcpy(t.data(), ctx->d_stamps, t.size() * sizeof(t[0]), hipMemcpyDeviceToHost));
+  const acrobat_launch_record whole = ctx->records.back();
+  ctx->records.pop_back();
+  const int32_t first = (int32_t)ctx->records.size();
+  float later = 0.0f;
+  unsigned long long before = 0;
+  for (int32_t lv = 1; lv < s.n_levels; ++lv) {
+    const auto* row = t.data() + (size_t)lv * groups;
+    const unsigned long long end = std::max(before + 1, *std::max_element(row, row + groups));
+    acrobat_launch_record r = whole;
+    r.level = lv;
+    r.n = s.level_off[lv + 1] - s.level_off[lv];
+    r.ms = lv == 1 ? 0.0f : (float)(end - before) * 1e-5f;  // 100 MHz
+    later += r.ms;
+    before = end;
+    ctx->records.push_back(r);
+  }
+  ctx->records[first].ms = std::max(whole.ms - later, 1e-5f);
+  return ACROBAT_OK;
+}
+
 // acrobat_treelstm_forward and its variant that allocates nothing.  `noalloc`: the index lists are staged in
 // the context's fixed pinned buffer and uploaded into the library's static device array, which also holds the
 // partial tiles of k-split levels; nothing is allocated or freed, no per-launch events are made (profiling is
@@ -616,6 +720,8 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     for (int32_t lv = 1; lv < s.n_levels; ++lv) n_wide = std::max(n_wide, s.level_off[lv + 1] - s.level_off[lv]);
     const bool unfused = !ctx->gather_fusion && !noalloc;
     const size_t n_iota = unfused ? (size_t)std::max(n_leaf, 2 * n_wide) : 0;
+    const TreePlan plan = plan_tree(ctx, s, H, D, V, noalloc, n_iota);
+    const size_t n_off = plan.groups > 0 ? (size_t)s.n_levels * plan.groups + 1 : 0;
     // (Uploading the leaf lists and launching level 0 before the internal levels are sorted was measured and
     // dropped: the second upload sits behind the leaf kernel in stream order, so its three copy commands land
     // between level 0 and level 1 - 0.731 instead of 0.691 ms per forward on 17 134 nodes - while the sort
@@ -640,7 +746,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
       ws.n_cu = ctx->n_cu;
     } else {
       TRY(reserve_splitk(ctx, stream));
-      TRY(reserve_indices(ctx, 3 * (size_t)N + n_iota, stream));
+      TRY(reserve_indices(ctx, 3 * (size_t)N + n_iota + n_off, stream));
       st = ctx->h_stage;
       d_idx = ctx->d_idx;
       ws = ctx->splitk;
@@ -668,9 +774,10 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     if (unfused) TRY(reserve_scratch(ctx, std::max((size_t)n_leaf * D, 4 * (size_t)n_wide * H), stream));
     finish.now();
     stage_leaves();
-    stage_internal();
+    if (plan.groups > 0) ctx->tree_groups.stage(*trees, s, plan.groups, st, st + N, st + 2 * (size_t)N, st + 3 * (size_t)N + n_iota);
+    else stage_internal();
     for (size_t i = 0; i < n_iota; ++i) st[3 * (size_t)N + i] = (int32_t)i;
-    HIP_TRY(ctx, copy_up(0, 3 * (size_t)N + n_iota));  // one upload (the second operands of level 0 are never read)
+    HIP_TRY(ctx, copy_up(0, 3 * (size_t)N + n_iota + n_off));  // one upload (the second operands of level 0 are never read)
     HIP_TRY(ctx, staging_in_flight());
     const int32_t* d_out = d_idx;
     const int32_t* d_ia = d_idx + N;
@@ -678,6 +785,51 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     const int32_t* d_iota = d_idx + 3 * (size_t)N;
 
     LaunchTimer timer{ctx, stream, !noalloc};
+    // Wide levels run on the split contraction: the weights they use are split first, and the leaves' embedding rows
+    // get their scales, in one launch.
+    const bool split_leaf = !plan.leaf && split_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ws);
+    const bool split_internal = plan.groups == 0 && n_wide > 0 && split_level_wins(EPI_TREE_INTERNAL, n_wide, H, 2 * H, ws);
+    struct { unsigned char* w; float* scale; } split_w[2] = {};
+    float* leaf_scale = nullptr;
+    SplitRowsArgs split_rows{};
+    if (split_leaf || split_internal) {
+      const size_t leaf_bytes = split_leaf ? (size_t)5 * H * D * sizeof(float) : 0;
+      const size_t int_bytes = split_internal ? (size_t)5 * H * 2 * H * sizeof(float) : 0;
+      const size_t scale_bytes = ((size_t)10 * H + n_leaf) * sizeof(float);
+      const size_t bytes = (leaf_bytes + int_bytes + scale_bytes + 255) / 256 * 256;
+      unsigned char* at = nullptr;
+      if (!noalloc) {
+        TRY(reserve_split(ctx, bytes, stream));
+        at = ctx->d_split;
+      } else if (bytes <= ws.partial_floats * sizeof(float)) {  // the end of the partial tiles' region
+        ws.partial_floats -= bytes / sizeof(float);
+        at = reinterpret_cast<unsigned char*>(ws.partial + ws.partial_floats);
+      }
+      if (at) {
+        SplitRowsArgs sr{};
+        float* scale = reinterpret_cast<float*>(at + leaf_bytes + int_bytes);
+        if (split_leaf) {  // the rows of gates i, o, u only
+          split_w[0] = {at, scale};
+          leaf_scale = scale + (size_t)10 * H;
+          sr.job[sr.count++] = {d_Wleaf, 3 * H, D, nullptr, H, 2 * H, at, scale};
+          sr.job[sr.count++] = {d_emb, n_leaf, D, d_ia, 0, 0, nullptr, leaf_scale};
+        }
+        if (split_internal) {
+          split_w[1] = {at + leaf_bytes, scale + (size_t)5 * H};
+          sr.job[sr.count++] = {d_U, 5 * H, 2 * H, nullptr, 5 * H, 0, split_w[1].w, split_w[1].scale};
+        }
+        split_rows = sr;
+      }
+    }
+    // Stationary launches of the plan: level 0, then the internal levels - in one launch, whose workgroups wait for each
+    // other, unless the call is captured into a graph (launches of that kind must take turns, which replays cannot be
+    // made to do) or gathers explicitly between levels; then the same kernel runs level by level, with the same results.
+    const bool one_launch = plan.groups > 0 && !unfused && !stream_is_capturing(stream);
+    StationaryArgs sa{};
+    sa.n_cb = H / 16;
+    sa.counters = ws.counters;
+    sa.status = ctx->h_status_dev;
+    sa.max_polls = ctx->max_polls == kDefaultMaxPolls ? kTreeMaxPolls : ctx->max_polls;
     for (int32_t lv = 0; lv < s.n_levels; ++lv) {
       const int32_t off = s.level_off[lv], n = s.level_off[lv + 1] - off;
       CellLevelArgs a{};
@@ -686,7 +838,10 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
       a.out_rows = d_out + off;
       a.h = d_h;
       a.c = d_c;
+      a.Wsplit = split_w[lv > 0].w;
+      a.w_scale = split_w[lv > 0].scale;
       if (lv == 0) {
+        a.src_scale = leaf_scale;
         a.nseg = 1; a.kseg = D;
         a.src0 = d_emb; a.idx0 = d_ia + off; a.ld0 = D;
         a.W = d_Wleaf; a.ldw = D; a.bias = d_bleaf;
@@ -720,6 +875,41 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
         TRY(timer.end());
       }
       TRY(timer.begin(lv == 0 ? ACROBAT_K_TREE_LEAF : ACROBAT_K_TREE_INTERNAL, lv, n));
+      if (lv == 0 && split_rows.count > 0) {  // timed with level 0, whose record covers both launches
+        LaunchEvents first;
+        std::swap(first.start, timer.ev.start);
+        HIP_TRY(ctx, launch_split_rows(split_rows, stream, first));
+      }
+      if (lv == 0 && plan.leaf) {
+        sa.a = a;
+        sa.src_bytes = (uint32_t)((size_t)(unfused ? n : V) * D * sizeof(float));
+        sa.n_groups = std::min(plan.leaf, (n + 15) / 16);
+        sa.level0 = 0; sa.level1 = 1;
+        if (timer.tile()) *timer.tile() = 16;
+        HIP_TRY(ctx, launch_stationary(EPI_TREE_LEAF, sa, stream, timer.ev));
+        TRY(timer.end());
+        continue;
+      }
+      if (lv > 0 && plan.groups > 0) {
+        sa.a = a;  // lists by absolute position
+        sa.a.idx0 -= off; sa.a.idx1 -= off; sa.a.out_rows -= off;
+        sa.src_bytes = (uint32_t)((size_t)(unfused ? 2 * n : N) * H * sizeof(float));
+        sa.n_groups = plan.groups;
+        sa.off = d_idx + 3 * (size_t)N + n_iota;
+        sa.level0 = lv; sa.level1 = one_launch ? s.n_levels : lv + 1;
+        if (timer.tile()) *timer.tile() = 16;
+        if (timer.ksplit()) *timer.ksplit() = 0;
+        if (sa.level1 - lv > 1) {
+          TRY(order_and_clean(ctx, sa, noalloc, stream));
+          if (timer.on()) TRY(reserve_stamps(ctx, (size_t)s.n_levels * plan.groups, stream, &sa.stamps));
+        }
+        HIP_TRY(ctx, launch_stationary(EPI_TREE_INTERNAL, sa, stream, timer.ev));
+        TRY(timer.end());
+        if (!one_launch) continue;
+        TRY(timer.finish());
+        if (sa.stamps) TRY(level_records(ctx, s, plan.groups));
+        return ACROBAT_OK;
+      }
       HIP_TRY(ctx, launch_cell_level(lv == 0 ? EPI_TREE_LEAF : EPI_TREE_INTERNAL, a, stream, ws,
                                      timer.tile(), timer.ksplit(), timer.ev));
       TRY(timer.end());
@@ -901,6 +1091,9 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
       return fail(ctx, ACROBAT_EINVAL, "weight matrix has 2^31 or more elements");
     TRY(reserve_splitk(ctx, stream));
     TRY(reserve_scratch(ctx, (size_t)R * 4 * (size_t)H, stream));
+    const size_t split_bytes = (size_t)4 * H * D * sizeof(float);
+    const bool split = split_level_wins(EPI_STORE_Z, R, H, D, ctx->splitk);
+    if (split) TRY(reserve_split(ctx, split_bytes + ((size_t)4 * H + R) * sizeof(float), stream));
     auto input_transform = [&](LaunchTimer& timer) {  // hoisted: every step of every sequence in one dense batch
       CellLevelArgs a{};
       a.n = R; a.H = H; a.nseg = 1; a.kseg = D;
@@ -908,6 +1101,18 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
       a.W = d_Wx; a.ldw = D; a.bias = d_b;
       a.zout = ctx->d_scratch;
       TRY(timer.begin(ACROBAT_K_LSTM_INPUT, 0, R));
+      if (split) {  // (timed with the contraction that follows)
+        float* scale = reinterpret_cast<float*>(ctx->d_split + split_bytes);
+        a.Wsplit = ctx->d_split;
+        a.w_scale = scale;
+        a.src_scale = scale + 4 * (size_t)H;
+        SplitRowsArgs sr{};
+        sr.job[sr.count++] = {d_Wx, 4 * H, D, nullptr, 4 * H, 0, ctx->d_split, scale};
+        sr.job[sr.count++] = {d_x, R, D, nullptr, R, 0, nullptr, scale + 4 * (size_t)H};
+        LaunchEvents first;
+        std::swap(first.start, timer.ev.start);
+        HIP_TRY(ctx, launch_split_rows(sr, stream, first));
+      }
       HIP_TRY(ctx, launch_cell_level(EPI_STORE_Z, a, stream, ctx->splitk, timer.tile(), timer.ksplit(), timer.ev));
       return timer.end();
     };
@@ -1491,6 +1696,8 @@ int acrobat_device_status(acrobat_ctx* ctx) {
   if (!ctx->h_status || *ctx->h_status == 0) return ACROBAT_OK;
   *ctx->h_status = 0;
   ctx->sync_dirty = true;  // a launch that gave up leaves its counters as they were
+  ctx->tree_sync_dirty = true;
+  if (ctx->device < kMaxDevices) g_static_counters_dirty[ctx->device] = true;
   return fail(ctx, ACROBAT_ETIMEOUT, "a workgroup of a persistent launch gave up waiting; the launch's outputs are incomplete");
 }
 

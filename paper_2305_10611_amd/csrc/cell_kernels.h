@@ -40,7 +40,14 @@ struct CellLevelArgs {
   // grid), y[row * ldo + j] is written for j < n_cols.  0 elsewhere (= H).
   int32_t n_cols;
   float* y; int32_t ldo;
+  // Operands of the split contraction (cell_split_kernels.hip); Wsplit null: only the fp32 kernels apply.
+  const void* Wsplit = nullptr;       // W's rows split by launch_split_rows, same row order and bytes per row as W
+  const float* w_scale = nullptr;     // scale of every row of W
+  const float* src_scale = nullptr;   // [n] scale of every node's row of src0 (nseg == 1); null: states, kStateScale
 };
+
+// Scale of a row of gated-cell states in the split contraction: |h| <= 1 becomes at most 2^14.
+constexpr float kStateScale = 16384.0f;
 
 // Device workspace for levels whose k range is split over several workgroups: partial
 // accumulator tiles, written by the contraction kernel and summed by the reduction kernel
@@ -86,6 +93,24 @@ inline void launch_with_events(Kernel kernel, dim3 grid, dim3 block, size_t lds_
 hipError_t launch_cell_level(CellEpilogue epi, const CellLevelArgs& a, hipStream_t stream,
                              const SplitKWorkspace& ws, int32_t* tile, int32_t* ksplit,
                              const LaunchEvents& ev = LaunchEvents());
+
+// Row scales, and split copies of weight rows, for the split contraction: up to four matrices in one launch.
+struct SplitRowsJob {
+  const float* src; int32_t rows, K;  // rows to treat, columns (a multiple of 32; also the row stride of src)
+  const int32_t* idx;                 // [rows] gathered rows of src (outputs are then by position); null: rows 0, 1, ...
+  int32_t skip_from, skip_rows;       // without idx: row r >= skip_from stands for row r + skip_rows (outputs too)
+  void* dst;                          // split copy, K * 4 bytes per row, or null
+  float* scale;                       // one per row
+};
+struct SplitRowsArgs {
+  SplitRowsJob job[4];
+  int32_t count;
+};
+hipError_t launch_split_rows(const SplitRowsArgs& s, hipStream_t stream, const LaunchEvents& ev = LaunchEvents());
+// A level on the split contraction (a.Wsplit set; TREE_LEAF, TREE_INTERNAL and STORE_Z; nseg > 0).
+// Whether a level (G gates of H units over K columns) is wide enough for the split contraction to win.
+bool split_level_wins(CellEpilogue epi, int32_t n, int32_t H, int32_t K, const SplitKWorkspace& ws);
+hipError_t launch_cell_split(CellEpilogue epi, const CellLevelArgs& a, hipStream_t stream, const LaunchEvents& ev = LaunchEvents());
 
 // MV-RNN level: for each of the n nodes at list positions [0,n):
 //   p = tanh(W [B a ; A b]),  P = W_M [A ; B]  with (a,A) / (b,B) the left / right child state.

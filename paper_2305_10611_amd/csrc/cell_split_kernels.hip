@@ -1,0 +1,294 @@
+// Wide levels on the fp16 matrix cores at fp32 precision (gfx950).
+//
+// The fp32 matrix instructions reach 157 TFLOP/s on this part, the fp16 ones 2.5 PFLOP/s.  A wide level is bound
+// by the former (cell_level_kernel: 131 TFLOP/s), so here every fp32 operand is split into two fp16 terms,
+//     s x = hi + lo + e,   hi = fp16(s x),   lo = fp16(s x - hi),   |e| <= 2^-24 |s x|,
+// and the product of two such numbers is taken as hi hi' + hi lo' + lo hi', three matrix instructions with fp32
+// accumulation; the term left out is at most 2^-24 of the product.  s is a power of two, so scaling is exact: it
+// lifts the largest element of a row to [2^14, 2^15), below the fp16 maximum, and keeps lo a normal fp16 number for
+// every element down to 2^-17 of the row's largest (the matrix cores take denormal fp16 operands, so smaller elements
+// lose precision gradually, at 2^-40 of the row's largest element).  Every weight row and every row of an input
+// matrix has a scale of its own, found by split_rows_kernel; rows of states of a gated cell, |h| <= 1, share the
+// scale kStateScale.  Both scales are taken out again in fp32 behind the contraction.
+// Measured against 64 bits, the states are as close as those of the fp32 kernels or closer (a matrix instruction
+// adds sixteen products before it rounds, so there are fewer roundings than in the fp32 contraction).
+// Infinities, NaNs and states out of range give a pre-activation that is not finite; such an element is computed
+// again with a plain fp32 dot product, which then says what fp32 says.
+#include "cell_epilogue.h"
+#include "split_fp16.h"
+
+#include <type_traits>
+
+namespace acrobat {
+namespace {
+
+// One wavefront per row.  A weight matrix is stored split: each 32-column slab of a row, 128 bytes as in fp32,
+// becomes its 32 hi terms followed by its 32 lo terms, so that the contraction fetches it as it fetches fp32 rows.
+// An input matrix only gets its row scales (its rows are split on their way to LDS).  Bound by the bytes: read once,
+// weights written once.
+__global__ __launch_bounds__(kThreads) void split_rows_kernel(const SplitRowsArgs s) {
+  const int lane = threadIdx.x & 63;
+  int r = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+  int q = 0;
+  while (q < s.count && r >= s.job[q].rows) r -= s.job[q++].rows;
+  if (q == s.count) return;
+  const SplitRowsJob& jb = s.job[q];
+  const size_t src_row = jb.idx ? (size_t)jb.idx[r] : (size_t)(r < jb.skip_from ? r : r + jb.skip_rows);
+  const float* x = jb.src + src_row * (size_t)jb.K;
+  const int chunks = jb.K >> 2;
+  float m = 0.0f;
+  for (int c = lane; c < chunks; c += 64) {
+    const floatx4 v = *reinterpret_cast<const floatx4*>(x + 4 * c);
+    m = fmaxf(m, fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
+  const float sc = scale_for(m);
+  const size_t dst_row = jb.idx ? (size_t)r : src_row;
+  if (lane == 0) jb.scale[dst_row] = sc;
+  if (!jb.dst) return;
+  unsigned char* out = static_cast<unsigned char*>(jb.dst) + dst_row * (size_t)jb.K * sizeof(float);
+  for (int c = lane; c < chunks; c += 64) {
+    half4 hi, lo;
+    split4(*reinterpret_cast<const floatx4*>(x + 4 * c), sc, hi, lo);
+    unsigned char* slab = out + (size_t)(c >> 3) * 128 + (c & 7) * 8;
+    *reinterpret_cast<half4*>(slab) = hi;
+    *reinterpret_cast<half4*>(slab + 64) = lo;
+  }
+}
+
+// The tile of cell_level_kernel (64 nodes x 32 hidden units x all G gates, four wavefronts = two node blocks x two
+// halves of a slab) on v_mfma_f32_32x32x16_f16.  Per 32-k slab a wavefront issues 3 G matrix instructions (480
+// cycles for five gates, fp32: 2 560) behind 2 + 2 G 16-byte LDS reads, so what the fp32 kernel could neglect now
+// counts: LDS (77 KB read and written per slab) and the slabs' way from the L2 (28 KB).  Slabs travel global ->
+// registers -> LDS with kSets slabs in flight; node rows are split on the way, weight rows arrive split.  Two
+// buffers and one barrier per slab: behind it slab kb is complete, and everybody is through with slab kb - 1, whose
+// buffer slab kb + 1 then fills while slab kb is multiplied.  Two workgroups share a compute unit.
+// LDS row = one slab of one row: 8 chunks of 16 bytes, hi of the four 8-k groups, then lo; chunk c of row r sits at
+// chunk position c ^ ((r >> 1) & 7), which keeps stores and operand reads free of bank conflicts.
+template <int G>
+struct SplitTile {
+  static constexpr int BM = 64;
+  static constexpr int ROWS = BM + 32 * G;
+  static constexpr int BUF_BYTES = ROWS * 128;
+  static constexpr int RED_BYTES = 2 * G * kBlockFloats * (int)sizeof(float);
+  static constexpr int SMEM_BYTES = 2 * BUF_BYTES > RED_BYTES ? 2 * BUF_BYTES : RED_BYTES;
+  static constexpr int NV = kOwnedRows<2>;
+};
+
+template <int G, int EPI>
+__global__ __launch_bounds__(kThreads, 2) void cell_split_kernel(const CellLevelArgs a) {
+  using L = SplitTile<G>;
+  constexpr int WM = 2, WK = 2, BM = L::BM, kSets = 2;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[L::SMEM_BYTES];
+  __shared__ int sidx[3 * BM];      // the tile's index table, see epilogue_fetch
+  __shared__ float s_inv[BM];       // inverse scale of every node row
+
+  // XCD-aware order as in cell_level_kernel: workgroup id % 8 is the XCD; XCD x runs the unit tiles x % 4 + 4 i of the
+  // node tiles 2 i' + x / 4 (the launcher pads an odd number of node tiles; with fewer than four unit tiles it is plain)
+  const int n_jt = a.H >> 5;
+  int jt, mt;
+  if (n_jt % 4 == 0) {
+    const int x = blockIdx.x & 7, q = blockIdx.x >> 3, jq = n_jt >> 2;
+    jt = (x & 3) + 4 * (q % jq);
+    mt = 2 * (q / jq) + (x >> 2);
+    if (mt * BM >= a.n) return;
+  } else {
+    jt = blockIdx.x % n_jt;
+    mt = blockIdx.x / n_jt;
+  }
+  const int j0 = jt * 32, m0 = mt * BM;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave % WM, wk = wave / WM;
+  const int H = a.H, n = a.n;
+
+  // ---- global -> LDS assignment: 16-byte chunk `tid & 7` of tile row `tid >> 3` (+ 32 i)
+  const int lrow = tid >> 3, c8 = tid & 7;
+  int row0[WM], row1[WM];
+  float scale[WM];
+#pragma unroll
+  for (int i = 0; i < WM; ++i) {
+    int node = m0 + lrow + 32 * i;
+    node = node < n ? node : n - 1;  // tail rows re-read the last node; never stored
+    row0[i] = a.idx0 ? a.idx0[node] : node;
+    row1[i] = a.idx1 ? a.idx1[node] : node;
+    scale[i] = a.src_scale ? a.src_scale[node] : kStateScale;
+    if (c8 == 2) sidx[lrow + 32 * i] = a.out_rows ? a.out_rows[node] : node;
+    if (c8 == 3) s_inv[lrow + 32 * i] = inverse_power(scale[i]);
+  }
+  // weight rows: bytes of this thread's chunk; gate and slab offsets are uniform
+  const unsigned char* const wsplit = static_cast<const unsigned char*>(a.Wsplit);
+  const size_t boff = (size_t)(j0 + lrow) * a.ldw * sizeof(float) + c8 * 16;
+  const size_t gate_stride = (size_t)H * a.ldw * sizeof(float);
+
+  floatx16 acc[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[g][v] = 0.0f;
+
+  const int slabs_per_seg = a.kseg / kBK;
+  const int S = a.nseg * slabs_per_seg;  // > 0 (launcher)
+  floatx4 ra[kSets][WM], rb[kSets][G];
+  const float* aptr0[WM];
+  const float* aptr1[WM];
+  auto load_b = [&](int set, int kb) {
+    kb = kb < S ? kb : S - 1;  // past the end: fetched again, never multiplied
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+      rb[set][g] = *reinterpret_cast<const floatx4*>(wsplit + gate_row<EPI>(g) * gate_stride + boff + (size_t)kb * 128);
+  };
+  auto load_a = [&](int set, int kb) {
+    kb = kb < S ? kb : S - 1;
+    const bool seg = kb >= slabs_per_seg;
+    const int koff = (kb - (seg ? slabs_per_seg : 0)) * kBK;
+#pragma unroll
+    for (int r = 0; r < WM; ++r) ra[set][r] = *reinterpret_cast<const floatx4*>((seg ? aptr1[r] : aptr0[r]) + koff);
+  };
+  // stores: rows 32 apart share their swizzle
+  const int sw = (lrow >> 1) & 7;
+  const int st_b = lrow * 128 + ((c8 ^ sw) << 4);
+  const int st_hi = lrow * 128 + (((c8 >> 1) ^ sw) << 4) + (c8 & 1) * 8;
+  const int st_lo = lrow * 128 + (((4 + (c8 >> 1)) ^ sw) << 4) + (c8 & 1) * 8;
+  auto store_slab = [&](int set, int buf) {
+    unsigned char* As = smem + buf * L::BUF_BYTES;
+    unsigned char* Bs = As + BM * 128;
+#pragma unroll
+    for (int r = 0; r < WM; ++r) {
+      half4 hi, lo;
+      split4(ra[set][r], scale[r], hi, lo);
+      *reinterpret_cast<half4*>(As + 32 * r * 128 + st_hi) = hi;
+      *reinterpret_cast<half4*>(As + 32 * r * 128 + st_lo) = lo;
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) *reinterpret_cast<floatx4*>(Bs + 32 * g * 128 + st_b) = rb[set][g];
+  };
+  // operand fragments: row lane % 32, 8-k group 2 wk + lane / 32
+  const int fsw = ((lane & 31) >> 1) & 7, fkg = 2 * wk + (lane >> 5);
+  const int fr_hi = (lane & 31) * 128 + ((fkg ^ fsw) << 4), fr_lo = (lane & 31) * 128 + (((4 + fkg) ^ fsw) << 4);
+
+#pragma unroll
+  for (int i = 0; i < kSets; ++i) load_b(i, i);  // does not depend on the indices
+#pragma unroll
+  for (int i = 0; i < WM; ++i) {
+    aptr0[i] = a.src0 + (size_t)row0[i] * (size_t)a.ld0 + c8 * 4;
+    aptr1[i] = a.nseg > 1 ? a.src1 + (size_t)row1[i] * (size_t)a.ld1 + c8 * 4 : aptr0[i];
+    if (c8 == 0) sidx[BM + lrow + 32 * i] = row0[i];
+    if (c8 == 1) sidx[2 * BM + lrow + 32 * i] = row1[i];
+  }
+#pragma unroll
+  for (int i = 0; i < kSets; ++i) load_a(i, i);
+  store_slab(0, 0);
+  load_b(0, kSets);
+  load_a(0, kSets);
+
+  auto iteration = [&](int kb, int set, int buf) {  // set = (kb + 1) % kSets, buf = kb & 1
+    __syncthreads();
+    const unsigned char* As = smem + buf * L::BUF_BYTES + wm * 32 * 128;
+    const unsigned char* Bs = smem + buf * L::BUF_BYTES + BM * 128;
+    half8 ahi = *reinterpret_cast<const half8*>(As + fr_hi), alo = *reinterpret_cast<const half8*>(As + fr_lo);
+    half8 bhi[G], blo[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      bhi[g] = *reinterpret_cast<const half8*>(Bs + g * 32 * 128 + fr_hi);
+      blo[g] = *reinterpret_cast<const half8*>(Bs + g * 32 * 128 + fr_lo);
+    }
+    store_slab(set, buf ^ 1);  // slab kb + 1
+    load_b(set, kb + 1 + kSets);
+    load_a(set, kb + 1 + kSets);
+#pragma unroll
+    for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(alo, bhi[g], acc[g], 0, 0, 0);
+#pragma unroll
+    for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ahi, blo[g], acc[g], 0, 0, 0);
+#pragma unroll
+    for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ahi, bhi[g], acc[g], 0, 0, 0);
+  };
+  static_assert(kSets == 2, "the loop below alternates two sets and two buffers");
+  int kb = 0;
+  for (; kb + 2 <= S; kb += 2) {
+    iteration(kb, 1, 0);
+    iteration(kb + 1, 0, 1);
+  }
+  if (kb < S) iteration(kb, 1, 0);
+
+  TileEpilogueOperands<G, EPI, WM, WK> eo;
+  tile_epilogue_fetch<G, EPI, WM, WK>(a, m0, j0, sidx, eo);
+  float own[G][L::NV];
+  reduce_k_waves<G, WM, WK>(acc, reinterpret_cast<float*>(smem), own);  // (starts with a barrier)
+
+  // scales out again; what is not finite is computed in fp32
+  const int j = j0 + (lane & 31);
+  bool bad = false;
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const float winv = inverse_power(a.w_scale[gate_row<EPI>(g) * H + j]);
+#pragma unroll
+    for (int v = 0; v < L::NV; ++v) {
+      const int r = tile_acc_row<WK>(wk, v);
+      const float z = own[g][v] * winv * s_inv[wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)];
+      own[g][v] = z;
+      bad |= !__builtin_isfinite(z);
+    }
+  }
+  if (__ballot(bad) != 0) {
+#pragma unroll
+    for (int v = 0; v < L::NV; ++v) {
+      const int r = tile_acc_row<WK>(wk, v);
+      const int t = wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+      const float* x0 = a.src0 + (size_t)sidx[BM + t] * (size_t)a.ld0;
+      const float* x1 = a.nseg > 1 ? a.src1 + (size_t)sidx[2 * BM + t] * (size_t)a.ld1 : x0;
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        if (__builtin_isfinite(own[g][v])) continue;
+        const float* w = a.W + ((size_t)gate_row<EPI>(g) * H + j) * a.ldw;
+        float z = 0.0f;
+#pragma unroll 1
+        for (int k = 0; k < a.nseg * a.kseg && z == z; ++k) z = __builtin_fmaf(k < a.kseg ? x0[k] : x1[k - a.kseg], w[k], z);
+        own[g][v] = z;
+      }
+    }
+  }
+  tile_epilogue_apply<G, EPI, WM, WK>(a, j0, own, eo);
+}
+
+template <int G, int EPI>
+hipError_t launch_split(const CellLevelArgs& a, hipStream_t stream, const LaunchEvents& ev) {
+  const int n_jt = a.H / 32;
+  const long n_mt = (a.n + 63) / 64;
+  const unsigned grid = (unsigned)(n_jt % 4 == 0 ? 2 * n_jt * ((n_mt + 1) / 2) : n_jt * n_mt);
+  launch_with_events((cell_split_kernel<G, EPI>), dim3(grid), dim3(kThreads), 0, stream, ev.start, ev.stop, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_split_rows(const SplitRowsArgs& s, hipStream_t stream, const LaunchEvents& ev) {
+  long rows = 0;
+  for (int q = 0; q < s.count; ++q) rows += s.job[q].rows;
+  if (rows == 0) return hipSuccess;
+  launch_with_events(split_rows_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(kThreads), 0, stream, ev.start, ev.stop, s);
+  return hipGetLastError();
+}
+
+bool split_level_wins(CellEpilogue epi, int32_t n, int32_t H, int32_t K, const SplitKWorkspace& ws) {
+  if (n <= 0 || K <= 0 || (epi != EPI_TREE_LEAF && epi != EPI_TREE_INTERNAL && epi != EPI_STORE_Z)) return false;
+  if (ws.force_bm) return false;
+  // A tile alone on a compute unit takes 25 us for K = 1024, 32 slabs at 0.78 us (fp32: 45), and shares its fixed cost
+  // with nobody; below about half a tile per compute unit the fp32 kernels for mid-size levels are as fast: H = 512,
+  // 568 nodes 25.4 against 37.9 us, 422 nodes 25.6 against 28.6, 226 nodes 25.1 against 26.7, 159 nodes 25.0 against
+  // 15.7; H = 256 (K = 512) 671 nodes 17.2 against 18.2, 394 nodes 16.8 against 15.5.  The launch that splits the
+  // weights (5 to 10 us) has to be earned as well.
+  return (long)((n + 63) / 64) * (H / 32) >= 128;
+}
+
+hipError_t launch_cell_split(CellEpilogue epi, const CellLevelArgs& a, hipStream_t stream, const LaunchEvents& ev) {
+  switch (epi) {
+    case EPI_TREE_LEAF: return launch_split<3, EPI_TREE_LEAF>(a, stream, ev);
+    case EPI_TREE_INTERNAL: return launch_split<5, EPI_TREE_INTERNAL>(a, stream, ev);
+    case EPI_STORE_Z: return launch_split<4, EPI_STORE_Z>(a, stream, ev);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace acrobat

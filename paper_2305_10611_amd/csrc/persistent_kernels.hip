@@ -60,36 +60,6 @@ __device__ __forceinline__ bool wait_for_flags(const unsigned* line, int n, unsi
   }
 }
 
-// Thread 0 of a workgroup waits until *counter >= target.  Returns false when the wait ran out or another
-// workgroup has raised the status word; the caller then leaves its loop.
-__device__ __forceinline__ bool wait_for(const unsigned* counter, unsigned target, unsigned* status, int max_polls) {
-  if (max_polls == 0) {  // test hook: every wait gives up at once, whether or not it would have had to wait
-    raise_status(status);
-    return false;
-  }
-  int polls = 0;
-  while (load_agent(counter) < target) {
-    if (++polls > max_polls) {
-      raise_status(status);
-      return false;
-    }
-    if ((polls & 255) == 0 && status_raised(status)) return false;
-    __builtin_amdgcn_s_sleep(1);
-  }
-  return true;
-}
-
-// A block's arrival counter goes back to zero for the next launch without a clearing launch in between: every
-// workgroup of the block counts itself out in the word behind the counter when it has left its loop (it no longer
-// looks at the counter then), and the last one to do so clears both words.  (After a wait that ran out the words
-// may be left in any state: the host clears them before the next launch once it has seen the status.)
-__device__ __forceinline__ void leave_block(unsigned* counter, unsigned members) {
-  if (__hip_atomic_fetch_add(counter + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == members - 1) {
-    __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(counter + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-}
-
 __global__ void fill_u32_kernel(unsigned* p, unsigned value, int n) {
   for (int i = threadIdx.x + blockIdx.x * blockDim.x; i < n; i += blockDim.x * gridDim.x) p[i] = value;
 }

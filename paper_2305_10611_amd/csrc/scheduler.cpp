@@ -86,6 +86,7 @@ int TreeScheduler::general_tree(const acrobat_trees& tr, int32_t t, int32_t voca
 int TreeScheduler::begin(const acrobat_trees& tr, int32_t vocab, TreeSchedule& out, std::vector<int32_t>* leaf_tokens,
                          std::string& err) {
   out.n_nodes = 0;
+  out.n_trees = 0;
   out.n_levels = 0;
   out.level_off.assign(1, 0);
   if (tr.n_trees < 0) { err = "n_trees is negative"; return ACROBAT_EINVAL; }
@@ -95,6 +96,7 @@ int TreeScheduler::begin(const acrobat_trees& tr, int32_t vocab, TreeSchedule& o
     if (tr.tree_off[t + 1] < tr.tree_off[t]) { err = "tree_off is decreasing"; return ACROBAT_EINVAL; }
   const int32_t N = tr.tree_off[tr.n_trees];
   out.n_nodes = N;
+  out.n_trees = tr.n_trees;
   if (N == 0) {
     out.level_nodes.clear(); out.lrow.clear(); out.rrow.clear();
     if (leaf_tokens) leaf_tokens->clear();
@@ -210,6 +212,47 @@ int schedule_trees(const acrobat_trees& tr, int32_t vocab, TreeSchedule& out, st
   }
   s.finish(tr, out);
   return ACROBAT_OK;
+}
+
+void TreeGrouping::stage(const acrobat_trees& trees, const TreeSchedule& s, int32_t groups, int32_t* out, int32_t* left,
+                         int32_t* right, int32_t* off) {
+  const int32_t n_trees = trees.n_trees, N = s.n_nodes;
+  group_.resize((size_t)N);
+  if (groups == 1) {
+    std::fill(group_.begin(), group_.end(), (uint8_t)0);
+  } else {  // counting sort of the trees by descending size
+    int32_t largest = 0;
+    for (int32_t t = 0; t < n_trees; ++t) largest = std::max(largest, trees.tree_off[t + 1] - trees.tree_off[t]);
+    count_.assign((size_t)largest + 2, 0);
+    for (int32_t t = 0; t < n_trees; ++t) ++count_[largest - (trees.tree_off[t + 1] - trees.tree_off[t]) + 1];
+    for (int32_t k = 0; k <= largest; ++k) count_[k + 1] += count_[k];
+    order_.resize((size_t)n_trees);
+    for (int32_t t = 0; t < n_trees; ++t) order_[count_[largest - (trees.tree_off[t + 1] - trees.tree_off[t])]++] = t;
+    for (int32_t r = 0; r < n_trees; ++r) {
+      const int32_t t = order_[r], lap = r / groups, at = r - lap * groups;
+      const int32_t g = lap & 1 ? groups - 1 - at : at;
+      std::fill(group_.begin() + trees.tree_off[t], group_.begin() + trees.tree_off[t + 1], (uint8_t)g);
+    }
+  }
+  for (int32_t g = 0; g < groups; ++g) off[g] = s.level_off[1];
+  for (int32_t lv = 1; lv < s.n_levels; ++lv) {
+    const int32_t p0 = s.level_off[lv], p1 = s.level_off[lv + 1];
+    count_.assign((size_t)groups, 0);
+    for (int32_t p = p0; p < p1; ++p) ++count_[group_[s.level_nodes[p]]];
+    int32_t* const first = off + (size_t)lv * groups;
+    for (int32_t g = 0, run = p0; g < groups; ++g) {
+      first[g] = run;
+      run += count_[g];
+      count_[g] = first[g];
+    }
+    for (int32_t p = p0; p < p1; ++p) {
+      const int32_t id = s.level_nodes[p], at = count_[group_[id]]++;
+      out[at] = id;
+      left[at] = s.lrow[p];
+      right[at] = s.rrow[p];
+    }
+  }
+  off[(size_t)s.n_levels * groups] = N;
 }
 
 int schedule_seqs(int32_t n_seq, const int32_t* len, SeqSchedule& out, std::string& err) {

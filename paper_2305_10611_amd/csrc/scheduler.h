@@ -10,6 +10,7 @@ namespace acrobat {
 
 struct TreeSchedule {
   int32_t n_nodes = 0;
+  int32_t n_trees = 0;
   int32_t n_levels = 0;
   std::vector<int32_t> level_off;    // [n_levels + 1]
   std::vector<int32_t> level_nodes;  // [N] global ids, ascending inside a level
@@ -35,6 +36,22 @@ class TreeScheduler {
   int general_tree(const acrobat_trees& tr, int32_t t, int32_t vocab, std::string& err);
   std::vector<int32_t> depth_, parent_, cursor_, count_;
   std::vector<uint8_t> mark_;  // fast path: "has a parent"; general path: children still to come
+};
+
+// Deals whole trees out to groups that run their internal levels independently of each other, and lists every internal
+// level group by group.  Trees by descending size go to the groups in turn, back and forth (0 .. g-1, g-1 .. 0, ...), so
+// the groups get alike numbers of nodes and alike tallest trees.
+class TreeGrouping {
+ public:
+  // Writes the lists of the internal levels, positions [level_off[1], N): row written, left and right child rows; inside
+  // a level by group, inside a group by ascending id.  off[lv * groups + g] is the first position of group g's share of
+  // level lv >= 1 (entries of level 0: its end), off[n_levels * groups] = N.
+  void stage(const acrobat_trees& trees, const TreeSchedule& s, int32_t groups, int32_t* out, int32_t* left, int32_t* right,
+             int32_t* off);
+
+ private:
+  std::vector<int32_t> order_, count_;
+  std::vector<uint8_t> group_;  // of every node (at most 256 groups)
 };
 
 struct SeqSchedule {

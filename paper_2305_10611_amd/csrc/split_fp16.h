@@ -1,0 +1,69 @@
+// fp32 operands as two fp16 terms for the fp16 matrix cores (device code, gfx950).
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace acrobat {
+namespace {
+
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+
+// exact reciprocal of a power of two with a normal reciprocal
+__device__ __forceinline__ float inverse_power(float s) { return __uint_as_float((254u << 23) - __float_as_uint(s)); }
+
+// power of two that lifts m > 0 to [2^14, 2^15); any power of two does where that one is out of range
+__device__ __forceinline__ float scale_for(float m) {
+  const int e = (int)(__float_as_uint(m) >> 23);
+  if (e == 255) return 1.0f;  // an infinity in the row: its products are computed again in fp32
+  const int s = 268 - e;
+  return __uint_as_float((unsigned)(s > 253 ? 253 : s) << 23);
+}
+
+__device__ __forceinline__ void split4(const floatx4 x, const float s, half4& hi, half4& lo) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    hi[e] = (_Float16)(x[e] * s);
+    lo[e] = (_Float16)__builtin_fmaf(x[e], s, -(float)hi[e]);
+  }
+}
+
+// The same for the eight k of a matrix operand, eight instructions per four elements: the scaled element and its
+// remainder are rounded straight into their half of a packed register.  (The pairs are interleaved because a half written
+// by one instruction must not be read by the next.)
+__device__ __forceinline__ void split4_packed(const floatx4 x, const float s, unsigned (&hi)[2], unsigned (&lo)[2]) {
+  asm("v_fma_mixlo_f16 %0, %4, %8, 0\n\t"
+      "v_fma_mixlo_f16 %1, %6, %8, 0\n\t"
+      "v_fma_mixhi_f16 %0, %5, %8, 0\n\t"
+      "v_fma_mixhi_f16 %1, %7, %8, 0\n\t"
+      "v_fma_mixlo_f16 %2, %4, %8, -%0 op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixlo_f16 %3, %6, %8, -%1 op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixhi_f16 %2, %5, %8, -%0 op_sel:[0,0,1] op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixhi_f16 %3, %7, %8, -%1 op_sel:[0,0,1] op_sel_hi:[0,0,1]\n\t"
+      "s_nop 1"
+      : "=&v"(hi[0]), "=&v"(hi[1]), "=&v"(lo[0]), "=&v"(lo[1])
+      : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(s));
+}
+__device__ __forceinline__ void split8(const floatx4 x0, const floatx4 x1, const float s, half8& hi, half8& lo) {
+  unsigned h0[2], l0[2], h1[2], l1[2];
+  split4_packed(x0, s, h0, l0);
+  split4_packed(x1, s, h1, l1);
+  hi = __builtin_bit_cast(half8, uintx4{h0[0], h0[1], h1[0], h1[1]});
+  lo = __builtin_bit_cast(half8, uintx4{l0[0], l0[1], l1[0], l1[1]});
+}
+
+// largest of the four lanes i, i + 16, i + 32, i + 48, in all of them
+__device__ __forceinline__ float largest_of_quarters(const float m) {
+  const unsigned u = __float_as_uint(m);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned v = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
+  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+__device__ __forceinline__ float largest(const floatx4 v, const float m) {
+  return fmaxf(m, fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
+}
+
+}  // namespace
+}  // namespace acrobat

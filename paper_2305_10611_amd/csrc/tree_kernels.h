@@ -1,0 +1,37 @@
+// Launch interface of the weight-stationary cell kernels (tree_kernels.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "cell_kernels.h"
+
+namespace acrobat {
+
+constexpr int kTreeMaxGroups = 256;
+constexpr int kTreeCounterStride = 32;  // uint32 between two groups' arrival counters (a cache line each)
+constexpr int kStationaryMaxK = 1024;   // columns of the contraction that fit the register files
+
+// Rows [list positions] of one or more levels.  a: the batch as for a level launch, with idx0 / idx1 / out_rows indexed
+// by absolute list position (null: the position itself) and, if off is null, n rows; both segments of a TREE_INTERNAL
+// contraction are rows of src0.
+struct StationaryArgs {
+  CellLevelArgs a;
+  uint32_t src_bytes;      // of src0, at most 2^32 - 512
+  int32_t n_cb;            // workgroups of a group, H / 16
+  int32_t n_groups;
+  // off[lv * n_groups + g]: first list position of group g's share of level lv; levels follow one another, so the entry
+  // behind it is the end of the share.  null: one level of a.n rows, shared evenly.
+  const int32_t* off;
+  int32_t level0, level1;  // levels to run; with more than one the workgroups of a group wait for each other
+  unsigned* counters;      // [n_groups * kTreeCounterStride], zero at launch and again when the launch has completed
+  unsigned* status;
+  int32_t max_polls;
+  unsigned long long* stamps;  // [levels * n_groups] 100 MHz clock at the end of a group's share of a level, or null
+};
+// Groups of H / 16 workgroups that are resident on the current device at once (eight XCDs, a group never crosses one);
+// 0 if the contraction does not fit.
+int stationary_groups(CellEpilogue epi, int32_t H, int32_t K, int32_t n_cu);
+hipError_t launch_stationary(CellEpilogue epi, const StationaryArgs& s, hipStream_t stream, const LaunchEvents& ev = LaunchEvents());
+
+}  // namespace acrobat

@@ -1,0 +1,339 @@
+// Weight-stationary cell kernels for gfx950: a workgroup keeps the weight rows of 16 hidden units (all G gates) in
+// its registers and node rows stream past them, 16 at a time.
+//
+// What this is for.  The level kernels fetch weight tiles again for every node tile: 640 KB of weights per 64 nodes at
+// H = 512, which is what bounds a level of a few hundred nodes, and every level of a tree batch is a launch of its own.
+// Here the weights of a cell are spread over the register files of the H / 16 workgroups of a GROUP - at H = 512 the
+// 32 compute units of one XCD hold all of U, 328 of their 512 KB of registers each - and the only operand that moves
+// is node rows, out of that XCD's L2.  The trees of a batch are dealt out to the groups; a node needs rows of its own
+// tree only, so a group runs all levels of its trees in ONE launch and its workgroups wait for each other between
+// levels (arrival counter, write-through stores, agent-scope loads: the exchange of the persistent recurrences).
+//
+// Contraction.  fp16 matrix cores on split operands (split_fp16.h): weights are split once when they are loaded, node
+// rows on their way into the operand registers.  Wavefront w of NW takes the 32-k steps w, w + NW, ... of the
+// contraction for all G * 16 columns: v_mfma_f32_16x16x32_f16, lane l supplies A[row l % 16][k] and B[k][column l % 16]
+// for k = 4 (l / 16) + 0 .. 3 and 16 more (two loads of 64 contiguous bytes per row and step) and holds
+// z[row 4 (l / 16) + v][column l % 16] in result register v.  A step's registers are requested again for the next
+// rows as soon as they have been split, so a block's rows are under way while the block before it is multiplied.
+// The NW partial sums meet in LDS (two buffers, one barrier per block); with eight wavefronts the threads of one half
+// finish even blocks and those of the other half odd ones, with four - two workgroups then share a compute unit - all
+// threads finish.
+//
+// Bound: the chain of dependent steps.  A level of one block per group takes 3 us (stores complete, arrival counter,
+// rows, 60 matrix instructions per wavefront, sums, gates), against 5 to 15 us for a launch of its own; a further block
+// of 16 rows 2.4 us at H = 512, of which 0.8 us are matrix instructions.  TreeLSTM forward, 256 trees, H = 512: 672 ->
+// 317 us; 64 trees, H = 256: 143 -> 95 us (with the wide leaf levels on the split tiles).  Tried: handing the buffers
+// from wavefront to wavefront with counters in LDS instead of the barrier (117 instead of 99 us on 2 943 rows),
+// a loop per turn so that the waits are exact (171 registers spilled).
+#include "tree_kernels.h"
+
+#include "cell_epilogue.h"
+#include "split_fp16.h"
+
+#include <algorithm>
+#include <atomic>
+#include <type_traits>
+
+namespace acrobat {
+namespace {
+
+constexpr int kZRow = 20;  // padded row of partial sums: the four rows of a result register fall on different banks
+
+// kStates: node rows are states, |h| <= 1, that other workgroups of the launch may have stored (agent-scope loads, one
+// scale for all); else rows of an input matrix (plain loads, a scale for every row and wavefront).
+constexpr int kListRows = 512;  // list positions of a level whose index lists sit in LDS at a time
+
+template <int G, int EPI, int NW, int NS, int RB>
+__global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const StationaryArgs s) {
+  constexpr bool kStates = EPI == EPI_TREE_INTERNAL;
+  constexpr int BR = 16 * RB;         // rows of a block
+  constexpr int ZW = G * BR * kZRow;  // floats of one wavefront's partial sums: [gate][row][column]
+  constexpr int TURNS = NW / 4;       // groups of 256 threads that take turns at finishing a block
+  extern __shared__ __attribute__((aligned(16))) float zbuf[];  // [2][NW][ZW]
+  __shared__ int s_out[kListRows], s_r0[kListRows], s_r1[kStates ? kListRows : 1];  // row written, operand rows
+  __shared__ float s_bias[G][16], s_winv[NW][G][16];
+  __shared__ int s_go;
+
+  // workgroup ids that agree modulo 8 share an XCD (placement only matters for speed)
+  const int slot = blockIdx.x >> 3;
+  const int group = (slot / s.n_cb) * 8 + (blockIdx.x & 7), cb = slot % s.n_cb;
+  if (group >= s.n_groups) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, kq = lane >> 4;
+  const int H = s.a.H, T = (s.a.nseg * s.a.kseg) >> 5;  // 32-k steps, at most NW * NS
+
+  // ---- this wavefront's weights: gate g, unit 16 cb + li, steps w + NW t
+  half8 whi[G][NS], wlo[G][NS];
+  {
+    floatx4 raw[G][NS][2];  // (every load in flight at once)
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const float* row = s.a.W + ((size_t)gate_row<EPI>(g) * H + 16 * cb + li) * (size_t)s.a.ldw + 4 * kq;
+#pragma unroll
+      for (int t = 0; t < NS; ++t) {
+        const int step = w + NW * t;
+        raw[g][t][0] = raw[g][t][1] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (step < T) {
+          raw[g][t][0] = *reinterpret_cast<const floatx4*>(row + 32 * step);
+          raw[g][t][1] = *reinterpret_cast<const floatx4*>(row + 32 * step + 16);
+        }
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      float m = 0.0f;
+#pragma unroll
+      for (int t = 0; t < NS; ++t) m = largest(raw[g][t][1], largest(raw[g][t][0], m));
+      const float sc = scale_for(largest_of_quarters(m));
+      if (lane < 16) s_winv[w][g][li] = inverse_power(sc) * (kStates ? 1.0f / kStateScale : 1.0f);
+      if (w == 0 && lane < 16) s_bias[g][li] = s.a.bias ? s.a.bias[gate_row<EPI>(g) * H + 16 * cb + li] : 0.0f;
+#pragma unroll
+      for (int t = 0; t < NS; ++t) split8(raw[g][t][0], raw[g][t][1], sc, whi[g][t], wlo[g][t]);
+    }
+  }
+
+  // ---- node rows: a ring of the NS steps of one block.  Steps past the contraction range and rows past the last block
+  // are requested past the end of the buffer, which reads zeros: no branch between the matrix instructions.
+  const __amdgpu_buffer_rsrc_t rsrc = agent_buffer(s.a.src0, s.src_bytes);
+  const int steps0 = s.a.kseg >> 5;  // steps of the first segment
+  floatx4 ring[RB][NS][2];
+  unsigned base0[RB], base1[RB];     // byte offset of this lane's part of its row at step 0 (second segment: less kseg)
+  auto request = [&](int r, int t, bool more) {
+    const int step = w + NW * t;
+    unsigned at = (kStates && step >= steps0 ? base1[r] : base0[r]) + 128u * step;
+    at = more && step < T ? at : 0xffffff00u;
+    if constexpr (kStates) {
+      ring[r][t][0] = load_agent_f4(rsrc, at);
+      ring[r][t][1] = load_agent_f4(rsrc, at + 64u);
+    } else {
+      ring[r][t][0] = load_buffer_f4(rsrc, at);
+      ring[r][t][1] = load_buffer_f4(rsrc, at + 64u);
+    }
+  };
+
+  // the elements this thread finishes in its turn: rows er, er + 16, ... of the block, unit j
+  const int turn = TURNS == 2 ? w >> 2 : 0;
+  const int er = (tid & 255) >> 4, eu = tid & 15, j = 16 * cb + eu;
+  unsigned* const counter = s.counters + (size_t)group * kTreeCounterStride;
+  unsigned arrived = 0;  // levels this group has announced
+
+  for (int lv = s.level0; lv < s.level1; ++lv) {
+    int p0, p1;  // the group's share of the level: positions [p0, p1) of the lists
+    if (s.off) {
+      p0 = s.off[lv * s.n_groups + group];
+      p1 = s.off[lv * s.n_groups + group + 1];
+    } else {  // an even share of all rows, in whole blocks
+      const int blocks = (s.a.n + BR - 1) / BR;
+      p0 = BR * (int)((long)blocks * group / s.n_groups);
+      p1 = BR * (int)((long)blocks * (group + 1) / s.n_groups);
+      p1 = p1 < s.a.n ? p1 : s.a.n;
+    }
+    if (p0 >= p1) break;  // (a group's levels only get narrower)
+    bool gone = false;
+    for (; p0 < p1; p0 += kListRows) {
+      const int n = p1 - p0 < kListRows ? p1 - p0 : kListRows, nb = (n + BR - 1) / BR;
+      __syncthreads();  // the lists of the rows before these have been read
+      for (int i = tid; i < BR * nb; i += 64 * NW) {  // tail rows repeat the last node; never stored
+        const int p = p0 + (i < n ? i : n - 1);
+        s_out[i] = s.a.out_rows ? s.a.out_rows[p] : p;
+        s_r0[i] = s.a.idx0 ? s.a.idx0[p] : p;
+        if constexpr (kStates) s_r1[i] = s.a.idx1[p];
+      }
+      // the group's previous level is complete once all its workgroups have announced it
+      if (arrived > 0 && tid == 0) s_go = wait_for(counter, (unsigned)s.n_cb * arrived, s.status, s.max_polls) ? 1 : 0;
+      __syncthreads();
+      if (arrived > 0 && !s_go) { gone = true; break; }
+
+      auto set_rows = [&](int b) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          const int i = BR * b + 16 * r + li;
+          base0[r] = (unsigned)s_r0[i] * (unsigned)s.a.ld0 * 4u + 16u * kq;
+          if constexpr (kStates) base1[r] = (unsigned)s_r1[i] * (unsigned)s.a.ld0 * 4u + 16u * kq - 128u * steps0;
+        }
+      };
+      set_rows(0);
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int t = 0; t < NS; ++t) request(r, t, true);
+      set_rows(nb > 1 ? 1 : 0);
+
+      for (int b = 0; b < nb; ++b) {
+        const bool mine = TURNS == 1 || (b & 1) == turn;
+        const bool more = b + 1 < nb;
+        EpilogueOperands<G, EPI, RB> eo;
+        if (mine) {
+#pragma unroll
+          for (int r = 0; r < RB; ++r) {
+            const int i = BR * b + 16 * r + er;
+            eo.live[r] = i < n;
+            eo.orow[r] = (size_t)s_out[i];
+            if constexpr (EPI == EPI_TREE_INTERNAL) {
+              eo.p0[r] = s.a.cprev_src[(size_t)s_r0[i] * H + j];
+              eo.p1[r] = s.a.cprev_src[(size_t)s_r1[i] * H + j];
+            }
+          }
+        }
+        float* const z = zbuf + (b & 1) * (NW * ZW) + w * ZW;
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          float sc = kStateScale, inv[4];
+          if constexpr (!kStates) {
+            float m = 0.0f;
+#pragma unroll
+            for (int t = 0; t < NS; ++t) m = largest(ring[r][t][1], largest(ring[r][t][0], m));
+            sc = scale_for(largest_of_quarters(m));
+            const float rinv = inverse_power(sc);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) inv[v] = __shfl(rinv, 4 * kq + v);  // (lane i < 16 holds row i)
+          }
+          floatx4 acc[G];
+#pragma unroll
+          for (int g = 0; g < G; ++g) acc[g] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+          for (int t = 0; t < NS; ++t) {
+            half8 ahi, alo;
+            split8(ring[r][t][0], ring[r][t][1], sc, ahi, alo);
+            request(r, t, more);
+#pragma unroll
+            for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(alo, whi[g][t], acc[g], 0, 0, 0);
+#pragma unroll
+            for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ahi, wlo[g][t], acc[g], 0, 0, 0);
+#pragma unroll
+            for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ahi, whi[g][t], acc[g], 0, 0, 0);
+          }
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            const float winv = s_winv[w][g][li];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              float x = acc[g][v] * winv;
+              if constexpr (!kStates) x *= inv[v];
+              z[(g * BR + 16 * r + 4 * kq + v) * kZRow + li] = x;
+            }
+          }
+        }
+        set_rows(b + 2 < nb ? b + 2 : 0);
+        // (a buffer written two blocks ago has been read: its readers have passed the barrier in between)
+        __syncthreads();
+        if (mine) {
+          const float* const zr = zbuf + (b & 1) * (NW * ZW);
+          float zs[G][RB];
+          float finite = 0.0f;
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            eo.bz[g] = s_bias[g][eu];
+#pragma unroll
+            for (int r = 0; r < RB; ++r) {
+              float sum = 0.0f;
+#pragma unroll
+              for (int q = 0; q < NW; ++q) sum += zr[q * ZW + (g * BR + 16 * r + er) * kZRow + eu];
+              zs[g][r] = sum;
+              finite = __builtin_fmaf(sum, 0.0f, finite);
+            }
+          }
+          if (__builtin_expect(finite != 0.0f, 0)) {  // what is not finite is computed in fp32
+#pragma unroll
+            for (int r = 0; r < RB; ++r) {
+              const int i = BR * b + 16 * r + er;
+              const float* const x0 = s.a.src0 + (size_t)s_r0[i] * (size_t)s.a.ld0;
+              const float* const x1 = kStates ? s.a.src0 + (size_t)s_r1[i] * (size_t)s.a.ld0 : x0;
+#pragma unroll
+              for (int g = 0; g < G; ++g) {
+                if (__builtin_isfinite(zs[g][r])) continue;
+                const float* const wr = s.a.W + ((size_t)gate_row<EPI>(g) * H + j) * (size_t)s.a.ldw;
+                float sum = 0.0f;
+#pragma unroll 1
+                for (int k = 0; k < 32 * T && sum == sum; ++k) {
+                  const float* const x = k < s.a.kseg ? x0 + k : x1 + (k - s.a.kseg);
+                  sum = __builtin_fmaf(kStates ? __hip_atomic_load(x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *x, wr[k], sum);
+                }
+                zs[g][r] = sum;
+              }
+            }
+          }
+          epilogue_apply<G, EPI, RB, kStates>(s.a, j, [&](int g, int r) { return zs[g][r]; }, eo);
+        }
+      }
+    }
+    if (gone) break;
+    if (s.stamps && cb == 0 && tid == 0) s.stamps[lv * s.n_groups + group] = wall_clock64();
+    if (lv + 1 < s.level1) {
+      wait_stores_done();  // this wavefront's stores have completed
+      __syncthreads();     // ... and so have the other wavefronts'
+      if (tid == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      ++arrived;
+    }
+  }
+  if (arrived > 0 && tid == 0) leave_block(counter, s.n_cb);
+}
+
+template <int G, int EPI, int NW, int NS>
+struct Stationary {
+  static constexpr int RB = EPI == EPI_TREE_INTERNAL ? 1 : 2;  // five gates leave no registers for a second 16 rows
+  static constexpr size_t kLdsBytes = (size_t)2 * NW * G * 16 * RB * kZRow * sizeof(float);
+  static const void* kernel() { return reinterpret_cast<const void*>(&cell_stationary_kernel<G, EPI, NW, NS, RB>); }
+  // More than 64 KB of dynamic LDS has to be asked for once per device (one bit per device id; two threads that both
+  // find the bit clear both set the attribute, which is harmless).
+  static hipError_t configure() {
+    if (kLdsBytes <= 60 * 1024) return hipSuccess;
+    static std::atomic<uint64_t> configured{0};
+    int dev = 0;
+    if (const hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+    const uint64_t bit = 1ull << (dev & 63);
+    if (dev < 64 && (configured.load(std::memory_order_acquire) & bit)) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(kernel(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+    if (e == hipSuccess && dev < 64) configured.fetch_or(bit, std::memory_order_release);
+    return e;
+  }
+  static hipError_t launch(const StationaryArgs& s, hipStream_t stream, const LaunchEvents& ev) {
+    if (const hipError_t e = configure(); e != hipSuccess) return e;
+    const unsigned grid = 8u * (unsigned)s.n_cb * (unsigned)((s.n_groups + 7) / 8);
+    launch_with_events((cell_stationary_kernel<G, EPI, NW, NS, RB>), dim3(grid), dim3(64 * NW), kLdsBytes, stream, ev.start, ev.stop, s);
+    return hipGetLastError();
+  }
+  // workgroups of this kernel that a compute unit holds (0: the query failed)
+  static int per_cu() {
+    int n = 0;
+    if (configure() != hipSuccess || hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel(), 64 * NW, kLdsBytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return 0;
+    }
+    return n;
+  }
+};
+
+// Calls f with the Stationary of the smallest instance that holds K columns: four wavefronts (two workgroups per
+// compute unit) up to K = 512, eight up to 1 024.
+template <int G, int EPI, class F>
+auto dispatch_steps(int32_t K, F&& f) {
+  if (K <= 128) return f(Stationary<G, EPI, 4, 1>());
+  if (K <= 256) return f(Stationary<G, EPI, 4, 2>());
+  if (K <= 512) return f(Stationary<G, EPI, 4, 4>());
+  if (K <= 768) return f(Stationary<G, EPI, 8, 3>());
+  return f(Stationary<G, EPI, 8, 4>());
+}
+template <class F>
+auto dispatch(CellEpilogue epi, int32_t K, F&& f) {
+  switch (epi) {
+    case EPI_TREE_LEAF: return dispatch_steps<3, EPI_TREE_LEAF>(K, f);
+    case EPI_STORE_Z: return dispatch_steps<4, EPI_STORE_Z>(K, f);
+    default: return dispatch_steps<5, EPI_TREE_INTERNAL>(K, f);
+  }
+}
+
+}  // namespace
+
+int stationary_groups(CellEpilogue epi, int32_t H, int32_t K, int32_t n_cu) {
+  if ((epi != EPI_TREE_LEAF && epi != EPI_TREE_INTERNAL && epi != EPI_STORE_Z) || K <= 0 || K > kStationaryMaxK || H <= 0 || H % 16)
+    return 0;
+  const int per_xcd = dispatch(epi, K, [](auto k) { return decltype(k)::per_cu(); }) * (n_cu / 8);
+  return 8 * std::min(per_xcd / (H / 16), kTreeMaxGroups / 8);
+}
+
+hipError_t launch_stationary(CellEpilogue epi, const StationaryArgs& s, hipStream_t stream, const LaunchEvents& ev) {
+  return dispatch(epi, s.a.nseg * s.a.kseg, [&](auto k) { return decltype(k)::launch(s, stream, ev); });
+}
+
+}  // namespace acrobat

@@ -1,0 +1,160 @@
+"""Cells on the fp16 matrix cores with split operands (weight-stationary kernels, split tiles) against the oracle, at the
+sizes where they can go wrong, and no less exact than fp32.
+
+Tolerance: an fp32 pre-activation of K terms of alike size has a relative error of about sqrt(K) 2^-24, 2e-6 at
+K = 1 024, and the gates pass it on at most once more per level; 1e-6 over the 2-norm of all states is what the
+fp32 kernels stay below (they measure 3e-7 to 5e-7)."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import generators as gen
+
+pytestmark = pytest.mark.gpu
+
+NT = oracle.default_threads()
+
+
+def rel(got, want):
+    want = want.astype(np.float64)
+    return float(np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want))
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_2305_10611_amd as A
+    c = A.Context(0)
+    yield c
+    c.close()
+
+
+# 2H = 64 .. 1 024 covers every instance (4 wavefronts up to 512 columns, 8 above), contraction steps that do not divide
+# evenly among the wavefronts, groups that leave compute units of an XCD empty; D below, at and above what fits
+@pytest.mark.parametrize("H,D,n,lo,hi", [(32, 32, 1, 1, 1), (32, 96, 3, 2, 2), (64, 64, 9, 1, 40), (160, 1024, 33, 1, 17),
+                                         (192, 544, 300, 1, 9), (256, 1056, 70, 3, 30), (288, 160, 8, 16, 33),
+                                         (352, 768, 17, 2, 60), (512, 512, 40, 5, 20), (512, 32, 2, 300, 400)])
+def test_tree_levels_in_one_launch(ctx, H, D, n, lo, hi):
+    from tests import parity as P
+    import paper_2305_10611_amd as A
+    w = gen.treelstm_workload(n, lo, hi, H, 50, "uniform", seed=H + n, bias_scale=0.2, D=D)
+    w, _ = gen.relabel_trees(w, gen.make_rng(H), extra={"token": w["token"]})
+    h, c = P.run_treelstm(ctx, w)
+    assert ctx.acrobat_device_status() == A.OK
+    oh, oc = oracle.treelstm(w, nthreads=NT)
+    assert rel(h, oh) < 1e-6 and rel(c, oc) < 1e-6
+    # and level by level: what a captured call launches (here: with explicit gathers in between)
+    ctx.acrobat_set_gather_fusion(False)
+    try:
+        h1, c1 = P.run_treelstm(ctx, w)
+    finally:
+        ctx.acrobat_set_gather_fusion(True)
+    assert np.array_equal(h, h1) and np.array_equal(c, c1)
+    h2, c2 = P.run_treelstm(ctx, w)  # the counters are back at zero
+    assert np.array_equal(h, h2) and np.array_equal(c, c2)
+
+
+def test_more_rows_of_a_level_than_the_lists_in_lds_hold(ctx):
+    from tests import parity as P
+    w = gen.treelstm_workload(2, 3000, 3300, 64, 50, "uniform", seed=5, bias_scale=0.2)  # two groups, about 1 000 rows each
+    h, c = P.run_treelstm(ctx, w)
+    oh, oc = oracle.treelstm(w, nthreads=NT)
+    assert rel(h, oh) < 1e-6 and rel(c, oc) < 1e-6
+
+
+@pytest.mark.parametrize("H,D,n", [(544, 96, 400), (544, 544, 700), (608, 64, 300)])
+def test_split_tiles_of_hidden_sizes_beyond_the_register_files(ctx, H, D, n):
+    """K = 2H > 1 024: levels of at least 128 tiles of 64 nodes x 32 units, ragged last tiles, unit tiles not a multiple of four."""
+    from tests import parity as P
+    w = gen.treelstm_workload(n, 2, 9, H, 50, "uniform", seed=H + n, bias_scale=0.2, D=D)
+    level_off, _ = (P.run_treelstm(ctx, w), ctx.acrobat_last_schedule())[1]
+    assert (int(level_off[2] - level_off[1]) + 63) // 64 * (H // 32) >= 128
+    h, c = P.run_treelstm(ctx, w)
+    oh, oc = oracle.treelstm(w, nthreads=NT)
+    assert rel(h, oh) < 1e-6 and rel(c, oc) < 1e-6
+
+
+def test_wide_leaf_levels_take_the_split_tiles(ctx):
+    from tests import parity as P
+    w = gen.treelstm_workload(1000, 2, 33, 128, 300, "uniform", seed=3, bias_scale=0.2, D=64)
+    assert (w["left"] < 0).sum() > 64 * 256  # four rounds of tiles
+    h, c = P.run_treelstm(ctx, w)
+    oh, oc = oracle.treelstm(w, nthreads=NT)
+    assert rel(h, oh) < 1e-6 and rel(c, oc) < 1e-6
+
+
+@pytest.mark.parametrize("H,D,n,hi", [(64, 32, 150, 60), (96, 608, 100, 90), (256, 96, 60, 100)])
+def test_lstm_input_transform(ctx, H, D, n, hi):
+    from tests import parity as P
+    s = gen.lstm_workload(n, 0, hi, H, D, seed=H + D, bias_scale=0.2)
+    h, c = P.run_lstm(ctx, s)
+    oh, oc = oracle.varlen_lstm(s, nthreads=NT)
+    assert rel(h, oh) < 1e-6 and rel(c, oc) < 1e-6
+
+
+@pytest.mark.parametrize("scale", [1e-20, 1e-6, 1.0, 3e4, 1e18])
+def test_row_scales_follow_the_inputs(ctx, scale):
+    """Embedding rows and weights of any magnitude keep their precision: the product stays of order one."""
+    from tests import parity as P
+    w = gen.treelstm_workload(40, 2, 30, 96, 100, "uniform", seed=17, bias_scale=0.2, D=64)
+    rows = np.float32(scale) * np.linspace(0.5, 2.0, 100, dtype=np.float32)[:, None]
+    w["emb"] = (w["emb"] * rows).astype(np.float32)
+    w["W_leaf"] = (w["W_leaf"] / np.float32(scale)).astype(np.float32)
+    h, c = P.run_treelstm(ctx, w)
+    oh, oc = oracle.treelstm(w, nthreads=NT)
+    assert rel(h, oh) < 1e-6 and rel(c, oc) < 1e-6
+
+
+@pytest.mark.parametrize("n,H,D", [(20, 64, 64), (1000, 128, 64)])  # stationary kernel; leaves on split tiles
+def test_infinities_and_nans_say_what_fp32_says(ctx, n, H, D):
+    from tests import parity as P
+    w = gen.treelstm_workload(n, 2, 33, H, 300, "uniform", seed=3, bias_scale=0.2, D=D)
+    w["emb"][5, 3], w["emb"][6, 0], w["emb"][7, 1] = np.inf, -np.inf, np.nan
+    w["emb"][8, :] = 3e38
+    w["U"][2 * H + 1, 4] = np.inf    # f_r gate of unit 1: forget everything or nothing
+    h, c = P.run_treelstm(ctx, w)
+    ctx.acrobat_set_persistent(False)
+    ctx.check(ctx.acrobat_set_tuning(64, 1, 0))  # the fp32 tiles
+    try:
+        h32, c32 = P.run_treelstm(ctx, w)
+    finally:
+        ctx.check(ctx.acrobat_set_tuning(0, 0, 0))
+        ctx.acrobat_set_persistent(True)
+    assert np.isnan(h32).any() and np.isfinite(h32).any()
+    for got, want in ((h, h32), (c, c32)):
+        assert np.array_equal(np.isfinite(got), np.isfinite(want))
+        fine = np.isfinite(want)
+        assert np.abs(got[fine] - want[fine]).max() < 1e-4
+
+
+def test_a_wait_that_runs_out_is_reported_and_the_next_call_is_whole():
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    w = gen.treelstm_workload(20, 4, 30, 128, 60, "uniform", seed=4, bias_scale=0.2)
+    for name in ("acrobat_treelstm_forward", "acrobat_treelstm_forward_noalloc"):
+        c = A.Context(0)
+        try:
+            c.acrobat_treelstm_forward = getattr(c, name)
+            assert c.acrobat_set_persistent(True, 0) == A.OK
+            P.run_treelstm(c, w)  # synchronises
+            assert c.acrobat_device_status() == A.ETIMEOUT
+            assert c.acrobat_set_persistent(True, -1) == A.OK
+            h, cc = P.run_treelstm(c, w)
+            assert c.acrobat_device_status() == A.OK
+            oh, oc = oracle.treelstm(w, nthreads=NT)
+            assert rel(h, oh) < 1e-6 and rel(cc, oc) < 1e-6
+        finally:
+            c.close()
+
+
+def test_profiling_times_every_level_of_the_one_launch(ctx):
+    from tests import parity as P
+    w = gen.treelstm_workload(50, 3, 30, 256, 60, "uniform", seed=4, bias_scale=0.2)
+    ctx.acrobat_set_profiling(True)
+    try:
+        P.run_treelstm(ctx, w)
+        rec = ctx.acrobat_last_profile()
+    finally:
+        ctx.acrobat_set_profiling(False)
+    level_off, _ = ctx.acrobat_last_schedule()
+    assert [r[1] for r in rec] == list(range(len(level_off) - 1)) and [r[2] for r in rec] == list(np.diff(level_off))
+    assert all(r[3] > 0 for r in rec)
