@@ -96,6 +96,12 @@ hipError_t order_waiting_launch(int device, hipStream_t stream) {
 }
 }  // namespace
 
+// A profiled launch that stamped the clock level by level: its record, the levels it ran, and their sizes.
+struct StampedLaunch {
+  int32_t record = -1, level0 = 0, level1 = 0, groups = 0, directions = 1;
+  const int32_t* level_off = nullptr;
+};
+
 struct acrobat_ctx {
   int device = 0;
   std::string err;
@@ -145,6 +151,7 @@ struct acrobat_ctx {
   unsigned* h_status = nullptr;     // pinned host word that a kernel raises when one of its waits runs out
   TreeGrouping tree_groups;         // of the last tree launch; keeps its buffers
   bool tree_sync_dirty = false;     // the same for splitk.counters and the tree launches
+  StampedLaunch stamped;            // profiling: of the call in progress
   unsigned long long* d_stamps = nullptr;  // profiling: clock at the end of every group's share of a level
   size_t stamps_cap = 0;
   bool sync_dirty = false;          // the arrival counters in d_sync may be non-zero: clear them before the next persistent recurrence
@@ -365,6 +372,7 @@ int begin_call(acrobat_ctx* ctx) {
   if (!ctx) return ACROBAT_EINVAL;
   ctx->err.clear();
   ctx->records.clear();
+  ctx->stamped = StampedLaunch();
   ctx->last_off = &ctx->level_off;
   ctx->last_nodes = &ctx->level_nodes;
   HIP_TRY(ctx, hipSetDevice(ctx->device));
@@ -642,28 +650,33 @@ int reserve_stamps(acrobat_ctx* ctx, size_t n, hipStream_t stream, unsigned long
   return ACROBAT_OK;
 }
 
-// Profiling: the record of the one launch for all internal levels becomes one record per level.  A level ends when the
-// last group is through with it (clock stamps of the launch); the first level also gets what came before it.
-int level_records(acrobat_ctx* ctx, const TreeSchedule& s, int32_t groups) {
-  std::vector<unsigned long long> t((size_t)s.n_levels * groups);
+// Profiling: ends the call's timing, and the record of a launch with clock stamps (ctx->stamped) becomes one record per
+// level.  A level ends when the last group is through with it; the first level also gets what came before it.
+int finish_stamped(acrobat_ctx* ctx, LaunchTimer& timer) {
+  TRY(timer.finish());
+  const StampedLaunch st = ctx->stamped;
+  ctx->stamped = StampedLaunch();
+  if (st.record < 0) return ACROBAT_OK;
+  std::vector<unsigned long long> t((size_t)st.level1 * st.groups);
   HIP_TRY(ctx, hipMemcpy(t.data(), ctx->d_stamps, t.size() * sizeof(t[0]), hipMemcpyDeviceToHost));
-  const acrobat_launch_record whole = ctx->records.back();
-  ctx->records.pop_back();
-  const int32_t first = (int32_t)ctx->records.size();
+  const acrobat_launch_record whole = ctx->records[st.record];
+  std::vector<acrobat_launch_record> levels;
   float later = 0.0f;
   unsigned long long before = 0;
-  for (int32_t lv = 1; lv < s.n_levels; ++lv) {
-    const auto* row = t.data() + (size_t)lv * groups;
-    const unsigned long long end = std::max(before + 1, *std::max_element(row, row + groups));
+  for (int32_t lv = st.level0; lv < st.level1; ++lv) {
+    const auto* row = t.data() + (size_t)lv * st.groups;
+    const unsigned long long end = std::max(before + 1, *std::max_element(row, row + st.groups));
     acrobat_launch_record r = whole;
     r.level = lv;
-    r.n = s.level_off[lv + 1] - s.level_off[lv];
-    r.ms = lv == 1 ? 0.0f : (float)(end - before) * 1e-5f;  // 100 MHz
+    r.n = st.directions * (st.level_off[lv + 1] - st.level_off[lv]);
+    r.ms = lv == st.level0 ? 0.0f : (float)(end - before) * 1e-5f;  // 100 MHz
     later += r.ms;
     before = end;
-    ctx->records.push_back(r);
+    levels.push_back(r);
   }
-  ctx->records[first].ms = std::max(whole.ms - later, 1e-5f);
+  levels[0].ms = std::max(whole.ms - later, 1e-5f);
+  ctx->records.erase(ctx->records.begin() + st.record);
+  ctx->records.insert(ctx->records.begin() + st.record, levels.begin(), levels.end());
   return ACROBAT_OK;
 }
 
@@ -881,7 +894,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
         HIP_TRY(ctx, launch_split_rows(split_rows, stream, first));
       }
       if (lv == 0 && plan.leaf) {
-        sa.a = a;
+        sa.a[0] = a;
         sa.src_bytes = (uint32_t)((size_t)(unfused ? n : V) * D * sizeof(float));
         sa.n_groups = std::min(plan.leaf, (n + 15) / 16);
         sa.level0 = 0; sa.level1 = 1;
@@ -891,8 +904,8 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
         continue;
       }
       if (lv > 0 && plan.groups > 0) {
-        sa.a = a;  // lists by absolute position
-        sa.a.idx0 -= off; sa.a.idx1 -= off; sa.a.out_rows -= off;
+        sa.a[0] = a;  // lists by absolute position
+        sa.a[0].idx0 -= off; sa.a[0].idx1 -= off; sa.a[0].out_rows -= off;
         sa.src_bytes = (uint32_t)((size_t)(unfused ? 2 * n : N) * H * sizeof(float));
         sa.n_groups = plan.groups;
         sa.off = d_idx + 3 * (size_t)N + n_iota;
@@ -906,9 +919,8 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
         HIP_TRY(ctx, launch_stationary(EPI_TREE_INTERNAL, sa, stream, timer.ev));
         TRY(timer.end());
         if (!one_launch) continue;
-        TRY(timer.finish());
-        if (sa.stamps) TRY(level_records(ctx, s, plan.groups));
-        return ACROBAT_OK;
+        if (sa.stamps) ctx->stamped = {(int32_t)ctx->records.size() - 1, 1, s.n_levels, plan.groups, 1, s.level_off.data()};
+        return finish_stamped(ctx, timer);
       }
       HIP_TRY(ctx, launch_cell_level(lv == 0 ? EPI_TREE_LEAF : EPI_TREE_INTERNAL, a, stream, ws,
                                      timer.tile(), timer.ksplit(), timer.ev));
@@ -920,6 +932,60 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
   } catch (...) {
     return fail(ctx, ACROBAT_EINVAL, "unexpected exception");
   }
+}
+
+// Groups a recurrence over sequences is dealt out to for one launch of the stationary kernel; 0: not on that kernel.
+struct SeqPlan {
+  int32_t groups = 0;
+  bool whole = false;  // one launch record for all steps (else one per step)
+};
+
+SeqPlan plan_recurrence(const acrobat_ctx* ctx, CellEpilogue epi, int32_t H, int32_t R, int32_t n_live, int32_t n_steps,
+                        int32_t directions) {
+  SeqPlan p;
+  if (!ctx->persistent || ctx->splitk.force_bm || H < 128 || n_steps < 2 || (double)R * H * sizeof(float) >= 4294967296.0 - 512.0)
+    return p;
+  // The kernels that were made for H = 128 and 256 step faster there, as does the one for the BiRNN at all its sizes
+  // (LSTM, 256 sequences of 1 to 100 steps: H = 128 216 against 262 us, H = 256 283 against 293, H = 512 443 against 393;
+  // BiRNN, H = 512, 64 sequences 87 against 119).  Below H = 128 a step is a launch of 4 us.
+  int32_t most = stationary_groups(epi, H, H, ctx->n_cu) / directions;
+  // A single gate leaves room for four workgroups per compute unit, but more than one only get in each other's way
+  // (600 sequences, H = 256: all steps 187, 143 and 137 us with four, two and one; H = 128, 1 000 sequences 115, 96, 106).
+  if (epi == EPI_RNN_STEP) most = std::min(most, 8 * ((H < 256 ? 64 : 32) / (H / 16)) / directions);
+  p.groups = directions * std::min({most, (n_live + 15) / 16, (int32_t)((4 * (int64_t)R + 4096) / n_steps)});
+  p.whole = epi == EPI_LSTM_STEP && H == 512 && n_live <= 256;  // (larger batches have always been reported step by step)
+  return p;
+}
+
+// The steps of a recurrence, lists and offset table staged and uploaded (sa.off): one launch, or one per step while the
+// stream is being captured.  step_off[t + 1] - step_off[t]: nodes of step t, per direction.
+int run_recurrence(acrobat_ctx* ctx, CellEpilogue epi, StationaryArgs& sa, const SeqPlan& plan, int32_t n_steps,
+                   const int32_t* step_off, int32_t directions, int32_t R, LaunchTimer& timer) {
+  const int32_t H = sa.a[0].H;
+  sa.src_bytes = (uint32_t)((size_t)R * H * sizeof(float));
+  sa.n_cb = H / 16;
+  sa.n_groups = plan.groups;
+  sa.counters = ctx->splitk.counters;
+  sa.status = ctx->h_status_dev;
+  sa.max_polls = ctx->max_polls == kDefaultMaxPolls ? kTreeMaxPolls : ctx->max_polls;
+  const bool one_launch = !stream_is_capturing(timer.stream);
+  const int32_t step_kind = epi == EPI_LSTM_STEP ? ACROBAT_K_LSTM_STEP : ACROBAT_K_RNN_STEP;
+  const int32_t whole_kind = epi == EPI_LSTM_STEP ? ACROBAT_K_LSTM_PERSISTENT : ACROBAT_K_RNN_PERSISTENT;
+  for (int32_t t = 0; t < n_steps; t += one_launch ? n_steps : 1) {
+    sa.level0 = t;
+    sa.level1 = one_launch ? n_steps : t + 1;
+    const int32_t n = plan.whole ? directions * R : directions * (step_off[t + 1] - step_off[t]);
+    TRY(timer.begin(plan.whole ? whole_kind : step_kind, t, n));
+    if (timer.tile()) *timer.tile() = 16;
+    if (one_launch) {
+      TRY(order_and_clean(ctx, sa, false, timer.stream));
+      if (timer.on() && !plan.whole) TRY(reserve_stamps(ctx, (size_t)n_steps * plan.groups, timer.stream, &sa.stamps));
+    }
+    HIP_TRY(ctx, launch_stationary(epi, sa, timer.stream, timer.ev));
+    TRY(timer.end());
+  }
+  if (sa.stamps) ctx->stamped = {(int32_t)ctx->records.size() - 1, 0, n_steps, plan.groups, directions, step_off};
+  return directions == 1 ? finish_stamped(ctx, timer) : ACROBAT_OK;
 }
 
 }  // namespace
@@ -1120,6 +1186,29 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
     // One launch for the whole recurrence where the shape allows it: the steps are the same batches in the
     // same order, executed by workgroups that keep W_h on chip and synchronise among themselves.
     const int32_t n_live = s.level_off[1];  // sequences with at least one step
+    {
+      const SeqPlan plan = (H == 128 || H == 256) && n_live <= kLstmSlots * kLstmMaxBlocks
+                               ? SeqPlan() : plan_recurrence(ctx, EPI_LSTM_STEP, H, R, n_live, s.n_levels, 1);
+      if (plan.groups > 0) {
+        const size_t n_off = (size_t)s.n_levels * plan.groups + 1;
+        TRY(reserve_indices(ctx, 2 * (size_t)R + n_off, stream));
+        int32_t* st = ctx->h_stage;
+        stage_seq_groups(n_seq, len, s.n_levels, plan.groups, 1, st, st + R, st + 2 * (size_t)R);
+        TRY(upload_indices(ctx, 2 * (size_t)R + n_off, stream));
+        LaunchTimer timer{ctx, stream};
+        TRY(input_transform(timer));
+        StationaryArgs sa{};
+        CellLevelArgs& a = sa.a[0];
+        a.n = R; a.H = H; a.nseg = 1; a.kseg = H;
+        a.src0 = d_h; a.ld0 = H; a.idx0 = ctx->d_idx + R; a.out_rows = ctx->d_idx;
+        a.h = d_h; a.c = d_c; a.cprev_src = d_c;
+        a.zadd = ctx->d_scratch;
+        a.W = d_Wh; a.ldw = H;
+        a.first = d_h;  // (nothing of it is read: zero states before the first step)
+        sa.off = ctx->d_idx + 2 * (size_t)R;
+        return run_recurrence(ctx, EPI_LSTM_STEP, sa, plan, s.n_levels, s.level_off.data(), 1, R, timer);
+      }
+    }
     const int32_t slots = kLstmSlots;
     const int32_t n_blocks = (n_live + slots - 1) / slots;
     if (ctx->persistent && s.n_levels >= 2 && (double)R * H * sizeof(float) < 4294967296.0 &&
@@ -1260,7 +1349,14 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
     const bool persistent = ctx->persistent && T >= 2 && (double)R * H * sizeof(float) < 4294967296.0 &&
                             rnn_persistent_eligible(H, 2 * blocks_per_dir, nullptr);
     const size_t n_slots = (size_t)blocks_per_dir * kRnnSlots;
-    if (persistent) {
+    const SeqPlan plan = persistent ? SeqPlan() : plan_recurrence(ctx, EPI_RNN_STEP, H, R, n_live, T, 2);
+    if (plan.groups > 0) {
+      const size_t n_off = (size_t)T * plan.groups + 1;
+      TRY(reserve_indices(ctx, 4 * (size_t)R + n_off, stream));
+      int32_t* st = ctx->h_stage;
+      stage_seq_groups(n_seq, len, T, plan.groups, 2, st, st + 2 * (size_t)R, st + 4 * (size_t)R);
+      TRY(upload_indices(ctx, 4 * (size_t)R + n_off, stream));
+    } else if (persistent) {
       TRY(reserve_sync(ctx, stream));
       TRY(reserve_indices(ctx, 2 * n_slots, stream));
       int32_t* st = ctx->h_stage;
@@ -1328,7 +1424,22 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
                                           timer.ev));
       TRY(timer.end());
     }
-    if (persistent) {
+    if (plan.groups > 0) {
+      StationaryArgs sa{};
+      sa.two = 1;
+      sa.first_bytes = (uint32_t)(H * sizeof(float));
+      for (int dir = 0; dir < 2; ++dir) {
+        CellLevelArgs& a = sa.a[dir];
+        a.n = 2 * R; a.H = H; a.nseg = 1; a.kseg = H;
+        a.src0 = hdir[dir]; a.ld0 = H; a.idx0 = ctx->d_idx + 2 * (size_t)R; a.out_rows = ctx->d_idx;
+        a.W = par[dir]->Wh; a.ldw = H;
+        a.zadd = xp[dir];
+        a.h = hdir[dir];
+        a.first = par[dir]->h_init;
+      }
+      sa.off = ctx->d_idx + 4 * (size_t)R;
+      TRY(run_recurrence(ctx, EPI_RNN_STEP, sa, plan, T, s.fwd_off.data(), 2, R, timer));
+    } else if (persistent) {
       RnnPersistentArgs pa{};
       pa.n_blocks = 2 * blocks_per_dir; pa.H = H;
       pa.slot_row0 = ctx->d_idx; pa.slot_len = ctx->d_idx + n_slots;
@@ -1343,7 +1454,7 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
       HIP_TRY(ctx, launch_rnn_persistent(pa, stream, timer.ev));
       TRY(timer.end());
     }
-    for (int32_t k = 0; k < (persistent ? 0 : T); ++k) {
+    for (int32_t k = 0; k < (persistent || plan.groups > 0 ? 0 : T); ++k) {
       const int32_t off = s.fwd_off[k], n = s.fwd_off[k + 1] - off;
       CellLevelArgs a[2] = {};
       for (int dir = 0; dir < 2; ++dir) {
@@ -1373,7 +1484,7 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
       HIP_TRY(ctx, launch_cell_level(EPI_RELU_OUT, a, stream, ctx->splitk, timer.tile(), timer.ksplit(), timer.ev));
       TRY(timer.end());
     }
-    return timer.finish();
+    return finish_stamped(ctx, timer);
   } catch (const std::bad_alloc&) {
     return fail(ctx, ACROBAT_ENOMEM, "host allocation failed");
   } catch (...) {

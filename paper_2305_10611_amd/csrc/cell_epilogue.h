@@ -102,7 +102,7 @@ __device__ __forceinline__ void epilogue_fetch(const CellLevelArgs& a, const int
   }
 }
 
-// kShared: h is read by other workgroups of the same launch, so the tree cells store it at agent scope.
+// kShared: h is read by other workgroups of the same launch, so it is stored at agent scope.
 template <bool kShared>
 __device__ __forceinline__ void store_h(float* p, float v) {
   if constexpr (kShared) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -142,7 +142,7 @@ __device__ __forceinline__ void epilogue_apply(const CellLevelArgs& a, const int
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       if (!o.live[v]) continue;
-      a.h[o.orow[v] * H + j] = fast_sigmoid(acc(0, v) + o.p0[v] + bz[0]);
+      store_h<kShared>(a.h + o.orow[v] * H + j, fast_sigmoid(acc(0, v) + o.p0[v] + bz[0]));
     }
   } else if constexpr (EPI == EPI_RELU_OUT) {
     if (j < a.n_cols) {
@@ -159,7 +159,7 @@ __device__ __forceinline__ void epilogue_apply(const CellLevelArgs& a, const int
       const float c = fast_sigmoid(acc(1, v) + o.zx[1][v] + bz[1]) * o.p0[v] +
                       fast_sigmoid(acc(0, v) + o.zx[0][v] + bz[0]) * fast_tanh(acc(3, v) + o.zx[3][v] + bz[3]);
       a.c[o.orow[v] * H + j] = c;
-      a.h[o.orow[v] * H + j] = fast_sigmoid(acc(2, v) + o.zx[2][v] + bz[2]) * fast_tanh(c);
+      store_h<kShared>(a.h + o.orow[v] * H + j, fast_sigmoid(acc(2, v) + o.zx[2][v] + bz[2]) * fast_tanh(c));
     }
   }
 }

@@ -25,7 +25,7 @@ constexpr int kPersistSyncWords = kPersistFlagWords + kPersistMaxBlocks * kPersi
 // counter; blocks never wait for each other.
 struct LstmPersistentArgs {
   int32_t n_blocks;          // node blocks in use, 1 .. kLstmMaxBlocks
-  int32_t H;                 // hidden size (the kernel is instantiated for 128, 256 and 512)
+  int32_t H;                 // hidden size (the kernel is instantiated for 128 and 256)
   const int32_t* slot_row0;  // [n_blocks * 16] first arena row of the slot's sequence
   const int32_t* slot_len;   // [n_blocks * 16] its length, non-increasing inside a block, 0 = empty slot
   const float* Wh;           // [4H, H], gate order (i, f, o, u)

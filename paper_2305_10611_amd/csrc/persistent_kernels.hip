@@ -475,7 +475,6 @@ bool lstm_persistent_eligible(int32_t H, int32_t n_blocks, const char** why) {
   switch (H) {
     case 128: ok = resident_at_once<128>(nbp * 8); break;
     case 256: ok = resident_at_once<256>(nbp * 16); break;
-    case 512: ok = resident_at_once<512>(nbp * 32); break;
     default: *why = "hidden size not instantiated"; return false;
   }
   if (!ok) *why = "the workgroups would not all be resident at once";
@@ -486,7 +485,6 @@ hipError_t launch_lstm_persistent(const LstmPersistentArgs& a, hipStream_t strea
   switch (a.H) {
     case 128: return launch_lstm_h<128>(a, stream, ev);
     case 256: return launch_lstm_h<256>(a, stream, ev);
-    case 512: return launch_lstm_h<512>(a, stream, ev);
   }
   return hipErrorInvalidValue;
 }

@@ -255,6 +255,44 @@ void TreeGrouping::stage(const acrobat_trees& trees, const TreeSchedule& s, int3
   off[(size_t)s.n_levels * groups] = N;
 }
 
+void stage_seq_groups(int32_t n_seq, const int32_t* len, int32_t n_steps, int32_t groups, int32_t directions, int32_t* out,
+                      int32_t* prev, int32_t* off) {
+  // ranks by descending length (counting sort), dealt out to groups / directions lists
+  const int32_t lists = groups / directions;
+  std::vector<int32_t> first((size_t)n_steps + 2, 0), row0;
+  int32_t n_live = 0;
+  for (int32_t q = 0; q < n_seq; ++q)
+    if (len[q] > 0) { ++first[n_steps - len[q] + 1]; ++n_live; }
+  for (int32_t k = 0; k <= n_steps; ++k) first[k + 1] += first[k];
+  std::vector<int32_t> order((size_t)n_live);
+  row0.resize((size_t)n_seq);
+  for (int32_t q = 0, row = 0; q < n_seq; ++q) {
+    row0[q] = row;
+    row += std::max(len[q], 0);
+    if (len[q] > 0) order[first[n_steps - len[q]]++] = q;
+  }
+  std::vector<std::vector<int32_t>> member((size_t)lists);
+  for (int32_t r = 0; r < n_live; ++r) {
+    const int32_t lap = r / lists, at = r - lap * lists;
+    member[lap & 1 ? lists - 1 - at : at].push_back(order[r]);  // (descending length inside a list)
+  }
+  int32_t p = 0;
+  for (int32_t t = 0; t < n_steps; ++t)
+    for (int32_t g = 0; g < groups; ++g) {
+      off[(size_t)t * groups + g] = p;
+      std::vector<int32_t>& m = member[directions == 2 ? g >> 1 : g];
+      const bool backward = directions == 2 && (g & 1);
+      if (!(directions == 2 && backward))
+        while (!m.empty() && len[m.back()] <= t) m.pop_back();
+      for (const int32_t q : m) {
+        out[p] = backward ? row0[q] + len[q] - 1 - t : row0[q] + t;
+        prev[p] = t == 0 ? 0 : backward ? out[p] + 1 : out[p] - 1;
+        ++p;
+      }
+    }
+  off[(size_t)n_steps * groups] = p;
+}
+
 int schedule_seqs(int32_t n_seq, const int32_t* len, SeqSchedule& out, std::string& err) {
   out = SeqSchedule();
   out.level_off.assign(1, 0);

@@ -14,9 +14,11 @@ constexpr int kStationaryMaxK = 1024;   // columns of the contraction that fit t
 
 // Rows [list positions] of one or more levels.  a: the batch as for a level launch, with idx0 / idx1 / out_rows indexed
 // by absolute list position (null: the position itself) and, if off is null, n rows; both segments of a TREE_INTERNAL
-// contraction are rows of src0.
+// contraction are rows of src0.  LSTM_STEP and RNN_STEP: idx0 names the row of the previous step.
 struct StationaryArgs {
-  CellLevelArgs a;
+  CellLevelArgs a[2];
+  int32_t two;             // != 0: odd groups work with a[1] (the two directions of a bidirectional recurrence)
+  uint32_t first_bytes;    // of a[].first: what level 0 of a recurrence reads instead of src0 (0: zero states)
   uint32_t src_bytes;      // of src0, at most 2^32 - 512
   int32_t n_cb;            // workgroups of a group, H / 16
   int32_t n_groups;

@@ -45,12 +45,13 @@ constexpr int kListRows = 512;  // list positions of a level whose index lists s
 
 template <int G, int EPI, int NW, int NS, int RB>
 __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const StationaryArgs s) {
-  constexpr bool kStates = EPI == EPI_TREE_INTERNAL;
+  constexpr bool kTree = EPI == EPI_TREE_INTERNAL;  // two operand rows per node
+  constexpr bool kStates = kTree || EPI == EPI_LSTM_STEP || EPI == EPI_RNN_STEP;
   constexpr int BR = 16 * RB;         // rows of a block
   constexpr int ZW = G * BR * kZRow;  // floats of one wavefront's partial sums: [gate][row][column]
   constexpr int TURNS = NW / 4;       // groups of 256 threads that take turns at finishing a block
   extern __shared__ __attribute__((aligned(16))) float zbuf[];  // [2][NW][ZW]
-  __shared__ int s_out[kListRows], s_r0[kListRows], s_r1[kStates ? kListRows : 1];  // row written, operand rows
+  __shared__ int l_out[2][kListRows], l_r0[2][kListRows], l_r1[kTree ? 2 : 1][kTree ? kListRows : 1];  // row written, operand rows
   __shared__ float s_bias[G][16], s_winv[NW][G][16];
   __shared__ int s_go;
 
@@ -58,9 +59,10 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
   const int slot = blockIdx.x >> 3;
   const int group = (slot / s.n_cb) * 8 + (blockIdx.x & 7), cb = slot % s.n_cb;
   if (group >= s.n_groups) return;
+  const CellLevelArgs& a = s.a[s.two ? group & 1 : 0];
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, kq = lane >> 4;
-  const int H = s.a.H, T = (s.a.nseg * s.a.kseg) >> 5;  // 32-k steps, at most NW * NS
+  const int H = a.H, T = (a.nseg * a.kseg) >> 5;  // 32-k steps, at most NW * NS
 
   // ---- this wavefront's weights: gate g, unit 16 cb + li, steps w + NW t
   half8 whi[G][NS], wlo[G][NS];
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
     floatx4 raw[G][NS][2];  // (every load in flight at once)
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const float* row = s.a.W + ((size_t)gate_row<EPI>(g) * H + 16 * cb + li) * (size_t)s.a.ldw + 4 * kq;
+      const float* row = a.W + ((size_t)gate_row<EPI>(g) * H + 16 * cb + li) * (size_t)a.ldw + 4 * kq;
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
         const int step = w + NW * t;
@@ -86,7 +88,7 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
       for (int t = 0; t < NS; ++t) m = largest(raw[g][t][1], largest(raw[g][t][0], m));
       const float sc = scale_for(largest_of_quarters(m));
       if (lane < 16) s_winv[w][g][li] = inverse_power(sc) * (kStates ? 1.0f / kStateScale : 1.0f);
-      if (w == 0 && lane < 16) s_bias[g][li] = s.a.bias ? s.a.bias[gate_row<EPI>(g) * H + 16 * cb + li] : 0.0f;
+      if (w == 0 && lane < 16) s_bias[g][li] = a.bias ? a.bias[gate_row<EPI>(g) * H + 16 * cb + li] : 0.0f;
 #pragma unroll
       for (int t = 0; t < NS; ++t) split8(raw[g][t][0], raw[g][t][1], sc, whi[g][t], wlo[g][t]);
     }
@@ -94,17 +96,20 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
 
   // ---- node rows: a ring of the NS steps of one block.  Steps past the contraction range and rows past the last block
   // are requested past the end of the buffer, which reads zeros: no branch between the matrix instructions.
-  const __amdgpu_buffer_rsrc_t rsrc = agent_buffer(s.a.src0, s.src_bytes);
-  const int steps0 = s.a.kseg >> 5;  // steps of the first segment
+  const __amdgpu_buffer_rsrc_t rsrc = agent_buffer(a.src0, s.src_bytes);
+  const __amdgpu_buffer_rsrc_t rsrc_first = agent_buffer(a.first, s.first_bytes);  // level 0 of a recurrence
+  const int steps0 = a.kseg >> 5;  // steps of the first segment
+  bool first = false;
   floatx4 ring[RB][NS][2];
   unsigned base0[RB], base1[RB];     // byte offset of this lane's part of its row at step 0 (second segment: less kseg)
   auto request = [&](int r, int t, bool more) {
     const int step = w + NW * t;
-    unsigned at = (kStates && step >= steps0 ? base1[r] : base0[r]) + 128u * step;
+    unsigned at = (kTree && step >= steps0 ? base1[r] : base0[r]) + 128u * step;
     at = more && step < T ? at : 0xffffff00u;
     if constexpr (kStates) {
-      ring[r][t][0] = load_agent_f4(rsrc, at);
-      ring[r][t][1] = load_agent_f4(rsrc, at + 64u);
+      const auto from = first ? rsrc_first : rsrc;
+      ring[r][t][0] = load_agent_f4(from, at);
+      ring[r][t][1] = load_agent_f4(from, at + 64u);
     } else {
       ring[r][t][0] = load_buffer_f4(rsrc, at);
       ring[r][t][1] = load_buffer_f4(rsrc, at + 64u);
@@ -117,39 +122,92 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
   unsigned* const counter = s.counters + (size_t)group * kTreeCounterStride;
   unsigned arrived = 0;  // levels this group has announced
 
-  for (int lv = s.level0; lv < s.level1; ++lv) {
-    int p0, p1;  // the group's share of the level: positions [p0, p1) of the lists
+  // The group's share of a level: positions [p0, p1) of the lists, in chunks of kListRows whose index lists sit in LDS
+  // (two buffers: the next chunk's lists are fetched while the stores of this one complete).
+  auto share_of = [&](int lv, int& p0, int& p1) {
     if (s.off) {
       p0 = s.off[lv * s.n_groups + group];
       p1 = s.off[lv * s.n_groups + group + 1];
     } else {  // an even share of all rows, in whole blocks
-      const int blocks = (s.a.n + BR - 1) / BR;
+      const int blocks = (a.n + BR - 1) / BR;
       p0 = BR * (int)((long)blocks * group / s.n_groups);
       p1 = BR * (int)((long)blocks * (group + 1) / s.n_groups);
-      p1 = p1 < s.a.n ? p1 : s.a.n;
+      p1 = p1 < a.n ? p1 : a.n;
     }
-    if (p0 >= p1) break;  // (a group's levels only get narrower)
-    bool gone = false;
-    for (; p0 < p1; p0 += kListRows) {
-      const int n = p1 - p0 < kListRows ? p1 - p0 : kListRows, nb = (n + BR - 1) / BR;
-      __syncthreads();  // the lists of the rows before these have been read
-      for (int i = tid; i < BR * nb; i += 64 * NW) {  // tail rows repeat the last node; never stored
-        const int p = p0 + (i < n ? i : n - 1);
-        s_out[i] = s.a.out_rows ? s.a.out_rows[p] : p;
-        s_r0[i] = s.a.idx0 ? s.a.idx0[p] : p;
-        if constexpr (kStates) s_r1[i] = s.a.idx1[p];
+  };
+  constexpr int PE = kListRows / (64 * NW);
+  int list_out[PE], list_r0[PE], list_r1[PE];
+  auto request_lists = [&](int p0, int p1) {  // tail rows repeat the last node; never stored
+#pragma unroll
+    for (int e = 0; e < PE; ++e) {
+      int p = p0 + tid + 64 * NW * e;
+      p = p < p1 ? p : p1 - 1;
+      list_out[e] = a.out_rows ? a.out_rows[p] : p;
+      list_r0[e] = a.idx0 ? a.idx0[p] : p;
+      list_r1[e] = kTree ? a.idx1[p] : 0;
+    }
+  };
+  auto keep_lists = [&](int buf) {
+#pragma unroll
+    for (int e = 0; e < PE; ++e) {
+      l_out[buf][tid + 64 * NW * e] = list_out[e];
+      l_r0[buf][tid + 64 * NW * e] = list_r0[e];
+      if constexpr (kTree) l_r1[buf][tid + 64 * NW * e] = list_r1[e];
+    }
+  };
+  int lv = s.level0, p0, p1, lists = 0;
+  share_of(lv, p0, p1);
+  if (p0 >= p1) return;  // (nothing in this level: nothing in a later one)
+  request_lists(p0, p1);
+  keep_lists(0);
+  int q0 = 0, q1 = 0;  // the share of the next level
+  if (lv + 1 < s.level1) share_of(lv + 1, q0, q1);
+  __syncthreads();
+  for (bool new_level = true;; lists ^= 1) {
+    const int n = p1 - p0 < kListRows ? p1 - p0 : kListRows, nb = (n + BR - 1) / BR;
+    const int* const s_out = l_out[lists];
+    const int* const s_r0 = l_r0[lists];
+    const int* const s_r1 = l_r1[kTree ? lists : 0];
+    if constexpr (kStates && !kTree) first = lv == 0;
+    // What comes next: the rest of this level, the next level, or nothing (a group's levels only get narrower).  Lists and
+    // offsets are cold - nobody has read them yet - so they are requested one and two levels ahead, behind the level's own
+    // loads, which would otherwise wait for them (loads return in order).
+    const bool last_chunk = p0 + kListRows >= p1;
+    const int c0 = last_chunk ? __builtin_amdgcn_readfirstlane(q0) : p0 + kListRows;
+    const int c1 = last_chunk ? __builtin_amdgcn_readfirstlane(q1) : p1;
+    int n0 = 0, n1 = 0;
+    EpilogueOperands<G, EPI, RB> eo;
+    auto fetch_operands = [&](int b) {  // of the gate arithmetic; rows of this workgroup's own units and inputs only
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const int i = BR * b + 16 * r + er;
+        eo.live[r] = i < n;
+        eo.orow[r] = (size_t)s_out[i];
+        if constexpr (EPI == EPI_TREE_INTERNAL) {
+          eo.p0[r] = a.cprev_src[(size_t)s_r0[i] * H + j];
+          eo.p1[r] = a.cprev_src[(size_t)s_r1[i] * H + j];
+        }
+        if constexpr (EPI == EPI_LSTM_STEP) {
+          eo.p0[r] = first ? 0.0f : a.cprev_src[(size_t)s_r0[i] * H + j];
+#pragma unroll
+          for (int g = 0; g < G; ++g) eo.zx[g][r] = a.zadd[eo.orow[r] * (size_t)(G * H) + g * H + j];
+        }
+        if constexpr (EPI == EPI_RNN_STEP) eo.p0[r] = a.zadd[eo.orow[r] * (size_t)H + j];
       }
-      // the group's previous level is complete once all its workgroups have announced it
-      if (arrived > 0 && tid == 0) s_go = wait_for(counter, (unsigned)s.n_cb * arrived, s.status, s.max_polls) ? 1 : 0;
+    };
+    if (!kTree && turn == 0) fetch_operands(0);  // (a recurrence's addends are cold memory: requested before the wait)
+    if (new_level && arrived > 0) {  // the group's previous level is complete once all its workgroups have announced it
+      if (tid == 0) s_go = wait_for(counter, (unsigned)s.n_cb * arrived, s.status, s.max_polls) ? 1 : 0;
       __syncthreads();
-      if (arrived > 0 && !s_go) { gone = true; break; }
-
+      if (!s_go) break;
+    }
+    {
       auto set_rows = [&](int b) {
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
           const int i = BR * b + 16 * r + li;
-          base0[r] = (unsigned)s_r0[i] * (unsigned)s.a.ld0 * 4u + 16u * kq;
-          if constexpr (kStates) base1[r] = (unsigned)s_r1[i] * (unsigned)s.a.ld0 * 4u + 16u * kq - 128u * steps0;
+          base0[r] = (unsigned)s_r0[i] * (unsigned)a.ld0 * 4u + 16u * kq;
+          if constexpr (kTree) base1[r] = (unsigned)s_r1[i] * (unsigned)a.ld0 * 4u + 16u * kq - 128u * steps0;
         }
       };
       set_rows(0);
@@ -158,23 +216,14 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
 #pragma unroll
         for (int t = 0; t < NS; ++t) request(r, t, true);
       set_rows(nb > 1 ? 1 : 0);
+      if (kTree && turn == 0) fetch_operands(0);
+      if (c0 < c1) request_lists(c0, c1);
+      if (last_chunk && lv + 2 < s.level1) share_of(lv + 2, n0, n1);
 
       for (int b = 0; b < nb; ++b) {
         const bool mine = TURNS == 1 || (b & 1) == turn;
         const bool more = b + 1 < nb;
-        EpilogueOperands<G, EPI, RB> eo;
-        if (mine) {
-#pragma unroll
-          for (int r = 0; r < RB; ++r) {
-            const int i = BR * b + 16 * r + er;
-            eo.live[r] = i < n;
-            eo.orow[r] = (size_t)s_out[i];
-            if constexpr (EPI == EPI_TREE_INTERNAL) {
-              eo.p0[r] = s.a.cprev_src[(size_t)s_r0[i] * H + j];
-              eo.p1[r] = s.a.cprev_src[(size_t)s_r1[i] * H + j];
-            }
-          }
-        }
+        if (mine && b > 0) fetch_operands(b);
         float* const z = zbuf + (b & 1) * (NW * ZW) + w * ZW;
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
@@ -237,33 +286,44 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
               const int i = BR * b + 16 * r + er;
-              const float* const x0 = s.a.src0 + (size_t)s_r0[i] * (size_t)s.a.ld0;
-              const float* const x1 = kStates ? s.a.src0 + (size_t)s_r1[i] * (size_t)s.a.ld0 : x0;
+              const float* const x0 = (first ? a.first : a.src0) + (size_t)s_r0[i] * (size_t)a.ld0;
+              const float* const x1 = kTree ? a.src0 + (size_t)s_r1[i] * (size_t)a.ld0 : x0;
+              const int k_end = first && s.first_bytes == 0 ? 0 : 32 * T;  // (no state before the first step: no product)
 #pragma unroll
               for (int g = 0; g < G; ++g) {
                 if (__builtin_isfinite(zs[g][r])) continue;
-                const float* const wr = s.a.W + ((size_t)gate_row<EPI>(g) * H + j) * (size_t)s.a.ldw;
+                const float* const wr = a.W + ((size_t)gate_row<EPI>(g) * H + j) * (size_t)a.ldw;
                 float sum = 0.0f;
 #pragma unroll 1
-                for (int k = 0; k < 32 * T && sum == sum; ++k) {
-                  const float* const x = k < s.a.kseg ? x0 + k : x1 + (k - s.a.kseg);
+                for (int k = 0; k < k_end && sum == sum; ++k) {
+                  const float* const x = k < a.kseg ? x0 + k : x1 + (k - a.kseg);
                   sum = __builtin_fmaf(kStates ? __hip_atomic_load(x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *x, wr[k], sum);
                 }
                 zs[g][r] = sum;
               }
             }
           }
-          epilogue_apply<G, EPI, RB, kStates>(s.a, j, [&](int g, int r) { return zs[g][r]; }, eo);
+          epilogue_apply<G, EPI, RB, kStates>(a, j, [&](int g, int r) { return zs[g][r]; }, eo);
         }
       }
     }
-    if (gone) break;
-    if (s.stamps && cb == 0 && tid == 0) s.stamps[lv * s.n_groups + group] = wall_clock64();
-    if (lv + 1 < s.level1) {
-      wait_stores_done();  // this wavefront's stores have completed
-      __syncthreads();     // ... and so have the other wavefronts'
+    if (c0 < c1) keep_lists(lists ^ 1);
+    if (last_chunk && s.stamps && cb == 0 && tid == 0) s.stamps[lv * s.n_groups + group] = wall_clock64();
+    const bool announce = last_chunk && lv + 1 < s.level1;
+    if (announce) wait_stores_done();  // this wavefront's stores have completed ...
+    __syncthreads();                   // ... and so have the other wavefronts'; the lists are complete
+    if (announce) {
       if (tid == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       ++arrived;
+    }
+    if (c0 >= c1) break;
+    p0 = c0;
+    p1 = c1;
+    new_level = last_chunk;
+    if (last_chunk) {
+      ++lv;
+      q0 = n0;
+      q1 = n1;
     }
   }
   if (arrived > 0 && tid == 0) leave_block(counter, s.n_cb);
@@ -271,7 +331,8 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
 
 template <int G, int EPI, int NW, int NS>
 struct Stationary {
-  static constexpr int RB = EPI == EPI_TREE_INTERNAL ? 1 : 2;  // five gates leave no registers for a second 16 rows
+  // 16-row blocks multiplied between two barriers: the states of many gates leave no registers for a second one
+  static constexpr int RB = EPI == EPI_TREE_INTERNAL || EPI == EPI_LSTM_STEP ? 1 : 2;
   static constexpr size_t kLdsBytes = (size_t)2 * NW * G * 16 * RB * kZRow * sizeof(float);
   static const void* kernel() { return reinterpret_cast<const void*>(&cell_stationary_kernel<G, EPI, NW, NS, RB>); }
   // More than 64 KB of dynamic LDS has to be asked for once per device (one bit per device id; two threads that both
@@ -318,7 +379,8 @@ template <class F>
 auto dispatch(CellEpilogue epi, int32_t K, F&& f) {
   switch (epi) {
     case EPI_TREE_LEAF: return dispatch_steps<3, EPI_TREE_LEAF>(K, f);
-    case EPI_STORE_Z: return dispatch_steps<4, EPI_STORE_Z>(K, f);
+    case EPI_LSTM_STEP: return dispatch_steps<4, EPI_LSTM_STEP>(K, f);
+    case EPI_RNN_STEP: return dispatch_steps<1, EPI_RNN_STEP>(K, f);
     default: return dispatch_steps<5, EPI_TREE_INTERNAL>(K, f);
   }
 }
@@ -326,14 +388,14 @@ auto dispatch(CellEpilogue epi, int32_t K, F&& f) {
 }  // namespace
 
 int stationary_groups(CellEpilogue epi, int32_t H, int32_t K, int32_t n_cu) {
-  if ((epi != EPI_TREE_LEAF && epi != EPI_TREE_INTERNAL && epi != EPI_STORE_Z) || K <= 0 || K > kStationaryMaxK || H <= 0 || H % 16)
+  if ((epi != EPI_TREE_LEAF && epi != EPI_TREE_INTERNAL && epi != EPI_LSTM_STEP && epi != EPI_RNN_STEP) || K <= 0 || K > kStationaryMaxK || H <= 0 || H % 16)
     return 0;
   const int per_xcd = dispatch(epi, K, [](auto k) { return decltype(k)::per_cu(); }) * (n_cu / 8);
   return 8 * std::min(per_xcd / (H / 16), kTreeMaxGroups / 8);
 }
 
 hipError_t launch_stationary(CellEpilogue epi, const StationaryArgs& s, hipStream_t stream, const LaunchEvents& ev) {
-  return dispatch(epi, s.a.nseg * s.a.kseg, [&](auto k) { return decltype(k)::launch(s, stream, ev); });
+  return dispatch(epi, s.a[0].nseg * s.a[0].kseg, [&](auto k) { return decltype(k)::launch(s, stream, ev); });
 }
 
 }  // namespace acrobat

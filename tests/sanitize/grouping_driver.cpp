@@ -87,6 +87,47 @@ int main() {
     for (int g = 0; g < N; ++g) CHECK(seen[g] == (l[g] >= 0));
     for (int g = 0; g < groups; ++g) CHECK(groups > n_trees || size[g] <= (N - n_leaf) / groups + most);  // dealt out evenly
   }
+  // sequences: every (step, sequence, direction) once, rows and previous rows in the direction of the steps, and position i
+  // of a group's share the same sequence at every step
+  for (int round = 0; round < 300; ++round) {
+    const int n_seq = rnd_in(1, 60), directions = rnd_in(1, 2);
+    std::vector<int32_t> len(n_seq), row0(n_seq);
+    int R = 0, T = 0;
+    for (int q = 0; q < n_seq; ++q) {
+      len[q] = rnd_in(0, 12);
+      row0[q] = R;
+      R += len[q];
+      T = len[q] > T ? len[q] : T;
+    }
+    if (T == 0) continue;
+    const int groups = directions * rnd_in(1, 20);
+    std::vector<int32_t> out((size_t)directions * R, -1), prev((size_t)directions * R, -1), off((size_t)T * groups + 1, -1);
+    stage_seq_groups(n_seq, len.data(), T, groups, directions, out.data(), prev.data(), off.data());
+    CHECK(off[0] == 0 && off[(size_t)T * groups] == directions * R);
+    std::vector<int> seen((size_t)directions * R, 0);
+    std::vector<int> seq_of(R);
+    for (int q = 0; q < n_seq; ++q)
+      for (int t = 0; t < len[q]; ++t) seq_of[row0[q] + t] = q;
+    for (int g = 0; g < groups; ++g) {
+      std::vector<int> at;
+      for (int t = 0; t < T; ++t) {
+        const int p0 = off[(size_t)t * groups + g], p1 = off[(size_t)t * groups + g + 1];
+        CHECK(p0 <= p1 && (t == 0 || p1 - p0 <= (int)at.size()));
+        std::vector<int> now;
+        for (int p = p0; p < p1; ++p) {
+          const bool backward = directions == 2 && (g & 1);
+          const int row = out[p], q = seq_of[row];
+          CHECK(row == (backward ? row0[q] + len[q] - 1 - t : row0[q] + t));
+          CHECK(prev[p] == (t == 0 ? 0 : backward ? row + 1 : row - 1));
+          CHECK(t == 0 || at[p - p0] == q);
+          CHECK(!seen[(size_t)backward * R + row]++);
+          now.push_back(q);
+        }
+        at = now;
+      }
+    }
+    for (int v : seen) CHECK(v == 1);
+  }
   std::printf("grouping: ok\n");
   return 0;
 }

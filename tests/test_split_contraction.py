@@ -158,3 +158,54 @@ def test_profiling_times_every_level_of_the_one_launch(ctx):
     level_off, _ = ctx.acrobat_last_schedule()
     assert [r[1] for r in rec] == list(range(len(level_off) - 1)) and [r[2] for r in rec] == list(np.diff(level_off))
     assert all(r[3] > 0 for r in rec)
+
+
+@pytest.mark.parametrize("H,D,n,lo,hi", [(128, 32, 300, 0, 9), (160, 32, 1, 3, 3), (320, 96, 75, 1, 30), (512, 64, 17, 2, 2),
+                                         (512, 32, 300, 0, 12), (640, 64, 40, 1, 7), (1024, 64, 20, 2, 9), (1056, 32, 9, 2, 4)])
+def test_recurrences_in_one_launch(ctx, H, D, n, lo, hi):
+    """Sizes the older single-launch kernels do not take; 1 056 has one launch per step.  Against the oracle, against one
+    launch per step, and again (the counters are back at zero)."""
+    from tests import parity as P
+    import paper_2305_10611_amd as A
+    s = gen.lstm_workload(n, lo, hi, H, D, seed=H + n, bias_scale=0.2)
+    b = gen.birnn_workload(n, lo, hi, H, D, 7, seed=H + n, bias_scale=0.2)
+    b["finit"][:3], b["binit"][1] = (9.0, -7e4, 1e-12), 300.0  # initial states are not bounded as later ones are
+    lstm, birnn = P.run_lstm(ctx, s), P.run_birnn(ctx, b)
+    assert ctx.acrobat_device_status() == A.OK
+    for got, want in zip(lstm + birnn, oracle.varlen_lstm(s, nthreads=NT) + oracle.birnn(b, nthreads=NT)):
+        assert rel(got, want) < 1e-6
+    for got, again in zip(lstm + birnn, P.run_lstm(ctx, s) + P.run_birnn(ctx, b)):
+        assert np.array_equal(got, again)
+    ctx.acrobat_set_persistent(False)
+    try:
+        for got, steps in zip(lstm + birnn, P.run_lstm(ctx, s) + P.run_birnn(ctx, b)):
+            assert rel(got, steps) < 2e-6
+    finally:
+        ctx.acrobat_set_persistent(True)
+
+
+def test_recurrences_recorded_into_a_graph():
+    """A captured call launches the same kernel once per step: the eager result bit for bit, replay after replay."""
+    import torch
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    s = gen.lstm_workload(30, 0, 9, 160, 32, seed=3, bias_scale=0.2)
+    ctx = A.Context(0)
+    try:
+        ref = P.run_lstm(ctx, s)  # also sizes the context's buffers
+        R, H = int(np.sum(s["len"])), int(s["H"])
+        t = {k: P.dev(s[k]) for k in ("x", "Wx", "Wh", "b")}
+        h, c = P.nan_filled(R, H), P.nan_filled(R, H)
+        st = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st, capture_error_mode="relaxed"):
+            rc = ctx.acrobat_varlen_lstm_forward(s["len"], H, int(s["D"]), t["x"], t["Wx"], t["Wh"], t["b"], h, c, st.cuda_stream)
+        assert rc == A.OK, ctx.acrobat_last_error()
+        for _ in range(3):
+            h.fill_(float("nan")); c.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(h.cpu().numpy(), ref[0]) and np.array_equal(c.cpu().numpy(), ref[1])
+    finally:
+        ctx.close()
