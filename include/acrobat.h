@@ -192,7 +192,8 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
  * The same switch covers acrobat_birnn_forward (H in {128, 256, 512}, at most 256 non-empty sequences, every
  * workgroup resident at once): both recurrences then run in one launch, blocks of 16 sequences per direction,
  * H / 16 workgroups per block exchanging h after every step in the same way.
- * It also covers acrobat_mvrnn_forward (d == 64 up to a widest internal level of 2 048 nodes, d == 128 up to 512):
+ * It also covers acrobat_mvrnn_forward (d == 64 up to a widest internal level of 2 048 nodes; d == 128 with
+ * a level of more than 512 nodes reports that launch level by level, as ACROBAT_K_MVRNN_LEVEL):
  * all internal levels then run in ONE launch in which
  * a node waits for its own two children only (flag words per node, polled with the same bound) instead of a
  * whole level waiting for the previous one, provided every workgroup of that launch is resident at once and the

@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
+#include <limits>
 #include <mutex>
 #include <new>
 #include <string>
@@ -442,6 +443,7 @@ int launch_buckets(acrobat_dfg* g, hipStream_t stream, int32_t* st, const int32_
       m.n = g->buckets.off[b + 1] - off;
       m.d = d.H;
       m.variant = ctx->mvrnn_variant;
+      m.quarters = m.n <= 256;
       m.out_rows = idx + off;
       m.lsrc = idx + n + off;
       m.rsrc = idx + 2 * n + off;
@@ -657,15 +659,18 @@ int finish_stamped(acrobat_ctx* ctx, LaunchTimer& timer) {
   const StampedLaunch st = ctx->stamped;
   ctx->stamped = StampedLaunch();
   if (st.record < 0) return ACROBAT_OK;
-  std::vector<unsigned long long> t((size_t)st.level1 * st.groups);
+  // groups == 0: a stamp for every list position behind level 0 instead of one for every level and group
+  const int32_t base = st.level_off[st.level0];
+  std::vector<unsigned long long> t(st.groups ? (size_t)st.level1 * st.groups : (size_t)(st.level_off[st.level1] - base));
   HIP_TRY(ctx, hipMemcpy(t.data(), ctx->d_stamps, t.size() * sizeof(t[0]), hipMemcpyDeviceToHost));
   const acrobat_launch_record whole = ctx->records[st.record];
   std::vector<acrobat_launch_record> levels;
   float later = 0.0f;
   unsigned long long before = 0;
   for (int32_t lv = st.level0; lv < st.level1; ++lv) {
-    const auto* row = t.data() + (size_t)lv * st.groups;
-    const unsigned long long end = std::max(before + 1, *std::max_element(row, row + st.groups));
+    const auto* row = t.data() + (st.groups ? (size_t)lv * st.groups : (size_t)(st.level_off[lv] - base));
+    const auto* row_end = st.groups ? row + st.groups : t.data() + (st.level_off[lv + 1] - base);
+    const unsigned long long end = std::max(before + 1, *std::max_element(row, row_end));
     acrobat_launch_record r = whole;
     r.level = lv;
     r.n = st.directions * (st.level_off[lv + 1] - st.level_off[lv]);
@@ -1063,17 +1068,20 @@ int acrobat_mvrnn_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t 
     // One launch for all internal levels where the kernel exists (d = 64) and every workgroup is resident at
     // once: a node then waits for its own two children instead of a whole level for the previous one.
     const int32_t n_internal = N - n_leaf;
-    // (Batches with very wide levels keep one launch per level: at 1 024 trees the single launch is 10 % slower,
-    // 0.54 vs 0.49 ms - its flag checks and write-through stores buy nothing where levels are bandwidth bound.)
+    // (Batches with very wide levels keep one launch per level at d = 64: at 1 024 trees the single launch is 10 %
+    // slower, 0.54 vs 0.49 ms - its flag checks and write-through stores buy nothing where levels are bandwidth bound.
+    // At d = 128 every launch reads 256 KB of weights per workgroup, 11 us: 353 us in one launch for 256 trees, 480 in
+    // thirteen.)
     int32_t widest = 0;
     for (int32_t lv = 1; lv < s.n_levels; ++lv) widest = std::max(widest, s.level_off[lv + 1] - s.level_off[lv]);
-    const int32_t widest_limit = d == 64 ? 2048 : 512;  // (a d = 128 node is four times the bytes)
+    const int32_t widest_limit = d == 64 ? 2048 : std::numeric_limits<int32_t>::max();
     const size_t flag_words = (size_t)N * 4;  // one per workgroup of a node
     // d = 64: four workgroups per node while the levels are narrow enough for a node's latency to be what counts
     // (the configuration of 64 trees, widest level 563: 0.097 against 0.100 ms; 16 trees 0.063 against 0.073;
     // 96 trees, widest level 850: 0.120 against 0.117, 192 trees 0.168 against 0.145 - every workgroup of a node
     // reads both child matrices whole)
-    const bool quarters = d == 64 && widest <= 640;
+    // (d = 128: while no level has more nodes than there are compute units)
+    const bool quarters = widest <= (d == 64 ? 640 : 256);
     const int df_wgs = ctx->persistent && ctx->mvrnn_variant == 0 && s.n_levels > 2 && widest <= widest_limit &&
                                !stream_is_capturing(stream)
                            ? mvrnn_dataflow_workgroups(d, n_internal, quarters) : 0;
@@ -1103,11 +1111,16 @@ int acrobat_mvrnn_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t 
       a.vec = d_vec; a.mat = d_mat;
       a.flags = ctx->d_node_flags; a.epoch = ctx->epoch;
       a.status = ctx->h_status_dev; a.max_polls = ctx->max_polls;
-      TRY(timer.begin(ACROBAT_K_MVRNN_PERSISTENT, 1, n_internal));
+      // (batches with a level of more than 512 nodes are reported level by level)
+      const bool by_level = d == 128 && widest > 512;
+      if (by_level && timer.on()) TRY(reserve_stamps(ctx, n_internal, stream, &a.stamps));
+      TRY(timer.begin(by_level ? ACROBAT_K_MVRNN_LEVEL : ACROBAT_K_MVRNN_PERSISTENT, 1, n_internal));
+      if (by_level && timer.tile()) *timer.tile() = 1;
       HIP_TRY(ctx, order_waiting_launch(ctx->device, stream));
       HIP_TRY(ctx, launch_mvrnn_dataflow(a, df_wgs, quarters, stream, timer.ev));
       TRY(timer.end());
-      return timer.finish();
+      if (a.stamps) ctx->stamped = {(int32_t)ctx->records.size() - 1, 1, s.n_levels, 0, 1, s.level_off.data()};
+      return finish_stamped(ctx, timer);
     }
     for (int32_t lv = 1; lv < s.n_levels; ++lv) {
       const int32_t off = s.level_off[lv], n = s.level_off[lv + 1] - off;
@@ -1115,6 +1128,7 @@ int acrobat_mvrnn_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t 
       a.n = n;
       a.d = d;
       a.variant = ctx->mvrnn_variant;
+      a.quarters = quarters;
       a.out_rows = d_out + off;
       a.lsrc = d_ia + off;
       a.rsrc = d_ib + off;

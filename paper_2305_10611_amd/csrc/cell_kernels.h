@@ -130,6 +130,8 @@ struct MvrnnLevelArgs {
   // the row once its part of the state has been stored (d = 64 without quarters: one word per row); the status word and the bound of every wait as for the other persistent kernels
   unsigned* flags; unsigned epoch;
   unsigned* status; int32_t max_polls;
+  bool quarters = true;                 // d = 128: four workgroups per node (one, with split operands, if false)
+  unsigned long long* stamps = nullptr; // d = 128, one workgroup per node: clock at the end of every list position, or null
 };
 // Same for two independent batches: one shared launch where the variants agree (then *tile / *ksplit
 // describe it and ev brackets it), else two launches in a row on the stream (ev.start on the first,
@@ -152,9 +154,9 @@ hipError_t launch_mvrnn_level(const MvrnnLevelArgs& a, hipStream_t stream, int32
                               const LaunchEvents& ev = LaunchEvents());
 
 // All internal levels of an MV-RNN batch in ONE launch: the lists hold every internal node in schedule
-// order; a node waits for its own two children only (a.flags / a.epoch), never for a whole level.  `quarters`
-// (d = 64 only; d = 128 always works that way): four workgroups per node, each a quarter of the node's matrix
-// product, for batches of narrow levels, where a node's latency is what counts; otherwise one workgroup per node.
+// order; a node waits for its own two children only (a.flags / a.epoch), never for a whole level.  `quarters`: four
+// workgroups per node, each a quarter of the node's matrix product, for batches of narrow levels, where a node's latency
+// is what counts; otherwise one workgroup per node.
 // a.flags needs four words per arena row (one per workgroup of a node; d = 64 without quarters uses the first
 // word per row of a [rows] array).
 // mvrnn_dataflow_workgroups: how many workgroups such a launch may have so that all are resident at once on the

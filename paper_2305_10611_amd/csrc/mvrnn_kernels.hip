@@ -31,8 +31,10 @@
 #include "cell_kernels.h"
 
 #include "agent_access.h"
+#include "split_fp16.h"
 
 #include <algorithm>
+#include <atomic>
 
 namespace acrobat {
 namespace {
@@ -63,6 +65,17 @@ __device__ __forceinline__ floatx2 load_agent_f2(const float* p) {
 __device__ __forceinline__ void store_agent_f2(float* p, floatx2 v) {
   __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// 4-byte accesses of data that another workgroup of the launch may have written or reads (kShared), or plain ones
+template <bool kShared>
+__device__ __forceinline__ float load_f1_at(__amdgpu_buffer_rsrc_t rsrc, unsigned lane_off, unsigned uniform_off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)lane_off, (int)uniform_off, kShared ? kAuxAgentScope : 0));
+}
+template <bool kShared>
+__device__ __forceinline__ void store_f1(float* p, float v) {
+  if constexpr (kShared) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = v;
 }
 
 struct NodeRef {  // where one node's operands live and where its results go
@@ -1010,6 +1023,309 @@ __global__ __launch_bounds__(256, 2) void mvrnn_rows_kernel(const MvrnnLevelArgs
   }
 }
 
+// d = 128, batches whose widest level has more nodes than there are compute units: one workgroup per node, on the
+// fp16 matrix cores with split operands (split_fp16.h).  (Narrower batches are a chain of single nodes, where four
+// workgroups with a quarter of the weights each start sooner: one tree of 30 leaves 108 against 134 us, 8 trees 80
+// against 98, 30 trees 177 against 185; 64 trees 199 against 176, 256 trees 588 against 353.)
+//   P = W_M [A ; B] is a [128 x 256] x [256 x 128] product; at fp32 rate it costs a compute unit 13.7 us of matrix
+// instructions, as four fp16 products 3.4 us, about what the node's 192 KB take at the copy rate.  (lo lo' is not left
+// out here: states are products of products down the tree, so what a node loses adds up - without it 2.9e-7 against 64
+// bits after 13 levels, with fp32 instructions 2.5e-7.)
+//  * W_M is split once per launch, every row with a scale of its own, and stays in LDS (128 KB: a 32-k slab of a row is
+//    its 32 hi terms and its 32 lo terms, eight 16-byte chunks, chunk c of row i at position c ^ (i & 7), so that
+//    operand reads of eight rows cover all banks).  It is the A operand of v_mfma_f32_32x32x16_f16: lane l reads row
+//    l % 32, k = 16 s + 8 (l / 32) + 0 .. 7.
+//  * Wavefront w owns output columns 32 w .. 32 w + 31, all 128 rows, and needs nothing but those columns of the
+//    children: lane l holds column l % 32 of half of the 256 rows of [A ; B] (rows 16 s + 8 (l / 32) + e), so every
+//    element is read once per workgroup, straight into the registers of the B operand.  The scale is the column's,
+//    found in the same lane and its partner; a step's registers are requested again for the next node as soon as they
+//    have been used.  (Eight wavefronts with 16 columns each: 124 instead of 94 us for 1 700 nodes, spills.)
+//  * B a and A b: rows x (the other child's vector) from the same registers, summed over 16 lanes by row rotations and
+//    over the rest through LDS; W [B a ; A b] with W in 128 registers per lane (two lanes per output row).
+// What is not finite is computed again in fp32 from memory.
+// Bound: HBM for wide levels (1 700 nodes move 334 MB), a node's chain (rows 128 KB at what one compute unit pulls, 256
+// matrix instructions per wavefront, stores) and the 256 KB of weights per workgroup and launch for narrow ones.
+//
+// DF (dataflow): one launch for all internal levels, as mvrnn_level_kernel<true> does for d = 64; one flag word per node.
+// The next node's rows are only requested early when its children are complete at that point.
+constexpr int kNodeWmBytes = 128 * 256 * (int)sizeof(float);
+constexpr int kNodeThreads = 256;
+constexpr int kNodeLdsBytes = kNodeWmBytes + (8 * 256 + 256 + 128) * (int)sizeof(float);
+
+// sum over the 16 lanes of a row, in all of them
+__device__ __forceinline__ float row_sum(float x) {
+#define ACROBAT_ROTATE(n) x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + (n), 0xf, 0xf, false))
+  ACROBAT_ROTATE(8);
+  ACROBAT_ROTATE(4);
+  ACROBAT_ROTATE(2);
+  ACROBAT_ROTATE(1);
+#undef ACROBAT_ROTATE
+  return x;
+}
+
+template <bool DF>
+__global__ __launch_bounds__(kNodeThreads, 1) void mvrnn_node_kernel(const MvrnnLevelArgs a) {
+  constexpr int D = 128, DD = D * D, S = 16;  // 16-k steps
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  unsigned char* const s_wm = lds;
+  float* const s_vp = reinterpret_cast<float*>(lds + kNodeWmBytes);  // [wavefront][256] partial sums of B a | A b
+  float* const s_v = s_vp + 8 * 256;                                  // [256] B a | A b
+  float* const s_inv = s_v + 256;                                     // [128] inverse scale of W_M's rows
+  __shared__ int s_go;
+
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lcol = lane & 31, lhi = lane >> 5;
+  int slot = blockIdx.x;
+  const int nslots = gridDim.x;
+  if (slot >= a.n) return;
+
+  struct RawIdx { int ls, rs, orow; };
+  struct Node { const float *ma, *mb, *va, *vb; size_t orow; };
+  const int32_t* __restrict__ lsrc = a.lsrc;
+  const int32_t* __restrict__ rsrc = a.rsrc;
+  const int32_t* __restrict__ orows = a.out_rows;
+  auto load_idx = [&](int node) {
+    const int u = __builtin_amdgcn_readfirstlane(node);
+    return RawIdx{lsrc[u], rsrc[u], orows[u]};
+  };
+  auto resolve = [&](const RawIdx& i) {
+    const int l = __builtin_amdgcn_readfirstlane(i.ls), r = __builtin_amdgcn_readfirstlane(i.rs);
+    Node n;
+    n.ma = l >= 0 ? a.mat + (size_t)l * DD : a.mat_tab + (size_t)(-(l + 1)) * DD;
+    n.mb = r >= 0 ? a.mat + (size_t)r * DD : a.mat_tab + (size_t)(-(r + 1)) * DD;
+    n.va = l >= 0 ? a.vec + (size_t)l * D : a.vec_tab + (size_t)(-(l + 1)) * D;
+    n.vb = r >= 0 ? a.vec + (size_t)r * D : a.vec_tab + (size_t)(-(r + 1)) * D;
+    n.orow = (size_t)i.orow;
+    return n;
+  };
+  float x[S][8];
+  float va = 0.0f, vb = 0.0f;  // the children's vectors at this lane's column
+  const unsigned lane_off = (unsigned)((8 * lhi * D + 32 * w + lcol) * sizeof(float));
+  auto load_step = [&](const Node& n, int s) {  // (DF: another workgroup of this launch may have stored the rows)
+    const __amdgpu_buffer_rsrc_t m = agent_buffer(s < S / 2 ? n.ma : n.mb, DD * sizeof(float));
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      x[s][e] = load_f1_at<DF>(m, lane_off, (unsigned)((16 * (s % (S / 2)) + e) * D * sizeof(float)));
+  };
+  auto load_vec = [&](const Node& n) {
+    va = load_f1_at<DF>(agent_buffer(n.va, D * sizeof(float)), (unsigned)((32 * w + lcol) * sizeof(float)), 0u);
+    vb = load_f1_at<DF>(agent_buffer(n.vb, D * sizeof(float)), (unsigned)((32 * w + lcol) * sizeof(float)), 0u);
+  };
+  auto children_done = [&](const RawIdx& i) {
+    const unsigned l = i.ls >= 0 ? load_agent(a.flags + 4 * (size_t)i.ls) : a.epoch;
+    const unsigned r = i.rs >= 0 ? load_agent(a.flags + 4 * (size_t)i.rs) : a.epoch;
+    return l == a.epoch && r == a.epoch;
+  };
+  auto wait_children = [&](const RawIdx& i) {  // thread 0 waits, bounded; false: a wait ran out here or elsewhere - drain
+    if (tid == 0) {
+      int polls = 0;
+      bool ok = true;
+      if (a.max_polls == 0) {  // test hook: every wait gives up at once
+        raise_status(a.status);
+        ok = false;
+      }
+      while (ok && !children_done(i)) {
+        if (++polls > a.max_polls) {
+          raise_status(a.status);
+          ok = false;
+          break;
+        }
+        if ((polls & 255) == 0 && status_raised(a.status)) { ok = false; break; }
+        __builtin_amdgcn_s_sleep(1);
+      }
+      s_go = ok ? 1 : 0;
+    }
+    __syncthreads();
+    return s_go != 0;
+  };
+
+  RawIdx raw = load_idx(slot);
+  RawIdx raw_next = load_idx(min(slot + nslots, a.n - 1));
+  Node cur = resolve(raw);
+  RawIdx cur_raw = raw;
+  bool have = false;  // the current node's rows have been requested
+  if constexpr (!DF) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) load_step(cur, s);
+    load_vec(cur);
+    have = true;
+  }
+  floatx4 wv[32];  // W: output row tid / 2, columns 128 (tid % 2) ...
+  {  // W_M: two threads per row
+    const int row = tid >> 1, half = tid & 1;
+    const float* src = a.WM + (size_t)row * (2 * D) + D * half;
+    floatx4 v[32];
+#pragma unroll
+    for (int q = 0; q < 32; ++q) v[q] = *reinterpret_cast<const floatx4*>(src + 4 * q);
+    float m = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 32; ++q) m = largest(v[q], m);
+    m = fmaxf(m, __shfl_xor(m, 1));
+    const float sc = scale_for(m);
+    if (half == 0) s_inv[row] = inverse_power(sc);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {  // 8-k group 16 half + q
+      half8 hi, lo;
+      split8(v[2 * q], v[2 * q + 1], sc, hi, lo);
+      unsigned char* const slab = s_wm + row * 1024 + (4 * half + (q >> 2)) * 128;
+      *reinterpret_cast<half8*>(slab + (((q & 3) ^ (row & 7)) << 4)) = hi;
+      *reinterpret_cast<half8*>(slab + (((4 + (q & 3)) ^ (row & 7)) << 4)) = lo;
+    }
+  }
+  if (DF && __all(children_done(cur_raw))) {  // (the first nodes' children are leaves: their rows before W's)
+#pragma unroll
+    for (int s = 0; s < S; ++s) load_step(cur, s);
+    load_vec(cur);
+    have = true;
+  }
+  {
+    const float* wsrc = a.W + (size_t)(tid >> 1) * (2 * D) + D * (tid & 1);
+#pragma unroll
+    for (int q = 0; q < 32; ++q) wv[q] = *reinterpret_cast<const floatx4*>(wsrc + 4 * q);
+  }
+  __syncthreads();
+
+  while (true) {
+    if constexpr (DF) {
+      if (!wait_children(cur_raw)) return;
+      if (!have) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) load_step(cur, s);
+        load_vec(cur);
+      }
+    }
+    const RawIdx nxt_raw = raw_next;
+    const Node nxt = resolve(nxt_raw);
+    raw_next = load_idx(min(slot + 2 * nslots, a.n - 1));
+    bool pre = slot + nslots < a.n;  // request the next node's rows as this node's are used up?
+    if constexpr (DF) pre = pre && __all(children_done(nxt_raw));
+
+    // scale of this lane's column over both children (its rows and those of lane +- 32)
+    float m = 0.0f;
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) m = fmaxf(m, fmaxf(fabsf(x[s][e]), fabsf(x[s][e + 1])));
+    m = fmaxf(m, __shfl_xor(m, 32));
+    const float sc = scale_for(m);
+
+    floatx16 acc[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[b][v] = 0.0f;
+    const float va_now = va, vb_now = vb;
+    if (pre) load_vec(nxt);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      // rows 16 s + 8 lhi + e of [A ; B] times the other child's vector, summed over the two halves of 16 lanes; A b sits
+      // behind B a
+      floatx4 t[2];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) t[e >> 2][e & 3] = row_sum(x[s][e] * (s < S / 2 ? vb_now : va_now));
+      if ((lcol & 15) == 0) {
+        float* const to = s_vp + (2 * w + (lcol >> 4)) * 256 + (s < S / 2 ? D + 16 * s : 16 * s - D) + 8 * lhi;
+        *reinterpret_cast<floatx4*>(to) = t[0];
+        *reinterpret_cast<floatx4*>(to + 4) = t[1];
+      }
+      half8 bhi, blo;
+      split8(floatx4{x[s][0], x[s][1], x[s][2], x[s][3]}, floatx4{x[s][4], x[s][5], x[s][6], x[s][7]}, sc, bhi, blo);
+      if (pre) load_step(nxt, s);
+      half8 ahi[4], alo[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const unsigned char* const slab = s_wm + (32 * b + lcol) * 1024 + (s >> 1) * 128;
+        const int kg = 2 * (s & 1) + lhi;
+        ahi[b] = *reinterpret_cast<const half8*>(slab + ((kg ^ (lcol & 7)) << 4));
+        alo[b] = *reinterpret_cast<const half8*>(slab + (((4 + kg) ^ (lcol & 7)) << 4));
+      }
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(alo[b], blo, acc[b], 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(alo[b], bhi, acc[b], 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ahi[b], blo, acc[b], 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ahi[b], bhi, acc[b], 0, 0, 0);
+    }
+
+    // ---- P: column 32 w + lcol, accumulator register v of block b: row 32 b + 8 (v / 4) + 4 lhi + v % 4
+    const float cinv = inverse_power(sc);
+    float* const P = a.mat + cur.orow * DD + 32 * w + lcol;
+    unsigned long long bad = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = 32 * b + 8 * q + 4 * lhi;
+        const floatx4 rinv = *reinterpret_cast<const floatx4*>(s_inv + row);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float p = acc[b][4 * q + e] * rinv[e] * cinv;
+          if (!__builtin_isfinite(p)) bad |= 1ull << (16 * b + 4 * q + e);
+          store_f1<DF>(P + (size_t)(row + e) * D, p);
+        }
+      }
+    __syncthreads();  // s_vp complete
+    {
+      const float* const q = s_vp + tid;
+      s_v[tid] = ((q[0] + q[256]) + (q[512] + q[768])) + ((q[1024] + q[1280]) + (q[1536] + q[1792]));
+    }
+    while (bad) {  // in fp32 instead
+      const int v = __builtin_ctzll(bad), row = 32 * (v >> 4) + 8 * ((v >> 2) & 3) + 4 * lhi + (v & 3);
+      bad &= bad - 1;
+      float t = 0.0f;
+#pragma unroll 1
+      for (int k = 0; k < 2 * D && t == t; ++k) {
+        const float* const q = (k < D ? cur.ma : cur.mb - (size_t)DD) + (size_t)k * D + 32 * w + lcol;
+        t = __builtin_fmaf(a.WM[(size_t)row * (2 * D) + k], DF ? __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *q, t);
+      }
+      store_f1<DF>(P + (size_t)row * D, t);
+    }
+    __syncthreads();  // s_v complete
+    {  // p = tanh(W [B a ; A b])
+      float part[8] = {};  // (short chains: as exact as a lane per 32 columns)
+#pragma unroll
+      for (int q = 0; q < 32; ++q) {
+        const floatx4 v4 = *reinterpret_cast<const floatx4*>(s_v + D * (tid & 1) + 4 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part[4 * (q & 1) + e] = __builtin_fmaf(wv[q][e], v4[e], part[4 * (q & 1) + e]);
+      }
+      float t = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
+      t += __shfl_xor(t, 1);
+      if ((tid & 1) == 0) store_f1<DF>(a.vec + cur.orow * D + (tid >> 1), fast_tanh(t));
+    }
+    if constexpr (DF) {  // the node is complete once every wavefront's stores are: announce it
+      wait_stores_done();
+      __syncthreads();
+      if (tid == 0) {
+        __hip_atomic_store(a.flags + 4 * cur.orow, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (a.stamps) a.stamps[slot] = wall_clock64();
+      }
+    }
+    slot += nslots;
+    if (slot >= a.n) break;
+    cur = nxt;
+    cur_raw = nxt_raw;
+    have = pre;
+  }
+}
+
+hipError_t configure_node_kernel(const void* kernel, std::atomic<uint64_t>& configured) {  // more than 64 KB of dynamic LDS, once per device
+  int dev = 0;
+  if (const hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+  const uint64_t bit = 1ull << (dev & 63);
+  if (dev < 64 && (configured.load(std::memory_order_acquire) & bit)) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kNodeLdsBytes);
+  if (e == hipSuccess && dev < 64) configured.fetch_or(bit, std::memory_order_release);
+  return e;
+}
+template <bool DF>
+hipError_t configure_node_kernel() {
+  static std::atomic<uint64_t> configured{0};
+  return configure_node_kernel(reinterpret_cast<const void*>(&mvrnn_node_kernel<DF>), configured);
+}
+
 __global__ __launch_bounds__(256) void mvrnn_leaf_copy_kernel(int n, int d, const int32_t* out_rows,
                                                               const int32_t* token, const float* vec_tab,
                                                               const float* mat_tab, float* vec, float* mat) {
@@ -1032,10 +1348,13 @@ hipError_t launch_mvrnn_level(const MvrnnLevelArgs& a, hipStream_t stream, int32
   const int grid = a.n < 512 ? a.n : 512;  // two resident workgroups per compute unit, each strides over the level
   if (a.d == 128 && a.variant == 1) {
     launch_with_events(mvrnn_stream_kernel<128>, dim3(a.n < 256 ? a.n : 256), dim3(256), 0, stream, ev.start, ev.stop, a);
-  } else if (a.d == 128) {
+  } else if (a.d == 128 && a.quarters) {
     // four workgroups per node slot, slots in groups of 8; 512 resident workgroups = 128 slots
     const int slots = a.n < 128 ? (a.n + 7) / 8 * 8 : 128;
     launch_with_events(mvrnn_rows_kernel<false>, dim3(4 * slots), dim3(256), 0, stream, ev.start, ev.stop, a);
+  } else if (a.d == 128) {
+    if (const hipError_t e = configure_node_kernel<false>(); e != hipSuccess) return e;
+    launch_with_events(mvrnn_node_kernel<false>, dim3(a.n < 256 ? a.n : 256), dim3(kNodeThreads), kNodeLdsBytes, stream, ev.start, ev.stop, a);
   } else if (a.variant == 1) {
     launch_with_events(mvrnn_stream_kernel<64>, dim3(grid), dim3(256), 0, stream, ev.start, ev.stop, a);
   } else {
@@ -1049,7 +1368,13 @@ int mvrnn_dataflow_workgroups(int32_t d, int32_t n, bool quarters) {
   int dev = 0, per_cu = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (d == 64 && !quarters) {
+  if (d == 128 && !quarters) {
+    if (configure_node_kernel<true>() != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mvrnn_node_kernel<true>, kNodeThreads, kNodeLdsBytes) != hipSuccess) return 0;
+    const long resident = (long)per_cu * cus;
+    return (int)(n < resident ? n : resident);
+  }
+  if (!quarters) {
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mvrnn_level_kernel<true>, 256, 0) != hipSuccess) return 0;
     const long resident = (long)per_cu * cus;
     return (int)(n < resident ? n : resident);
@@ -1068,6 +1393,10 @@ hipError_t launch_mvrnn_dataflow(const MvrnnLevelArgs& a, int workgroups, bool q
   if ((a.d != 64 && a.d != 128) || workgroups <= 0 || !a.flags || !a.status) return hipErrorInvalidValue;
   if (a.d == 64 && !quarters) {
     launch_with_events(mvrnn_level_kernel<true>, dim3((unsigned)workgroups), dim3(256), 0, stream, ev.start, ev.stop, a);
+    return hipGetLastError();
+  }
+  if (a.d == 128 && !quarters) {
+    launch_with_events(mvrnn_node_kernel<true>, dim3((unsigned)workgroups), dim3(kNodeThreads), kNodeLdsBytes, stream, ev.start, ev.stop, a);
     return hipGetLastError();
   }
   if (workgroups % 32) return hipErrorInvalidValue;

@@ -209,3 +209,50 @@ def test_recurrences_recorded_into_a_graph():
             assert np.array_equal(h.cpu().numpy(), ref[0]) and np.array_equal(c.cpu().numpy(), ref[1])
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("trees,lo,hi", [(300, 2, 3), (140, 4, 30), (257, 2, 2)])
+def test_mvrnn_d128_one_workgroup_per_node(ctx, trees, lo, hi):
+    """More nodes in a level than compute units: one workgroup per node, in one launch and level by level the same bits."""
+    from tests import parity as P
+    w = gen.mvrnn_workload(trees, lo, hi, 128, seed=trees)
+    w["mat_tab"] *= np.logspace(-6, 2, w["V"], dtype=np.float32)[gen.make_rng(1).permutation(w["V"])][:, None, None]  # columns' scales follow
+    vec, mat = P.run_mvrnn(ctx, w, copy_leaves=0)
+    assert ctx.acrobat_device_status() == 0
+    level_off, _ = ctx.acrobat_last_schedule()
+    assert np.diff(level_off)[1:].max() > 256
+    internal = w["left"] >= 0
+    ov, om = oracle.mvrnn(w, nthreads=NT)
+    for n in np.flatnonzero(internal):
+        # of a sum of two products the larger one's rounding is what remains where they cancel: against the magnitudes added
+        lim = 4e-6 * max(1e-30, np.abs(om[n]).max())
+        assert np.abs(mat[n] - om[n]).max() < lim
+    # The vectors are fp32 sums: a row of a child matrix scaled by up to 100 gives entries of B a up to about 300 (an identity
+    # plus noise, |a| up to 3), a row of W adds 256 of them times up to 0.09, about 430 in all, in some 400 additions:
+    # 430 sqrt(400) 2^-24 = 5e-4 in the argument of tanh, four times that is allowed.
+    assert np.abs(vec[internal] - ov[internal]).max() < 2e-3
+    ctx.acrobat_set_persistent(False)
+    try:
+        vec1, mat1 = P.run_mvrnn(ctx, w, copy_leaves=0)
+    finally:
+        ctx.acrobat_set_persistent(True)
+    assert np.array_equal(vec[internal], vec1[internal]) and np.array_equal(mat[internal], mat1[internal])
+
+
+def test_mvrnn_d128_infinities_and_nans_say_what_fp32_says(ctx):
+    from tests import parity as P
+    w = gen.mvrnn_workload(300, 2, 3, 128, seed=9)
+    w["mat_tab"][3, 5, 7], w["mat_tab"][9, 0, 0], w["mat_tab"][20, 1, 2] = np.inf, np.nan, 3e38
+    w["WM"][4, 6] = -np.inf
+    vec, mat = P.run_mvrnn(ctx, w, copy_leaves=0)
+    internal = w["left"] >= 0
+    ctx.check(ctx.acrobat_set_tuning(0, 0, 1))  # the streaming kernel, fp32
+    try:
+        _, want = P.run_mvrnn(ctx, w, copy_leaves=0)
+    finally:
+        ctx.check(ctx.acrobat_set_tuning(0, 0, 0))
+    got, want = mat[internal], want[internal]
+    assert (~np.isfinite(want)).any() and np.isfinite(want).any()
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+    fine = np.isfinite(want)
+    assert np.abs(got[fine] - want[fine]).max() <= 1e-5 * np.abs(want[fine]).max()
