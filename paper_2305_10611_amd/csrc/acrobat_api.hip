@@ -603,9 +603,9 @@ constexpr int32_t kDefaultMaxPolls = 1 << 18;
 constexpr int32_t kTreeMaxPolls = 1 << 24;
 
 // Which levels of a tree batch run on the weight-stationary kernels: leaf = groups for level 0, groups = groups the
-// trees are dealt out to for the internal levels; 0: those levels run on the level kernels.
+// trees are dealt out to for the internal levels from level `first` on; 0: those levels run on the level kernels.
 struct TreePlan {
-  int32_t leaf = 0, groups = 0;
+  int32_t leaf = 0, groups = 0, first = 1;
 };
 
 TreePlan plan_tree(const acrobat_ctx* ctx, const TreeSchedule& s, int32_t H, int32_t D, int32_t V, bool noalloc, size_t n_iota) {
@@ -623,9 +623,20 @@ TreePlan plan_tree(const acrobat_ctx* ctx, const TreeSchedule& s, int32_t H, int
   const int32_t n_internal = N - n_leaf;
   if (n_internal == 0 || (double)N * H * sizeof(float) >= kMaxBytes) return p;
   p.groups = stationary_groups(EPI_TREE_INTERNAL, H, 2 * H, ctx->n_cu);
+  const int32_t wide = s.level_off[2] - s.level_off[1];
+  // Groups of the smaller instances would fit a compute unit twice.  While a group's share of the widest level is small,
+  // one is better: half the weights to fetch (64 trees, H = 256 91 against 95 us, 300 trees 130 against 135; 1 024 trees
+  // 261 against 249; at H = 128 it makes no difference).
+  const int32_t once = 8 * (32 / std::max(H / 16, 1));
+  if (H >= 192 && once > 0 && wide <= 192 * once) p.groups = std::min(p.groups, once);
   // no more groups than trees of the first internal level can keep busy, and no offset table larger than the lists
   p.groups = std::min(p.groups, std::min(s.n_trees, s.level_off[2] - s.level_off[1]));
   p.groups = (int32_t)std::min<int64_t>(p.groups, (4 * (int64_t)N + 4096) / s.n_levels);
+  // A few large trees keep few groups busy: their wide levels run on the whole chip instead (one tree of 3 000 leaves,
+  // H = 512: 546 us with all levels in one launch, 442 with a launch per level).
+  if (p.groups > 0 && 2 * p.groups * (H / 16) <= ctx->n_cu)
+    while (p.first < s.n_levels && s.level_off[p.first + 1] - s.level_off[p.first] > 192 * p.groups) ++p.first;
+  if (p.first == s.n_levels) p.groups = 0;
   if (noalloc && (3 * (size_t)N + n_iota + (size_t)s.n_levels * p.groups + 1) * sizeof(int32_t) > kStaticIndexBytes) p.groups = 0;
   return p;
 }
@@ -806,7 +817,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     // Wide levels run on the split contraction: the weights they use are split first, and the leaves' embedding rows
     // get their scales, in one launch.
     const bool split_leaf = !plan.leaf && split_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ws);
-    const bool split_internal = plan.groups == 0 && n_wide > 0 && split_level_wins(EPI_TREE_INTERNAL, n_wide, H, 2 * H, ws);
+    const bool split_internal = (plan.groups == 0 || plan.first > 1) && n_wide > 0 && split_level_wins(EPI_TREE_INTERNAL, n_wide, H, 2 * H, ws);
     struct { unsigned char* w; float* scale; } split_w[2] = {};
     float* leaf_scale = nullptr;
     SplitRowsArgs split_rows{};
@@ -908,7 +919,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
         TRY(timer.end());
         continue;
       }
-      if (lv > 0 && plan.groups > 0) {
+      if (lv > 0 && plan.groups > 0 && lv >= plan.first) {
         sa.a[0] = a;  // lists by absolute position
         sa.a[0].idx0 -= off; sa.a[0].idx1 -= off; sa.a[0].out_rows -= off;
         sa.src_bytes = (uint32_t)((size_t)(unfused ? 2 * n : N) * H * sizeof(float));
@@ -924,7 +935,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
         HIP_TRY(ctx, launch_stationary(EPI_TREE_INTERNAL, sa, stream, timer.ev));
         TRY(timer.end());
         if (!one_launch) continue;
-        if (sa.stamps) ctx->stamped = {(int32_t)ctx->records.size() - 1, 1, s.n_levels, plan.groups, 1, s.level_off.data()};
+        if (sa.stamps) ctx->stamped = {(int32_t)ctx->records.size() - 1, lv, s.n_levels, plan.groups, 1, s.level_off.data()};
         return finish_stamped(ctx, timer);
       }
       HIP_TRY(ctx, launch_cell_level(lv == 0 ? EPI_TREE_LEAF : EPI_TREE_INTERNAL, a, stream, ws,

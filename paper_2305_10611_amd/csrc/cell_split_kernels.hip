@@ -156,10 +156,10 @@ __global__ __launch_bounds__(kThreads, 2) void cell_split_kernel(const CellLevel
     unsigned char* Bs = As + BM * 128;
 #pragma unroll
     for (int r = 0; r < WM; ++r) {
-      half4 hi, lo;
-      split4(ra[set][r], scale[r], hi, lo);
-      *reinterpret_cast<half4*>(As + 32 * r * 128 + st_hi) = hi;
-      *reinterpret_cast<half4*>(As + 32 * r * 128 + st_lo) = lo;
+      unsigned hi[2], lo[2];
+      split4_packed(ra[set][r], scale[r], hi, lo);
+      *reinterpret_cast<uint2*>(As + 32 * r * 128 + st_hi) = make_uint2(hi[0], hi[1]);
+      *reinterpret_cast<uint2*>(As + 32 * r * 128 + st_lo) = make_uint2(lo[0], lo[1]);
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) *reinterpret_cast<floatx4*>(Bs + 32 * g * 128 + st_b) = rb[set][g];

@@ -55,8 +55,26 @@ def test_tree_levels_in_one_launch(ctx, H, D, n, lo, hi):
 
 def test_more_rows_of_a_level_than_the_lists_in_lds_hold(ctx):
     from tests import parity as P
-    w = gen.treelstm_workload(2, 3000, 3300, 64, 50, "uniform", seed=5, bias_scale=0.2)  # two groups, about 1 000 rows each
+    w = gen.treelstm_workload(300, 100, 130, 512, 50, "uniform", seed=5, bias_scale=0.2, D=32)  # eight groups, 1 400 rows each
     h, c = P.run_treelstm(ctx, w)
+    oh, oc = oracle.treelstm(w, nthreads=NT)
+    assert rel(h, oh) < 1e-6 and rel(c, oc) < 1e-6
+
+
+@pytest.mark.parametrize("H,n,leaves", [(512, 1, 2000), (64, 2, 1500)])
+def test_wide_levels_of_a_few_large_trees_run_on_the_whole_chip(ctx, H, n, leaves):
+    from tests import parity as P
+    w = gen.treelstm_workload(n, leaves, leaves, H, 50, "uniform", seed=H, bias_scale=0.2, D=32)
+    ctx.acrobat_set_profiling(True)
+    try:
+        h, c = P.run_treelstm(ctx, w)
+        rec = ctx.acrobat_last_profile()
+    finally:
+        ctx.acrobat_set_profiling(False)
+    level_off, _ = ctx.acrobat_last_schedule()
+    assert [r[1] for r in rec] == list(range(len(level_off) - 1)) and [r[2] for r in rec] == list(np.diff(level_off))
+    assert rec[1][5] != 0 or rec[1][4] != 16  # level 1 on a level kernel ...
+    assert rec[-1][4:] == (16, 0)             # ... the last one in the launch for the rest
     oh, oc = oracle.treelstm(w, nthreads=NT)
     assert rel(h, oh) < 1e-6 and rel(c, oc) < 1e-6
 
