@@ -24,10 +24,13 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA_TFLOPS = 157.3  # MI355X dense fp32 matrix peak
+# products of fp32 operands that are split into two fp16 terms: three dense fp16 matrix instructions for one fp32 one
+PEAK_SPLIT_TFLOPS = 2516.6 / 3
 PEAK_HBM_GBS = 8000.0
 # ceilings measured on this machine: a loop of nothing but fp32 matrix instructions on all compute
 # units, and a plain streaming read by 256 workgroups
 MEASURED_MFMA_TFLOPS = 155.0
+MEASURED_SPLIT_TFLOPS = 1300.0 / 3  # (a large fp16 matrix product)
 MEASURED_HBM_GBS = 5800.0
 
 # HBM bytes per launch of the dominant kernel, from the committed rocprofv3 counter summaries
@@ -36,13 +39,11 @@ MEASURED_HBM_GBS = 5800.0
 # the figures are those of the library as of the commit named with each and are reported with that label, not as
 # live measurements; a workload without a summary reports null.
 MEASURED_TRAFFIC = {  # (workload, dominant kernel) -> (bytes per launch, summary, commit the library was at)
-    ("treelstm_h256_8x20", "kind=2 tile=16"): (3.43e6, "profiles/treelstm_h256_small_configs.md", "98cad87"),
     ("treelstm_h256_8x20", "kind=2 tile=6"): (3.64e6, "profiles/treelstm_h256_small_configs.md (stepwise kernel on every level)", "b76ed52"),
     ("treelstm_h256_64", "kind=2 tile=6"): (9.3e6, "profiles/treelstm_h256_small_configs.md", "e1d1bbb"),
     ("treelstm_h512_256", "kind=2 tile=64"): (80.0e6, "profiles/treelstm_h512_256_cell_level_kernel.md", "90fe6c3"),
     ("mvrnn_d64_64", "kind=14 tile=0"): (81.6e6, "profiles/mvrnn_d64_64_mvrnn_level_kernel.md", "0f6c915"),
     ("mvrnn_d64_64", "kind=3 tile=1"): (6.9e6, "profiles/mvrnn_d64_64_mvrnn_level_kernel.md (one launch per level)", "b76ed52"),
-    ("lstm_h512_256", "kind=13 tile=16"): (227.9e6, "profiles/lstm_h512_256_cell_kernels.md", "2065830"),
     ("lstm_h512_256", "kind=6 tile=6"): (12.3e6, "profiles/lstm_h512_256_cell_kernels.md (one launch per step)", "138cebb"),
     ("paper_birnn_large_bs64", "kind=15 tile=16"): (24.5e6, "profiles/birnn_large_64_and_mvrnn_d128_64.md", "2065830"),
 }
@@ -457,9 +458,16 @@ def main():
             e[2] += ms
     dom_tile = max(by_tile, key=lambda q: by_tile[q][2])
     launches, units, ms_sum = by_tile[dom_tile]
+    # Kernels on split fp16 operands are held against the fp16 matrix rate: the levels of a tree batch and the recurrences
+    # of other sizes than 128 and 256 on the one-launch path.
+    on_split = args.persistent == "auto" and not args.tuning and (
+        kind == "treelstm" and H <= 512 or kind == "lstm" and H >= 128 and H not in (128, 256) or
+        kind == "birnn" and H >= 128 and dominant == A.binding.K_RNN_STEP)
+    peak_matrix, measured_matrix = ((PEAK_SPLIT_TFLOPS, MEASURED_SPLIT_TFLOPS) if on_split else
+                                    (PEAK_FP32_MFMA_TFLOPS, MEASURED_MFMA_TFLOPS))
     if bound == "mfma":
         achieved = units * flops_per[dominant] / (ms_sum * 1e-3) / 1e12
-        peak, unit = PEAK_FP32_MFMA_TFLOPS, "TFLOP/s"
+        peak, unit = round(peak_matrix, 1), "TFLOP/s"
     else:
         achieved = (units * bytes_per[dominant] + launches * weight_bytes[dominant]) / (ms_sum * 1e-3) / 1e9
         peak, unit = PEAK_HBM_GBS, "GB/s"
@@ -479,8 +487,8 @@ def main():
     agg = {"datasheet": 0.0, "measured_ceilings": 0.0}
     for k, lv, n, tile, ms, ks in per_launch:
         if k in flops_per:
-            agg["datasheet"] += floor_ms(k, n, PEAK_FP32_MFMA_TFLOPS, PEAK_HBM_GBS)
-            agg["measured_ceilings"] += floor_ms(k, n, MEASURED_MFMA_TFLOPS, MEASURED_HBM_GBS)
+            agg["datasheet"] += floor_ms(k, n, peak_matrix, PEAK_HBM_GBS)
+            agg["measured_ceilings"] += floor_ms(k, n, measured_matrix, MEASURED_HBM_GBS)
     agg = {key: round(v / t_device_ms, 4) for key, v in agg.items()}
     # the dominant kernel is only part of the step: the same fraction for the whole step (every launch, the gaps
     # between them, host scheduling and upload), so that the headline figure is not mistaken for it
@@ -501,8 +509,8 @@ def main():
             fl = n * flops_per[k]
             by = n * bytes_per[k] + weight_bytes[k]
             tf, gbs = fl / ms / 1e9, by / ms / 1e6
-            which = "mfma" if fl / (PEAK_FP32_MFMA_TFLOPS * 1e9) >= by / (PEAK_HBM_GBS * 1e6) else "hbm"
-            print(f"{k:>4} {lv:>4} {n:>6} {tile:>4} {ks:>3} {ms * 1e3:>9.2f} {tf:>8.2f} {100 * tf / PEAK_FP32_MFMA_TFLOPS:>6.1f} "
+            which = "mfma" if fl / (peak_matrix * 1e9) >= by / (PEAK_HBM_GBS * 1e6) else "hbm"
+            print(f"{k:>4} {lv:>4} {n:>6} {tile:>4} {ks:>3} {ms * 1e3:>9.2f} {tf:>8.2f} {100 * tf / peak_matrix:>6.1f} "
                   f"{gbs:>8.1f} {100 * gbs / PEAK_HBM_GBS:>6.1f} {which:>5}", file=sys.stderr)
         print(f"device sum {t_device_ms:.3f} ms, end-to-end {ms_per_step:.3f} ms/step, schedule {t_schedule_ms:.3f} ms",
               file=sys.stderr)

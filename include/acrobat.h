@@ -175,10 +175,10 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
 
 /* Level-launch strategy of the recurrence (the paper's activity breakdown, table 6, and its remark on
  * persistence in Evaluation, "Overall Performance": launch overhead is of the order of the kernel time).
- * Enabled (the default), acrobat_varlen_lstm_forward runs all time steps in ONE launch whenever H is 128,
- * 256 or 512, at most 256 sequences have a step to run, and every workgroup of that launch is resident on
- * the GPU at once (an occupancy query; otherwise, or when disabled, one launch per step as described
- * above).  The batches are the same - step t over the sequences with len > t - and so is the schedule
+ * Enabled (the default), acrobat_varlen_lstm_forward runs all time steps in ONE launch whenever H is 128
+ * or 256, at most 256 sequences have a step to run, and every workgroup of that launch is resident on
+ * the GPU at once (an occupancy query), and for other sizes as described further down (otherwise, or when
+ * disabled, one launch per step as described above).  The batches are the same - step t over the sequences with len > t - and so is the schedule
  * that acrobat_last_schedule reports; the workgroups keep W_h on chip for all steps and synchronise
  * among themselves through arrival counters in device memory.  Every wait inside that kernel is bounded
  * by max_polls polls of a counter (max_polls < 0: the default, about a quarter of a million; max_polls == 0 is a
@@ -205,7 +205,8 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
  * out to groups of H / 16 workgroups that keep U on chip, and a group runs all internal levels of its trees in ONE
  * launch, its workgroups waiting for each other between levels (max_polls < 0: up to sixteen million polls there).
  * A captured call, and one with explicit gathers, launches the same kernel once per level instead, with the same
- * results bit for bit.  With profiling on, the levels of the one launch are timed by clock stamps inside it.
+ * results bit for bit (one for which no call of its size has made room before the capture takes the kernels of the
+ * disabled path where those need none).  With profiling on, the levels of the one launch are timed by clock stamps inside it.
  * Nothing else may occupy the GPU's compute units for long while such a launch runs (another stream's
  * kernels delay the workgroups that are not yet resident; the bound turns a too long delay into
  * ACROBAT_ETIMEOUT instead of a hang).  Two launches of this kind must never share the GPU - each could hold

@@ -252,16 +252,28 @@ int reserve_scratch(acrobat_ctx* ctx, size_t n_floats, hipStream_t stream) {
   return ACROBAT_OK;
 }
 
-int reserve_split(acrobat_ctx* ctx, size_t bytes, hipStream_t stream) {
-  if (bytes <= ctx->split_cap) return ACROBAT_OK;
-  if (stream_is_capturing(stream)) return fail(ctx, ACROBAT_EINVAL, "stream capture: split workspace too small, run once without capture first");
-  if (ctx->d_split) HIP_TRY(ctx, hipFree(ctx->d_split));  // waits for kernels still using it
+// Whether reserve_indices(n) can be had: a call under capture that lacks the room for an offset table goes without it.
+bool indices_fit(acrobat_ctx* ctx, size_t n, hipStream_t stream) {
+  return (n <= ctx->stage_cap && n <= ctx->idx_cap) || !stream_is_capturing(stream);
+}
+
+// Room for split weights and row scales.  False where there is none - the stream is being captured and no call of this
+// size came before, or the device memory is used up: the level then runs on the fp32 tiles, which need none.
+bool reserve_split(acrobat_ctx* ctx, size_t bytes, hipStream_t stream) {
+  if (bytes <= ctx->split_cap) return true;
+  if (stream_is_capturing(stream)) return false;
+  if (ctx->d_split) (void)hipFree(ctx->d_split);  // waits for kernels still using it
   ctx->d_split = nullptr;
   ctx->split_cap = 0;
   const size_t cap = bytes + bytes / 8;  // (the row scales grow with the batch)
-  HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&ctx->d_split), cap));
+  void* p = nullptr;
+  if (hipMalloc(&p, cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  ctx->d_split = static_cast<unsigned char*>(p);
   ctx->split_cap = cap;
-  return ACROBAT_OK;
+  return true;
 }
 
 // Partial-tile workspace of the k-split levels: 128 MiB.
@@ -633,7 +645,7 @@ TreePlan plan_tree(const acrobat_ctx* ctx, const TreeSchedule& s, int32_t H, int
   p.groups = std::min(p.groups, std::min(s.n_trees, s.level_off[2] - s.level_off[1]));
   p.groups = (int32_t)std::min<int64_t>(p.groups, (4 * (int64_t)N + 4096) / s.n_levels);
   // A few large trees keep few groups busy: their wide levels run on the whole chip instead (one tree of 3 000 leaves,
-  // H = 512: 546 us with all levels in one launch, 442 with a launch per level).
+  // H = 512: 546 us with all levels in one launch, 442 with a launch per level, 371 this way).
   if (p.groups > 0 && 2 * p.groups * (H / 16) <= ctx->n_cu)
     while (p.first < s.n_levels && s.level_off[p.first + 1] - s.level_off[p.first] > 192 * p.groups) ++p.first;
   if (p.first == s.n_levels) p.groups = 0;
@@ -749,7 +761,8 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     for (int32_t lv = 1; lv < s.n_levels; ++lv) n_wide = std::max(n_wide, s.level_off[lv + 1] - s.level_off[lv]);
     const bool unfused = !ctx->gather_fusion && !noalloc;
     const size_t n_iota = unfused ? (size_t)std::max(n_leaf, 2 * n_wide) : 0;
-    const TreePlan plan = plan_tree(ctx, s, H, D, V, noalloc, n_iota);
+    TreePlan plan = plan_tree(ctx, s, H, D, V, noalloc, n_iota);
+    if (!noalloc && !indices_fit(ctx, 3 * (size_t)N + n_iota + (size_t)s.n_levels * plan.groups + 1, stream)) plan.groups = 0;
     const size_t n_off = plan.groups > 0 ? (size_t)s.n_levels * plan.groups + 1 : 0;
     // (Uploading the leaf lists and launching level 0 before the internal levels are sorted was measured and
     // dropped: the second upload sits behind the leaf kernel in stream order, so its three copy commands land
@@ -828,8 +841,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
       const size_t bytes = (leaf_bytes + int_bytes + scale_bytes + 255) / 256 * 256;
       unsigned char* at = nullptr;
       if (!noalloc) {
-        TRY(reserve_split(ctx, bytes, stream));
-        at = ctx->d_split;
+        if (reserve_split(ctx, bytes, stream)) at = ctx->d_split;
       } else if (bytes <= ws.partial_floats * sizeof(float)) {  // the end of the partial tiles' region
         ws.partial_floats -= bytes / sizeof(float);
         at = reinterpret_cast<unsigned char*>(ws.partial + ws.partial_floats);
@@ -1183,8 +1195,8 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
     TRY(reserve_splitk(ctx, stream));
     TRY(reserve_scratch(ctx, (size_t)R * 4 * (size_t)H, stream));
     const size_t split_bytes = (size_t)4 * H * D * sizeof(float);
-    const bool split = split_level_wins(EPI_STORE_Z, R, H, D, ctx->splitk);
-    if (split) TRY(reserve_split(ctx, split_bytes + ((size_t)4 * H + R) * sizeof(float), stream));
+    const bool split = split_level_wins(EPI_STORE_Z, R, H, D, ctx->splitk) &&
+                       reserve_split(ctx, split_bytes + ((size_t)4 * H + R) * sizeof(float), stream);
     auto input_transform = [&](LaunchTimer& timer) {  // hoisted: every step of every sequence in one dense batch
       CellLevelArgs a{};
       a.n = R; a.H = H; a.nseg = 1; a.kseg = D;
@@ -1214,8 +1226,8 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
     {
       const SeqPlan plan = (H == 128 || H == 256) && n_live <= kLstmSlots * kLstmMaxBlocks
                                ? SeqPlan() : plan_recurrence(ctx, EPI_LSTM_STEP, H, R, n_live, s.n_levels, 1);
-      if (plan.groups > 0) {
-        const size_t n_off = (size_t)s.n_levels * plan.groups + 1;
+      const size_t n_off = (size_t)s.n_levels * plan.groups + 1;
+      if (plan.groups > 0 && indices_fit(ctx, 2 * (size_t)R + n_off, stream)) {
         TRY(reserve_indices(ctx, 2 * (size_t)R + n_off, stream));
         int32_t* st = ctx->h_stage;
         stage_seq_groups(n_seq, len, s.n_levels, plan.groups, 1, st, st + R, st + 2 * (size_t)R);
@@ -1240,7 +1252,9 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
         lstm_persistent_eligible(H, n_blocks, nullptr)) {
       TRY(reserve_sync(ctx, stream));
       const size_t n_slots = (size_t)n_blocks * slots;
-      TRY(reserve_indices(ctx, 2 * n_slots, stream));
+      // (at least what a launch per step needs, so that a smaller call with other sizes can be captured afterwards)
+      const size_t n_idx = stream_is_capturing(stream) ? 2 * n_slots : 2 * std::max(n_slots, (size_t)R);
+      TRY(reserve_indices(ctx, n_idx, stream));
       int32_t* st = ctx->h_stage;
       // sequences by non-increasing length (ties by id): a counting sort over the lengths; rank r goes to block
       // r / slots, slot r % slots, so a block's live slots are a prefix at every step, its sequences are of
@@ -1374,9 +1388,10 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
     const bool persistent = ctx->persistent && T >= 2 && (double)R * H * sizeof(float) < 4294967296.0 &&
                             rnn_persistent_eligible(H, 2 * blocks_per_dir, nullptr);
     const size_t n_slots = (size_t)blocks_per_dir * kRnnSlots;
-    const SeqPlan plan = persistent ? SeqPlan() : plan_recurrence(ctx, EPI_RNN_STEP, H, R, n_live, T, 2);
+    SeqPlan plan = persistent ? SeqPlan() : plan_recurrence(ctx, EPI_RNN_STEP, H, R, n_live, T, 2);
+    const size_t n_off = (size_t)T * plan.groups + 1;
+    if (!indices_fit(ctx, 4 * (size_t)R + n_off, stream)) plan.groups = 0;
     if (plan.groups > 0) {
-      const size_t n_off = (size_t)T * plan.groups + 1;
       TRY(reserve_indices(ctx, 4 * (size_t)R + n_off, stream));
       int32_t* st = ctx->h_stage;
       stage_seq_groups(n_seq, len, T, plan.groups, 2, st, st + 2 * (size_t)R, st + 4 * (size_t)R);

@@ -10,7 +10,7 @@
 namespace acrobat {
 
 constexpr int kLstmSlots = 16;           // sequences per node block of the LSTM launch
-constexpr int kLstmMaxBlocks = 16;       // its node blocks at most (two per XCD; at H = 512 two workgroups per compute unit)
+constexpr int kLstmMaxBlocks = 16;       // its node blocks at most (two per XCD)
 constexpr int kPersistMaxBlocks = 8;     // groups of the probe at most (one per XCD)
 constexpr int kPersistMaxColBlocks = 32;   // workgroups per node block at most (H = 512)
 constexpr int kPersistCounterStride = 32;  // uint32 between two groups' arrival counters of the probe (one cache line each)

@@ -72,10 +72,10 @@ __global__ void fill_u32_kernel(unsigned* p, unsigned value, int n) {
 // 16-byte LDS read feeds four instructions), and holds z[slot 4 (l/16) + v][unit l%16] in result register v.
 // A step is one 16-row product per wavefront whatever the number of live slots; a block's sequences are of similar
 // length (the host sorts them), so few of those rows are dead.
-// At H = 512 sixteen blocks are 512 workgroups, two per compute unit (204 registers each): one multiplies while the
-// other exchanges its rows.  The two that share a compute unit have ids 256 apart and must belong to different
-// blocks - workgroups of one block wait for each other, and as co-residents they were measured to take turns
-// (8 us per step instead of 5.3) - hence the numbering below.
+// Blocks whose workgroups have ids 256 apart may share a compute unit and must be different ones - workgroups of one
+// block wait for each other, and as co-residents they were measured to take turns - hence the numbering below.
+// Instances: H = 128 and 256.  At H = 512 the weight-stationary kernel steps faster (393 against 443 us for 256
+// sequences of 1 to 100 steps); here it is slower (262 against 216 us at H = 128, 293 against 283 at H = 256).
 template <int H>
 __global__ __launch_bounds__(kThreads, 2) void lstm_persistent_kernel(const LstmPersistentArgs a) {
   constexpr int CB = H / 16;   // column blocks = workgroups per node block

@@ -229,6 +229,43 @@ def test_recurrences_recorded_into_a_graph():
         ctx.close()
 
 
+def test_captured_calls_without_room_for_the_split_take_the_fp32_tiles():
+    """The call before the capture needs no split weights and shorter lists; the captured one does without them."""
+    import torch
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    small = gen.treelstm_workload(300, 20, 20, 32, 200, "uniform", seed=5, D=32)
+    w = gen.treelstm_workload(300, 20, 20, 512, 200, "uniform", seed=5, D=32)
+    small_s = gen.lstm_workload(200, 20, 60, 256, 512, seed=6)
+    s = gen.lstm_workload(90, 20, 60, 512, 512, seed=7)
+    ctx = A.Context(0)
+    try:
+        P.run_treelstm(ctx, small)
+        P.run_lstm(ctx, small_s)
+        N, R, H = int(w["tree_off"][-1]), int(np.sum(s["len"])), 512
+        t = {k: P.dev(w[k]) for k in ("emb", "W_leaf", "b_leaf", "U", "b")}
+        q = {k: P.dev(s[k]) for k in ("x", "Wx", "Wh", "b")}
+        h, c, hs, cs = P.nan_filled(N, H), P.nan_filled(N, H), P.nan_filled(R, H), P.nan_filled(R, H)
+        st = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        graphs = []
+        for call in (lambda: ctx.acrobat_treelstm_forward(w, H, 32, int(w["V"]), t["emb"], t["W_leaf"], t["b_leaf"], t["U"],
+                                                          t["b"], h, c, st.cuda_stream),
+                     lambda: ctx.acrobat_varlen_lstm_forward(s["len"], H, 512, q["x"], q["Wx"], q["Wh"], q["b"], hs, cs,
+                                                             st.cuda_stream)):
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=st, capture_error_mode="relaxed"):
+                rc = call()
+            assert rc == A.OK, ctx.acrobat_last_error()
+            g.replay()  # (before the next call: a graph's upload reads the context's staging buffer)
+            torch.cuda.synchronize()
+            graphs.append(g)
+        for got, want in zip((h, c, hs, cs), (*oracle.treelstm(w, nthreads=NT), *oracle.varlen_lstm(s, nthreads=NT))):
+            assert rel(got.cpu().numpy(), want) < 1e-6
+    finally:
+        ctx.close()
+
+
 @pytest.mark.parametrize("trees,lo,hi", [(300, 2, 3), (140, 4, 30), (257, 2, 2)])
 def test_mvrnn_d128_one_workgroup_per_node(ctx, trees, lo, hi):
     """More nodes in a level than compute units: one workgroup per node, in one launch and level by level the same bits."""
