@@ -142,6 +142,9 @@ struct acrobat_ctx {
   // split weights, row scales (launch_split_rows); rewritten by every call that uses them
   unsigned char* d_split = nullptr;
   size_t split_cap = 0;  // in bytes
+  // packed operands and c states of the launch in progress (packed_kernels.hip)
+  unsigned char* d_packed = nullptr;
+  size_t packed_cap = 0;  // in bytes
   bool gather_fusion = true;  // false: explicit gather launches (ablation)
   int mvrnn_variant = 0;  // which MV-RNN level kernel (acrobat_set_tuning): 1 = streaming
   // tree generation: a zero row (previous-sibling state of a first child) and the scores on the host
@@ -284,6 +287,24 @@ bool reserve_split(acrobat_ctx* ctx, size_t bytes, hipStream_t stream) {
   }
   ctx->d_split = static_cast<unsigned char*>(p);
   ctx->split_cap = cap;
+  return true;
+}
+
+// Room for packed operands; false where there is none, as for the split: the rows are then gathered from the arena.
+bool reserve_packed(acrobat_ctx* ctx, size_t bytes, hipStream_t stream) {
+  if (bytes <= ctx->packed_cap) return true;
+  if (stream_is_capturing(stream)) return false;
+  if (ctx->d_packed) (void)hipFree(ctx->d_packed);  // waits for kernels still using it
+  ctx->d_packed = nullptr;
+  ctx->packed_cap = 0;
+  const size_t cap = bytes + bytes / 4;  // (batches of one kind differ by a few nodes)
+  void* p = nullptr;
+  if (hipMalloc(&p, cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  ctx->d_packed = static_cast<unsigned char*>(p);
+  ctx->packed_cap = cap;
   return true;
 }
 
@@ -544,6 +565,7 @@ void acrobat_destroy(acrobat_ctx* ctx) {
   if (ctx->d_idx) (void)hipFree(ctx->d_idx);
   if (ctx->d_scratch) (void)hipFree(ctx->d_scratch);
   if (ctx->d_split) (void)hipFree(ctx->d_split);
+  if (ctx->d_packed) (void)hipFree(ctx->d_packed);
   if (ctx->d_stamps) (void)hipFree(ctx->d_stamps);
   if (ctx->splitk.partial) (void)hipFree(ctx->splitk.partial);
   if (ctx->splitk.counters) (void)hipFree(ctx->splitk.counters);
@@ -642,7 +664,7 @@ TreePlan plan_tree(const acrobat_ctx* ctx, const TreeSchedule& s, int32_t H, int
   if (!tiles && (double)std::max(V, N) * D * sizeof(float) < kMaxBytes) p.leaf = stationary_groups(EPI_TREE_LEAF, H, D, ctx->n_cu);
   const int32_t n_internal = N - n_leaf;
   if (n_internal == 0 || (double)N * H * sizeof(float) >= kMaxBytes) return p;
-  p.groups = stationary_groups(EPI_TREE_INTERNAL, H, 2 * H, ctx->n_cu);
+  p.groups = std::min(stationary_groups(EPI_TREE_INTERNAL, H, 2 * H, ctx->n_cu), packed_groups(EPI_TREE_INTERNAL, H, 2 * H, 0, ctx->n_cu));
   const int32_t wide = s.level_off[2] - s.level_off[1];
   // Groups of the smaller instances would fit a compute unit twice.  While a group's share of the widest level is small,
   // one is better: half the weights to fetch (64 trees, H = 256 91 against 95 us, 300 trees 130 against 135; 1 024 trees
@@ -684,7 +706,7 @@ int launch_waiting_levels(acrobat_ctx* ctx, CellEpilogue epi, const StationaryAr
                           const LaunchEvents& ev) {
   HIP_TRY(ctx, enqueue_waiting_launch(ctx->device, stream, ev, [&](const LaunchEvents& events) {
             const hipError_t e = clean_group_counters(ctx, sa.counters, noalloc, stream);
-            return e != hipSuccess ? e : launch_stationary(epi, sa, stream, events);
+            return e != hipSuccess ? e : sa.operand ? launch_packed(epi, sa, stream, events) : launch_stationary(epi, sa, stream, events);
           }));
   return ACROBAT_OK;
 }
@@ -791,6 +813,21 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     TreePlan plan = plan_tree(ctx, s, H, D, V, noalloc, n_iota);
     if (!noalloc && !indices_fit(ctx, 3 * (size_t)N + n_iota + (plan.grouped ? (size_t)s.n_levels * plan.groups + 1 : 0), stream)) plan.groups = 0;
     const size_t n_off = plan.groups > 0 && plan.grouped ? (size_t)s.n_levels * plan.groups + 1 : 0;
+    // Stationary launches of the plan: level 0, then the internal levels - in one launch, whose workgroups wait for each
+    // other, unless the call is captured into a graph (launches of that kind must take turns, which replays cannot be
+    // made to do), cannot be given its turn, or gathers explicitly between levels; then the levels run one by one, with the
+    // same results.
+    const bool one_launch = plan.groups > 0 && !unfused && !stream_is_capturing(stream) && may_wait(ctx, stream);
+    // One launch of several levels takes its operands packed, given the room: blocks of 16 nodes, 8 H bytes of split states
+    // and as much of c states for each.
+    // (The leaf kernels on tiles do not know about places: for 36 000 leaves at H = 512 a launch that takes their states there
+    // costs 95 us, which is all that the levels save.)
+    const int64_t blocks = one_launch && plan.leaf && n_off > 0 && s.n_levels - plan.first > 1
+                               ? share_blocks((int64_t)N - s.level_off[plan.first], (int64_t)s.n_levels * plan.groups) : 0;
+    const size_t operand_bytes = (size_t)blocks * 128 * H;
+    bool packed = blocks > 0 && (double)blocks * 128 * H <= kPackedMaxBytes &&
+                  (!noalloc || (4 * (size_t)N + n_off) * sizeof(int32_t) <= kStaticIndexBytes);
+    packed = packed && (noalloc || reserve_packed(ctx, 2 * operand_bytes, stream));
     // (Uploading the leaf lists and launching level 0 before the internal levels are sorted was measured and
     // dropped: the second upload sits behind the leaf kernel in stream order, so its three copy commands land
     // between level 0 and level 1 - 0.731 instead of 0.691 ms per forward on 17 134 nodes - while the sort
@@ -815,12 +852,21 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
       ws.n_cu = ctx->n_cu;
     } else {
       TRY(reserve_splitk(ctx, stream));
-      TRY(reserve_indices(ctx, 3 * (size_t)N + n_iota + n_off, stream));
+      TRY(reserve_indices(ctx, 3 * (size_t)N + n_iota + n_off + (packed ? (size_t)N : 0), stream));
       st = ctx->h_stage;
       d_idx = ctx->d_idx;
       ws = ctx->splitk;
     }
-    // staging layout: out row | first operand row (token at a leaf) | second operand row, N entries each
+    unsigned char* packed_at = ctx->d_packed;
+    if (packed && noalloc) {  // the end of the partial tiles' region; a quarter of it stays
+      const size_t floats = 2 * operand_bytes / sizeof(float);
+      packed = floats <= ws.partial_floats / 4 * 3;
+      if (packed) {
+        ws.partial_floats -= floats;
+        packed_at = reinterpret_cast<unsigned char*>(ws.partial + ws.partial_floats);
+      }
+    }
+    // staging layout: out row | first operand row (token at a leaf) | second operand row, N entries each | offsets | places
     const size_t n_int = (size_t)(N - n_leaf);
     auto stage_leaves = [&]() {
       std::memcpy(st, s.level_nodes.data(), (size_t)n_leaf * sizeof(int32_t));
@@ -842,12 +888,15 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     };
     if (unfused) TRY(reserve_scratch(ctx, std::max((size_t)n_leaf * D, 4 * (size_t)n_wide * H), stream));
     finish.now();
-    stage_leaves();
+    if (!packed) stage_leaves();  // (else in the order of their places, below)
     if (n_off > 0)
       ctx->tree_groups.stage(*trees, s, plan.groups, plan.in_order, st, st + N, st + 2 * (size_t)N, st + 3 * (size_t)N + n_iota);
     else stage_internal();
+    const size_t at_off = 3 * (size_t)N + n_iota, at_place = at_off + n_off;
+    if (packed)
+      ctx->tree_groups.places(s, ctx->leaf_tokens, plan.groups, plan.first, st, st + N, st + 2 * (size_t)N, st + at_off, st + at_place);
     for (size_t i = 0; i < n_iota; ++i) st[3 * (size_t)N + i] = (int32_t)i;
-    HIP_TRY(ctx, copy_up(0, 3 * (size_t)N + n_iota + n_off));  // one upload (the second operands of level 0 are never read)
+    HIP_TRY(ctx, copy_up(0, at_place + (packed ? (size_t)N : 0)));  // one upload (the second operands of level 0 are never read)
     HIP_TRY(ctx, staging_in_flight());
     const int32_t* d_out = d_idx;
     const int32_t* d_ia = d_idx + N;
@@ -890,11 +939,6 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
         split_rows = sr;
       }
     }
-    // Stationary launches of the plan: level 0, then the internal levels - in one launch, whose workgroups wait for each
-    // other, unless the call is captured into a graph (launches of that kind must take turns, which replays cannot be
-    // made to do), cannot be given its turn, or gathers explicitly between levels; then the same kernel runs level by
-    // level, with the same results.
-    const bool one_launch = plan.groups > 0 && !unfused && !stream_is_capturing(stream) && may_wait(ctx, stream);
     StationaryArgs sa{};
     sa.n_cb = H / 16;
     sa.counters = ws.counters;
@@ -952,6 +996,12 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
       }
       if (lv == 0 && plan.leaf) {
         sa.a[0] = a;
+        if (packed) {
+          sa.operand = packed_at;
+          sa.operand_bytes = (uint32_t)operand_bytes;
+          sa.cells = reinterpret_cast<float*>(packed_at + operand_bytes);
+          sa.place = d_idx + at_place;
+        }
         sa.src_bytes = (uint32_t)((size_t)(unfused ? n : V) * D * sizeof(float));
         sa.n_groups = std::min(plan.leaf, (n + 15) / 16);
         sa.level0 = 0; sa.level1 = 1;
@@ -959,6 +1009,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
         if (timer.ksplit()) *timer.ksplit() = -1;
         HIP_TRY(ctx, launch_stationary(EPI_TREE_LEAF, sa, stream, timer.ev));
         TRY(timer.end());
+        sa.operand = nullptr;
         continue;
       }
       if (lv > 0 && plan.groups > 0 && lv >= plan.first) {
@@ -975,6 +1026,19 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
         if (timer.tile()) *timer.tile() = 16;
         if (timer.ksplit()) *timer.ksplit() = sa.level1 - lv > 1 ? 0 : -1;
         if (sa.level1 - lv > 1) {
+          if (packed) {  // the states that are there already, to their places (timed with the levels)
+            sa.operand = packed_at;
+            sa.operand_bytes = (uint32_t)operand_bytes;
+            sa.cells = reinterpret_cast<float*>(packed_at + operand_bytes);
+            sa.place = d_idx + at_place;
+            sa.first_position = off;
+            const int32_t there = plan.leaf ? n_leaf : 0;  // (that kernel has taken the leaves' there)
+            if (off > there) {
+              LaunchEvents first;
+              std::swap(first.start, timer.ev.start);
+              HIP_TRY(ctx, launch_pack_states({off - there, H, d_out + there, sa.place + there, d_h, d_c, sa.operand, sa.cells}, stream, first));
+            }
+          }
           if (timer.on()) TRY(reserve_stamps(ctx, (size_t)s.n_levels * plan.groups, stream, &sa.stamps));
           TRY(launch_waiting_levels(ctx, EPI_TREE_INTERNAL, sa, noalloc, stream, timer.ev));
         } else {
@@ -1000,30 +1064,41 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
 
 // Groups a recurrence over sequences is dealt out to for one launch of the stationary kernel; 0: not on that kernel.
 struct SeqPlan {
-  int32_t groups = 0;
+  int32_t groups = 0, variant = 0;
   bool whole = false;  // one launch record for all steps (else one per step)
+  size_t n_off = 0, n_idx = 0;  // entries of the offset table; of all lists: rows, previous rows, offsets, places
+  size_t operand_bytes = 0;     // of packed states; c states take as much
 };
 
-SeqPlan plan_recurrence(const acrobat_ctx* ctx, CellEpilogue epi, int32_t H, int32_t R, int32_t n_live, int32_t n_steps,
+SeqPlan plan_recurrence(acrobat_ctx* ctx, CellEpilogue epi, int32_t H, int32_t R, int32_t n_live, int32_t n_steps,
                         int32_t directions, hipStream_t stream) {
   SeqPlan p;
   if (!ctx->persistent || ctx->splitk.force_bm || H < 128 || n_steps < 2 || (double)R * H * sizeof(float) >= 4294967296.0 - 512.0)
     return p;
-  // The kernels that were made for H = 128 and 256 step faster there, as does the one for the BiRNN at all its sizes
-  // (LSTM, 256 sequences of 1 to 100 steps: H = 128 216 against 262 us, H = 256 283 against 293, H = 512 443 against 393;
-  // BiRNN, H = 512, 64 sequences 87 against 119).  Below H = 128 a step is a launch of 4 us.
-  int32_t most = stationary_groups(epi, H, H, ctx->n_cu) / directions;
-  // A single gate leaves room for four workgroups per compute unit, but more than one only get in each other's way
-  // (600 sequences, H = 256: all steps 187, 143 and 137 us with four, two and one; H = 128, 1 000 sequences 115, 96, 106).
-  if (epi == EPI_RNN_STEP) most = std::min(most, 8 * ((H < 256 ? 64 : 32) / (H / 16)) / directions);
+  // The kernels of persistent_kernels.hip step faster at H = 128 and, with a single gate, 256 while a batch has at most 256
+  // sequences, and with a single gate at H = 512 while their workgroups have a compute unit each (LSTM, sequences of 1
+  // to 60 steps, H = 128, 8 / 256 sequences 115 / 148 against 128 / 168 us, but H = 256 160 / 201 against 140 / 184.  BiRNN, 1 to 40 steps, H = 128 82 / 100 against 93 / 119, H = 256 91 / 136 against 97 / 143; H = 512,
+  // 64 sequences 138 against 141, 128 200 against 158, 256 354 against 202).  Below H = 128 a step is a launch of 4 us.
+  p.variant = packed_variant(epi, H, n_live, directions, ctx->n_cu);
+  const int32_t most = packed_groups(epi, H, H, p.variant, ctx->n_cu) / directions;
   p.groups = directions * std::min({most, (n_live + 15) / 16, (int32_t)((4 * (int64_t)R + 4096) / n_steps)});
-  p.whole = epi == EPI_LSTM_STEP && H == 512 && n_live <= 256;  // (larger batches have always been reported step by step)
+  // (the sizes that have always been one launch with one record)
+  p.whole = n_live <= 256 && (H == 512 || (epi == EPI_LSTM_STEP && H == 256));
   // Launches that wait must take turns, which replays of a graph cannot be made to do: a captured call takes a launch per
-  // step, except for the size whose captured calls have always been one launch (256 sequences of 1 to 100 steps replay in
-  // 529 us, step by step in 1 502).  Step by step the level kernels are faster, which need not fetch all weights first (75
+  // step, except for the sizes whose captured calls have always been one launch (LSTM, H = 512, 256 sequences of 1 to 100
+  // steps step by step: 1 502 us).  Step by step the level kernels are faster, which need not fetch all weights first (75
   // sequences of 1 to 60, H = 320: 351 against 537 us), but for wide single-gate steps (BiRNN, 600 sequences, H = 384 437
   // against 599, H = 192 234 against 248, H = 128 204 against 180; 64 sequences, H = 384 225 against 179).
   if (!p.whole && stream_is_capturing(stream) && !(epi == EPI_RNN_STEP && n_live > 256 && H >= 192)) p.groups = 0;
+  if (p.groups == 0) return p;
+  const int64_t entries = (int64_t)directions * R, blocks = share_blocks(entries, (int64_t)n_steps * p.groups);
+  p.n_off = (size_t)n_steps * p.groups + 1;
+  p.n_idx = 3 * (size_t)entries + p.n_off;
+  p.operand_bytes = (size_t)blocks * 64 * H;
+  // (a captured call that lacks the room does without)
+  if ((double)p.operand_bytes > kPackedMaxBytes || !indices_fit(ctx, p.n_idx, stream) ||
+      !reserve_packed(ctx, (epi == EPI_LSTM_STEP ? 2 : 1) * p.operand_bytes, stream))
+    p.groups = 0;
   return p;
 }
 
@@ -1032,7 +1107,11 @@ int run_recurrence(acrobat_ctx* ctx, CellEpilogue epi, StationaryArgs& sa, const
                    const int32_t* step_off, int32_t directions, int32_t R, LaunchTimer& timer) {
   const int32_t H = sa.a[0].H;
   sa.src_bytes = (uint32_t)((size_t)R * H * sizeof(float));
-  sa.n_cb = H / 16;
+  sa.operand = ctx->d_packed;
+  sa.operand_bytes = (uint32_t)plan.operand_bytes;
+  sa.cells = reinterpret_cast<float*>(ctx->d_packed + plan.operand_bytes);
+  sa.n_cb = packed_members(epi, H, plan.variant);
+  sa.variant = plan.variant;
   sa.n_groups = plan.groups;
   sa.counters = ctx->splitk.counters;
   sa.status = ctx->h_status_dev;
@@ -1051,7 +1130,7 @@ int run_recurrence(acrobat_ctx* ctx, CellEpilogue epi, StationaryArgs& sa, const
       if (timer.on() && !plan.whole) TRY(reserve_stamps(ctx, (size_t)n_steps * plan.groups, timer.stream, &sa.stamps));
       TRY(launch_waiting_levels(ctx, epi, sa, false, timer.stream, timer.ev));
     } else {
-      HIP_TRY(ctx, launch_stationary(epi, sa, timer.stream, timer.ev));
+      HIP_TRY(ctx, launch_packed(epi, sa, timer.stream, timer.ev));
     }
     TRY(timer.end());
   }
@@ -1273,14 +1352,14 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
     // same order, executed by workgroups that keep W_h on chip and synchronise among themselves.
     const int32_t n_live = s.level_off[1];  // sequences with at least one step
     {
-      const SeqPlan plan = (H == 128 || H == 256) && n_live <= kLstmSlots * kLstmMaxBlocks
+      const SeqPlan plan = H == 128 && n_live <= kLstmSlots * kLstmMaxBlocks
                                ? SeqPlan() : plan_recurrence(ctx, EPI_LSTM_STEP, H, R, n_live, s.n_levels, 1, stream);
-      const size_t n_off = (size_t)s.n_levels * plan.groups + 1;
-      if (plan.groups > 0 && indices_fit(ctx, 2 * (size_t)R + n_off, stream)) {
-        TRY(reserve_indices(ctx, 2 * (size_t)R + n_off, stream));
+      if (plan.groups > 0) {
+        TRY(reserve_indices(ctx, plan.n_idx, stream));
         int32_t* st = ctx->h_stage;
-        stage_seq_groups(n_seq, len, s.n_levels, plan.groups, 1, st, st + R, st + 2 * (size_t)R);
-        TRY(upload_indices(ctx, 2 * (size_t)R + n_off, stream));
+        const size_t at_place = 2 * (size_t)R + plan.n_off;
+        stage_seq_groups(n_seq, len, s.n_levels, plan.groups, 1, st, st + R, st + 2 * (size_t)R, st + at_place);
+        TRY(upload_indices(ctx, plan.n_idx, stream));
         LaunchTimer timer{ctx, stream};
         TRY(input_transform(timer));
         StationaryArgs sa{};
@@ -1290,8 +1369,8 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
         a.h = d_h; a.c = d_c; a.cprev_src = d_c;
         a.zadd = ctx->d_scratch;
         a.W = d_Wh; a.ldw = H;
-        a.first = d_h;  // (nothing of it is read: zero states before the first step)
         sa.off = ctx->d_idx + 2 * (size_t)R;
+        sa.place = ctx->d_idx + at_place;
         return run_recurrence(ctx, EPI_LSTM_STEP, sa, plan, s.n_levels, s.level_off.data(), 1, R, timer);
       }
     }
@@ -1434,17 +1513,18 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
     // same batches, executed by workgroups that keep W_h on chip and synchronise among themselves.
     const int32_t n_live = s.fwd_off[1];  // sequences with at least one token
     const int32_t blocks_per_dir = (n_live + kRnnSlots - 1) / kRnnSlots;
-    const bool persistent = may_wait(ctx, stream) && T >= 2 && (double)R * H * sizeof(float) < 4294967296.0 &&
+    const bool may_persist = may_wait(ctx, stream) && T >= 2 && (double)R * H * sizeof(float) < 4294967296.0 &&
                             rnn_persistent_eligible(H, 2 * blocks_per_dir, nullptr);
     const size_t n_slots = (size_t)blocks_per_dir * kRnnSlots;
-    SeqPlan plan = persistent ? SeqPlan() : plan_recurrence(ctx, EPI_RNN_STEP, H, R, n_live, T, 2, stream);
-    const size_t n_off = (size_t)T * plan.groups + 1;
-    if (!indices_fit(ctx, 4 * (size_t)R + n_off, stream)) plan.groups = 0;
+    const bool preferred = H < 512 || 2 * blocks_per_dir * (H / 16) <= ctx->n_cu;  // (figures in plan_recurrence)
+    const SeqPlan plan = may_persist && preferred ? SeqPlan() : plan_recurrence(ctx, EPI_RNN_STEP, H, R, n_live, T, 2, stream);
+    const bool persistent = may_persist && plan.groups == 0;
+    const size_t at_place = 4 * (size_t)R + plan.n_off;
     if (plan.groups > 0) {
-      TRY(reserve_indices(ctx, 4 * (size_t)R + n_off, stream));
+      TRY(reserve_indices(ctx, plan.n_idx, stream));
       int32_t* st = ctx->h_stage;
-      stage_seq_groups(n_seq, len, T, plan.groups, 2, st, st + 2 * (size_t)R, st + 4 * (size_t)R);
-      TRY(upload_indices(ctx, 4 * (size_t)R + n_off, stream));
+      stage_seq_groups(n_seq, len, T, plan.groups, 2, st, st + 2 * (size_t)R, st + 4 * (size_t)R, st + at_place);
+      TRY(upload_indices(ctx, plan.n_idx, stream));
     } else if (persistent) {
       // (at least what a launch per step needs, so that a smaller call with other sizes can be captured afterwards)
       TRY(reserve_indices(ctx, stream_is_capturing(stream) ? 2 * n_slots : std::max(2 * n_slots, 4 * (size_t)R), stream));
@@ -1516,7 +1596,6 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
     if (plan.groups > 0) {
       StationaryArgs sa{};
       sa.two = 1;
-      sa.first_bytes = (uint32_t)(H * sizeof(float));
       for (int dir = 0; dir < 2; ++dir) {
         CellLevelArgs& a = sa.a[dir];
         a.n = 2 * R; a.H = H; a.nseg = 1; a.kseg = H;
@@ -1527,6 +1606,7 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
         a.first = par[dir]->h_init;
       }
       sa.off = ctx->d_idx + 4 * (size_t)R;
+      sa.place = ctx->d_idx + at_place;
       TRY(run_recurrence(ctx, EPI_RNN_STEP, sa, plan, T, s.fwd_off.data(), 2, R, timer));
     } else if (persistent) {
       RnnPersistentArgs pa{};

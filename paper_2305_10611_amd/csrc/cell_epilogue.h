@@ -109,9 +109,13 @@ __device__ __forceinline__ void store_h(float* p, float v) {
   else *p = v;
 }
 
-template <int G, int EPI, int NV, bool kShared = false, class Acc>
+struct NoFurtherStates {
+  __device__ __forceinline__ void operator()(int, float, float) const {}
+};
+// `further` gets a leaf's states (row v, h, c) as well.
+template <int G, int EPI, int NV, bool kShared = false, class Acc, class Further = NoFurtherStates>
 __device__ __forceinline__ void epilogue_apply(const CellLevelArgs& a, const int j, Acc&& acc,
-                                               const EpilogueOperands<G, EPI, NV>& o) {
+                                               const EpilogueOperands<G, EPI, NV>& o, Further&& further = Further()) {
   const int H = a.H;
   const float* bz = o.bz;
   if constexpr (EPI == EPI_STORE_Z) {
@@ -126,8 +130,10 @@ __device__ __forceinline__ void epilogue_apply(const CellLevelArgs& a, const int
     for (int v = 0; v < NV; ++v) {
       if (!o.live[v]) continue;
       const float c = fast_sigmoid(acc(0, v) + bz[0]) * fast_tanh(acc(2, v) + bz[2]);
+      const float h = fast_sigmoid(acc(1, v) + bz[1]) * fast_tanh(c);
       a.c[o.orow[v] * H + j] = c;
-      store_h<kShared>(a.h + o.orow[v] * H + j, fast_sigmoid(acc(1, v) + bz[1]) * fast_tanh(c));
+      store_h<kShared>(a.h + o.orow[v] * H + j, h);
+      further(v, h, c);
     }
   } else if constexpr (EPI == EPI_TREE_INTERNAL) {
 #pragma unroll

@@ -43,7 +43,7 @@ struct CellLevelArgs {
   // Operands of the split contraction (cell_split_kernels.hip); Wsplit null: only the fp32 kernels apply.
   const void* Wsplit = nullptr;       // W's rows split by launch_split_rows, same row order and bytes per row as W
   const float* w_scale = nullptr;     // scale of every row of W
-  const float* first = nullptr;       // recurrences in one launch only: rows that level 0 reads instead of src0's
+  const float* first = nullptr;       // single-gate recurrences in one launch only: the row that step 0 reads instead of src0's
   const float* src_scale = nullptr;   // [n] scale of every node's row of src0 (nseg == 1); null: states, kStateScale
 };
 

@@ -276,8 +276,50 @@ void TreeGrouping::stage(const acrobat_trees& trees, const TreeSchedule& s, int3
   }
 }
 
+void TreeGrouping::places(const TreeSchedule& s, const std::vector<int32_t>& leaf_tokens, int32_t groups, int32_t first,
+                          int32_t* out, int32_t* left, const int32_t* right, const int32_t* off, int32_t* place) {
+  const int32_t n_leaf = s.level_off[1], p_first = s.level_off[first];
+  position_.resize((size_t)s.n_nodes);
+  for (int32_t p = 0; p < n_leaf; ++p) position_[s.level_nodes[p]] = p;
+  for (int32_t p = n_leaf; p < p_first; ++p) {
+    position_[out[p]] = p;
+    place[p] = -1;
+  }
+  int32_t k = 0;  // leaves listed
+  for (int32_t lv = first; lv < s.n_levels; ++lv)
+    for (int32_t g = 0; g < groups; ++g) {
+      const int32_t share = lv * groups + g, p0 = off[share], p1 = off[share + 1];
+      const int32_t at = 32 * share_block(p0, p_first, share);
+      for (int32_t b = p0; b < p1; b += 16) {
+        const int32_t end = std::min(b + 16, p1);
+        for (int32_t side = 0; side < 2; ++side)
+          for (int32_t p = b; p < end; ++p) {  // (children come at earlier levels)
+            const int32_t child = side ? right[p] : left[p], from = position_[child], to = at + 2 * (p - p0) + side;
+            if (from < n_leaf) {
+              out[k] = child;
+              left[k] = leaf_tokens[from];
+              place[k++] = to;
+              position_[child] = -1;
+            } else {
+              place[from] = to;
+            }
+          }
+        for (int32_t p = b; p < end; ++p) {
+          position_[out[p]] = p;
+          place[p] = -1;
+        }
+      }
+    }
+  for (int32_t p = 0; k < n_leaf && p < n_leaf; ++p)
+    if (position_[s.level_nodes[p]] >= 0) {
+      out[k] = s.level_nodes[p];
+      left[k] = leaf_tokens[p];
+      place[k++] = -1;
+    }
+}
+
 void stage_seq_groups(int32_t n_seq, const int32_t* len, int32_t n_steps, int32_t groups, int32_t directions, int32_t* out,
-                      int32_t* prev, int32_t* off) {
+                      int32_t* prev, int32_t* off, int32_t* place) {
   // ranks by descending length (counting sort), dealt out to groups / directions lists
   const int32_t lists = groups / directions;
   std::vector<int32_t> first((size_t)n_steps + 2, 0), row0;
@@ -312,6 +354,11 @@ void stage_seq_groups(int32_t n_seq, const int32_t* len, int32_t n_steps, int32_
       }
     }
   off[(size_t)n_steps * groups] = p;
+  for (int32_t share = 0; place && share < n_steps * groups; ++share) {
+    const int32_t p0 = off[share], n = off[share + 1] - p0, next = share + groups;
+    const int32_t kept = next < n_steps * groups ? off[next + 1] - off[next] : 0;  // (a list loses its shortest at the end)
+    for (int32_t i = 0; i < n; ++i) place[p0 + i] = i < kept ? 16 * share_block(off[next], 0, next) + i : -1;
+  }
 }
 
 int schedule_seqs(int32_t n_seq, const int32_t* len, SeqSchedule& out, std::string& err) {

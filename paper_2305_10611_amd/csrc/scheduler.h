@@ -49,8 +49,16 @@ class TreeGrouping {
   // level lv >= 1 (entries of level 0: its end), off[n_levels * groups] = N.
   void stage(const acrobat_trees& trees, const TreeSchedule& s, int32_t groups, bool in_order, int32_t* out, int32_t* left,
              int32_t* right, int32_t* off);
+  // Places for groups that run levels first .. n_levels - 1 of the staged lists: share (lv, g) of those has blocks of 16 rows
+  // from share_block() on, and the node in row r of block b reads places 2 (16 b + r) (left) and one more (right).  place[p]
+  // of every list position: where its parent reads it, -1 if nobody does.  The leaves are listed here as well, positions
+  // [0, level_off[1]): out = row written, left = token, in the order of their places - a block's left children, then its right
+  // ones, so that neighbours in the list go to neighbouring rows of an operand - and behind them those without a place.
+  void places(const TreeSchedule& s, const std::vector<int32_t>& leaf_tokens, int32_t groups, int32_t first, int32_t* out,
+              int32_t* left, const int32_t* right, const int32_t* off, int32_t* place);
 
  private:
+  std::vector<int32_t> position_;  // of every node: of a leaf in level_nodes (-1 once listed), of others in the lists
   std::vector<int32_t> order_, count_;
   std::vector<uint8_t> group_;  // of every node (at most 256 groups)
 };
@@ -64,13 +72,20 @@ struct SeqSchedule {
 
 int schedule_seqs(int32_t n_seq, const int32_t* len, SeqSchedule& out, std::string& err);
 
+// First block of 16 rows of a share that starts at list position p0: counted from position `base`, share number
+// level * groups + group.  Rounding down, with a block to spare for every share, keeps them apart.
+inline int32_t share_block(int32_t p0, int32_t base, int32_t share) { return (p0 - base) / 16 + share; }
+// Blocks that shares numbered below n_shares of n list positions may take up.
+inline int64_t share_blocks(int64_t n, int64_t n_shares) { return n / 16 + n_shares + 1; }
+
 // Deals sequences out to groups that run their recurrences independently of each other (by descending length, back and
 // forth) and lists every step group by group.  Step t of sequence s writes row seq_off[s] + t and reads the row before it
 // (directions == 2: odd groups list the backward direction, which starts at the last row and reads the row behind).
 // out / prev: directions * (sum len) entries; prev of step 0 is 0 (the initial state's row).
 // off[t * groups + g]: first position of group g's share of step t, off[n_steps * groups] the end.
+// place[p]: 16 block + row of the same sequence's next step (blocks as share_block(off, 0, t * groups + g)), -1 at its last.
 void stage_seq_groups(int32_t n_seq, const int32_t* len, int32_t n_steps, int32_t groups, int32_t directions, int32_t* out,
-                      int32_t* prev, int32_t* off);
+                      int32_t* prev, int32_t* off, int32_t* place = nullptr);
 
 // Bidirectional RNN with an output phase: levels 0 .. max len - 1 hold step k of both directions
 // (codes: forward row, then R + backward row), the last level holds every output operator (2R + row).

@@ -7,6 +7,7 @@ namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 
@@ -72,6 +73,42 @@ __device__ __forceinline__ float largest_of_quarters(const float m) {
 
 __device__ __forceinline__ float largest(const floatx4 v, const float m) {
   return fmaxf(m, fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
+}
+
+// A 32-k step of 16 rows on its way into the layout of a matrix operand.  A matrix instruction wants lane l to hold row
+// l % 16, but a load whose neighbouring lanes are in different rows fetches 37 KB/us per compute unit where one whose lanes
+// read whole cache lines, eight lanes each, fetches 126 (pieces of 64 bytes: 65).  So a step is requested line by line - half
+// h: lane l, row 8 h + l / 8, 16 bytes number l % 8 -, split where it arrives and turned through 2 KB of LDS that belong to
+// the wavefront (the LDS serves a wavefront's instructions in order: no barrier, and the next step may be written as soon
+// as the reads of this one have been issued).  A row in LDS is the 32 hi terms, then the 32 lo terms, in 16-byte units
+// swizzled so that neither side has bank conflicts.
+constexpr int kTurnFloats = 512;
+__device__ __forceinline__ void turn_write(float* const tile, const int lane, const floatx4 (&lines)[2], const float s0,
+                                           const float s1) {
+  const int wr = lane >> 3, p = lane & 7;
+  const int at = 32 * wr + 2 * (p >> 2) + 4 * ((p & 3) ^ (wr >> 1));
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");  // (for the compiler only: no instruction)
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    unsigned hi[2], lo[2];
+    split4_packed(lines[h], h ? s1 : s0, hi, lo);
+    // (row 8 h + l / 8: the swizzle of the second half is that of the first with the halves of a row exchanged)
+    *reinterpret_cast<uintx2*>(tile + 256 * h + (h ? at ^ 16 : at)) = uintx2{hi[0], hi[1]};
+    *reinterpret_cast<uintx2*>(tile + 256 * h + (h ? at : at ^ 16)) = uintx2{lo[0], lo[1]};
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+}
+// lane l: row l % 16, k = 4 (l / 16) + 0 .. 3 and 16 more
+__device__ __forceinline__ void turn_read(const float* const tile, const int lane, half8& hi, half8& lo) {
+  const int li = lane & 15, at = 32 * li + 4 * ((lane >> 4) ^ (li >> 1));
+  hi = *reinterpret_cast<const half8*>(tile + at);
+  lo = *reinterpret_cast<const half8*>(tile + (at ^ 16));
+}
+// largest over the eight lanes that hold one line, in all of them
+__device__ __forceinline__ float largest_of_line(float m) {
+  m = fmaxf(m, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(m), 0xB1, 0xF, 0xF, true)));   // lane ^ 1
+  m = fmaxf(m, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(m), 0x4E, 0xF, 0xF, true)));   // lane ^ 2
+  return fmaxf(m, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(m), 0x141, 0xF, 0xF, true)));  // the other four
 }
 
 }  // namespace

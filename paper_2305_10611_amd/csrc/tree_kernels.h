@@ -15,11 +15,10 @@ constexpr int kStationaryMaxStepK = 512;  // the same for the steps of a recurre
 
 // Rows [list positions] of one or more levels.  a: the batch as for a level launch, with idx0 / idx1 / out_rows indexed
 // by absolute list position (null: the position itself) and, if off is null, n rows; both segments of a TREE_INTERNAL
-// contraction are rows of src0.  LSTM_STEP and RNN_STEP: idx0 names the row of the previous step.
+// contraction are rows of src0.  LSTM_STEP and RNN_STEP (packed_kernels.hip): idx0 names the row of the previous step.
 struct StationaryArgs {
   CellLevelArgs a[2];
   int32_t two;             // != 0: odd groups work with a[1] (the two directions of a bidirectional recurrence)
-  uint32_t first_bytes;    // of a[].first: what level 0 of a recurrence reads instead of src0 (0: zero states)
   uint32_t src_bytes;      // of src0, at most 2^32 - 512
   int32_t n_cb;            // workgroups of a group, H / 16
   int32_t n_groups;
@@ -31,6 +30,13 @@ struct StationaryArgs {
   unsigned* status;
   int32_t max_polls;
   unsigned long long* stamps;  // [levels * n_groups] 100 MHz clock at the end of a group's share of a level, or null
+  // packed_kernels.hip, and the operands that leaves go to: the operands of all blocks, split states and c states, and every list position's place in
+  // them - 16 block + row of the node that reads it, of a tree node 2 (16 block + row) + side; -1: nobody reads it here
+  void* operand; uint32_t operand_bytes;  // at most kPackedMaxBytes
+  float* cells;
+  const int32_t* place;
+  int32_t first_position;  // list position from which blocks are counted
+  int32_t variant;         // which instance, see packed_variant
 };
 // Groups of H / 16 workgroups that are resident on the current device at once (eight XCDs, a group never crosses one);
 // 0 if the contraction does not fit.
@@ -42,5 +48,23 @@ hipError_t launch_stationary(CellEpilogue epi, const StationaryArgs& s, hipStrea
 constexpr int32_t kPartsMaxRows = 64;
 hipError_t launch_tree_level(const StationaryArgs& s, int32_t p_first, int32_t n, const SplitKWorkspace& ws, hipStream_t stream,
                              const LaunchEvents& ev = LaunchEvents());
+
+// The same for the kernel whose operands arrive packed (packed_kernels.hip): levels [level0, level1) of trees, or steps of a
+// recurrence, always with an offset table; bit for bit the results of the gathering kernel.
+constexpr double kPackedMaxBytes = 4294967296.0 - 131072.0;
+// `variant`: instances with more or fewer units a workgroup (0 for trees); packed_variant picks one for a recurrence's batch.
+int packed_groups(CellEpilogue epi, int32_t H, int32_t K, int32_t variant, int32_t n_cu);
+int packed_members(CellEpilogue epi, int32_t H, int32_t variant);  // workgroups of a group (n_cb)
+int packed_variant(CellEpilogue epi, int32_t H, int32_t n_live, int32_t directions, int32_t n_cu);
+hipError_t launch_packed(CellEpilogue epi, const StationaryArgs& s, hipStream_t stream, const LaunchEvents& ev = LaunchEvents());
+
+// States of tree nodes that other kernels have stored go to their places: list positions [0, n).
+struct PackStatesArgs {
+  int32_t n, H;
+  const int32_t* rows; const int32_t* place;
+  const float* h; const float* c;
+  void* operand; float* cells;
+};
+hipError_t launch_pack_states(const PackStatesArgs& p, hipStream_t stream, const LaunchEvents& ev = LaunchEvents());
 
 }  // namespace acrobat

@@ -28,6 +28,7 @@
 #include "tree_kernels.h"
 
 #include "cell_epilogue.h"
+#include "packed_rows.h"
 #include "split_fp16.h"
 
 #include <algorithm>
@@ -45,8 +46,7 @@ constexpr int kListRows = 512;  // list positions of a level whose index lists s
 
 template <int G, int EPI, int NW, int NS, int RB>
 __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const StationaryArgs s) {
-  constexpr bool kTree = EPI == EPI_TREE_INTERNAL;  // two operand rows per node
-  constexpr bool kStates = kTree || EPI == EPI_LSTM_STEP || EPI == EPI_RNN_STEP;
+  constexpr bool kTree = EPI == EPI_TREE_INTERNAL, kStates = kTree;  // two operand rows per node, states
   constexpr int BR = 16 * RB;         // rows of a block
   constexpr int ZW = G * BR * kZRow;  // floats of one wavefront's partial sums: [gate][row][column]
   constexpr int TURNS = NW / 4;       // groups of 256 threads that take turns at finishing a block
@@ -100,9 +100,8 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
   // ---- node rows: a ring of the NS steps of one block.  Steps past the contraction range and rows past the last block
   // are requested past the end of the buffer, which reads zeros: no branch between the matrix instructions.
   const __amdgpu_buffer_rsrc_t rsrc = agent_buffer(a.src0, s.src_bytes);
-  const __amdgpu_buffer_rsrc_t rsrc_first = agent_buffer(a.first, s.first_bytes);  // level 0 of a recurrence
   const int steps0 = a.kseg >> 5;  // steps of the first segment
-  bool first = false;
+  const __amdgpu_buffer_rsrc_t places = agent_buffer(s.operand, s.operand ? s.operand_bytes : 0u);  // leaves only
   floatx4 ring[RB][NS][2];
   unsigned base0[RB], base1[RB];     // byte offset of this lane's part of its row at step 0 (second segment: less kseg)
   auto request = [&](int r, int t, bool more) {
@@ -110,9 +109,8 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
     unsigned at = (kTree && step >= steps0 ? base1[r] : base0[r]) + 128u * step;
     at = more && step < T ? at : 0xffffff00u;
     if constexpr (kStates) {
-      const auto from = first ? rsrc_first : rsrc;
-      ring[r][t][0] = load_agent_f4(from, at);
-      ring[r][t][1] = load_agent_f4(from, at + 64u);
+      ring[r][t][0] = load_agent_f4(rsrc, at);
+      ring[r][t][1] = load_agent_f4(rsrc, at + 64u);
     } else {
       ring[r][t][0] = load_buffer_f4(rsrc, at);
       ring[r][t][1] = load_buffer_f4(rsrc, at + 64u);
@@ -171,7 +169,6 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
     const int* const s_out = l_out[lists];
     const int* const s_r0 = l_r0[lists];
     const int* const s_r1 = l_r1[kTree ? lists : 0];
-    if constexpr (kStates && !kTree) first = lv == 0;
     // What comes next: the rest of this level, the next level, or nothing (a group's levels only get narrower).  Lists and
     // offsets are cold - nobody has read them yet - so they are requested one and two levels ahead, behind the level's own
     // loads, which would otherwise wait for them (loads return in order).
@@ -190,15 +187,8 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
           eo.p0[r] = a.cprev_src[(size_t)s_r0[i] * H + j];
           eo.p1[r] = a.cprev_src[(size_t)s_r1[i] * H + j];
         }
-        if constexpr (EPI == EPI_LSTM_STEP) {
-          eo.p0[r] = first ? 0.0f : a.cprev_src[(size_t)s_r0[i] * H + j];
-#pragma unroll
-          for (int g = 0; g < G; ++g) eo.zx[g][r] = a.zadd[eo.orow[r] * (size_t)(G * H) + g * H + j];
-        }
-        if constexpr (EPI == EPI_RNN_STEP) eo.p0[r] = a.zadd[eo.orow[r] * (size_t)H + j];
       }
     };
-    if (!kTree && turn == 0) fetch_operands(0);  // (a recurrence's addends are cold memory: requested before the wait)
     if (new_level && arrived > 0) {  // the group's previous level is complete once all its workgroups have announced it
       if (tid == 0) s_go = wait_for(counter, (unsigned)s.n_cb * arrived, s.status, s.max_polls) ? 1 : 0;
       __syncthreads();
@@ -219,7 +209,7 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
 #pragma unroll
         for (int t = 0; t < NS; ++t) request(r, t, true);
       set_rows(nb > 1 ? 1 : 0);
-      if (kTree && turn == 0) fetch_operands(0);
+      if (turn == 0) fetch_operands(0);
       if (c0 < c1) request_lists(c0, c1);
       if (last_chunk && lv + 2 < s.level1) share_of(lv + 2, n0, n1);
 
@@ -295,7 +285,6 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
             // What is not finite, or not to be split, is computed in fp32.  (The result takes the place of the first
             // partial sum in LDS, which only this thread reads: kept in registers, it would cost spills in every block.)
             float* const zw = zbuf + (b & 1) * (NW * ZW);
-            const int k_end = first && s.first_bytes == 0 ? 0 : 32 * T;  // (no state before the first step: no product)
 #pragma unroll 1
             for (int e = 0; e < G * RB; ++e) {
               const int g = e / RB, row = 16 * (e % RB) + er;
@@ -308,10 +297,10 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
               const unsigned at1 = kTree ? (unsigned)s_r1[BR * b + row] * (unsigned)a.ld0 * 4u - 4u * a.kseg : at0;
               sum = 0.0f;
 #pragma unroll 1
-              for (int k = 0; k < k_end; k += 4) {
+              for (int k = 0; k < 32 * T; k += 4) {
                 const unsigned at = (k < a.kseg ? at0 : at1) + 4u * k;
                 floatx4 x;
-                if constexpr (kStates) x = load_agent_f4(first ? rsrc_first : rsrc, at);
+                if constexpr (kStates) x = load_agent_f4(rsrc, at);
                 else x = load_buffer_f4(rsrc, at);
                 const floatx4 wk = *reinterpret_cast<const floatx4*>(wr + k);
 #pragma unroll
@@ -323,7 +312,10 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_stationary_kernel(const Stati
             }
             sum_up();
           }
-          epilogue_apply<G, EPI, RB, kStates>(a, j, [&](int g, int r) { return zs[g][r]; }, eo);
+          epilogue_apply<G, EPI, RB, kStates>(a, j, [&](int g, int r) { return zs[g][r]; }, eo, [&](int r, float h, float c) {
+            if (EPI == EPI_TREE_LEAF && s.operand)
+              store_tree_place(places, s.cells, H, s.place[p0 + BR * b + 16 * r + er], cb, eu, lane, h, c);
+          });
         }
       }
     }
@@ -499,7 +491,7 @@ __global__ __launch_bounds__(64) void cell_parts_kernel(const StationaryArgs s, 
 template <int G, int EPI, int NW, int NS>
 struct Stationary {
   // 16-row blocks multiplied between two barriers: the states of many gates leave no registers for a second one
-  static constexpr int RB = EPI == EPI_TREE_INTERNAL || EPI == EPI_LSTM_STEP ? 1 : 2;
+  static constexpr int RB = EPI == EPI_TREE_INTERNAL ? 1 : 2;
   static constexpr size_t kLdsBytes = (size_t)2 * NW * G * 16 * RB * kZRow * sizeof(float);
   static const void* kernel() { return reinterpret_cast<const void*>(&cell_stationary_kernel<G, EPI, NW, NS, RB>); }
   // More than 64 KB of dynamic LDS has to be asked for once per device (one bit per device id; two threads that both
@@ -537,35 +529,24 @@ struct Stationary {
 };
 
 // Calls f with the Stationary of the smallest instance that holds K columns: four wavefronts (two workgroups per
-// compute unit) up to K = 512, eight up to 1 024.  Recurrences have no use for the latter: K = H, and a group of more than
-// 32 workgroups of eight wavefronts does not fit the 32 compute units of an XCD (stationary_groups says 0 above H = 512).
+// compute unit) up to K = 512, eight up to 1 024.
 template <int G, int EPI, class F>
 auto dispatch_steps(int32_t K, F&& f) {
   if (K <= 128) return f(Stationary<G, EPI, 4, 1>());
   if (K <= 256) return f(Stationary<G, EPI, 4, 2>());
-  if constexpr (EPI == EPI_TREE_LEAF || EPI == EPI_TREE_INTERNAL) {
-    if (K > 768) return f(Stationary<G, EPI, 8, 4>());
-    if (K > 512) return f(Stationary<G, EPI, 8, 3>());
-  }
+  if (K > 768) return f(Stationary<G, EPI, 8, 4>());
+  if (K > 512) return f(Stationary<G, EPI, 8, 3>());
   return f(Stationary<G, EPI, 4, 4>());
 }
 template <class F>
 auto dispatch(CellEpilogue epi, int32_t K, F&& f) {
-  switch (epi) {
-    case EPI_TREE_LEAF: return dispatch_steps<3, EPI_TREE_LEAF>(K, f);
-    case EPI_LSTM_STEP: return dispatch_steps<4, EPI_LSTM_STEP>(K, f);
-    case EPI_RNN_STEP: return dispatch_steps<1, EPI_RNN_STEP>(K, f);
-    default: return dispatch_steps<5, EPI_TREE_INTERNAL>(K, f);
-  }
+  return epi == EPI_TREE_LEAF ? dispatch_steps<3, EPI_TREE_LEAF>(K, f) : dispatch_steps<5, EPI_TREE_INTERNAL>(K, f);
 }
 
 }  // namespace
 
 int stationary_groups(CellEpilogue epi, int32_t H, int32_t K, int32_t n_cu) {
-  const bool recurrence = epi == EPI_LSTM_STEP || epi == EPI_RNN_STEP;
-  if ((epi != EPI_TREE_LEAF && epi != EPI_TREE_INTERNAL && !recurrence) || K <= 0 || K > kStationaryMaxK || H <= 0 || H % 16 ||
-      (recurrence && K > kStationaryMaxStepK))
-    return 0;
+  if ((epi != EPI_TREE_LEAF && epi != EPI_TREE_INTERNAL) || K <= 0 || K > kStationaryMaxK || H <= 0 || H % 16) return 0;
   const int per_xcd = dispatch(epi, K, [](auto k) { return decltype(k)::per_cu(); }) * (n_cu / 8);
   return 8 * std::min(per_xcd / (H / 16), kTreeMaxGroups / 8);
 }
