@@ -16,6 +16,7 @@
 
 #include "acrobat.h"
 #include "cell_kernels.h"
+#include "dense_kernels.h"
 #include "dfg_runtime.h"
 #include "persistent_kernels.h"
 #include "scheduler.h"
@@ -646,6 +647,7 @@ constexpr int32_t kStationaryMaxPolls = 1 << 24;
 // trees are dealt out to for the internal levels from level `first` on; 0: those levels run on the level kernels.
 struct TreePlan {
   int32_t leaf = 0, groups = 0, first = 1;
+  bool dense_leaf = false;  // level 0 on the packed product
   bool grouped = false;   // by trees, with a table of the groups' shares
   bool in_order = false;  // groups of consecutive trees
 };
@@ -655,13 +657,15 @@ TreePlan plan_tree(const acrobat_ctx* ctx, const TreeSchedule& s, int32_t H, int
   const int32_t N = s.n_nodes;
   constexpr double kMaxBytes = 4294967296.0 - 512.0;  // rows are read through a buffer resource
   if (!ctx->persistent || ctx->splitk.force_bm) return p;
-  // A leaf level of four or more rounds of 64-node tiles goes to the split tiles: 8 808 leaves at H = 512 take 76 us
-  // there (10 of them for splitting the weights) and 100 us on the stationary kernel, whose workgroups each convert
-  // every row for 48 columns; 1 996 leaves at H = 256 take 17.5 and 17 us.
+  // A wide leaf level goes to the packed product, or where that has no room to the split tiles from four rounds of them on;
+  // others stay on the stationary kernel, whose workgroups each convert every row for 48 columns.
   const int32_t n_leaf = s.level_off[1];
+  p.dense_leaf = dense_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ctx->splitk) &&
+                 (!noalloc || dense_scratch_bytes(n_leaf, D) <= kStaticScratchBytes / 8);
   const bool tiles = split_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ctx->splitk) && (long)((n_leaf + 63) / 64) * (H / 32) >= 1024 &&
                      (!noalloc || ((size_t)5 * H * D + 10 * (size_t)H + n_leaf) * sizeof(float) < kStaticScratchBytes / 2);
-  if (!tiles && (double)std::max(V, N) * D * sizeof(float) < kMaxBytes) p.leaf = stationary_groups(EPI_TREE_LEAF, H, D, ctx->n_cu);
+  if (!p.dense_leaf && !tiles && (double)std::max(V, N) * D * sizeof(float) < kMaxBytes)
+    p.leaf = stationary_groups(EPI_TREE_LEAF, H, D, ctx->n_cu);
   const int32_t n_internal = N - n_leaf;
   if (n_internal == 0 || (double)N * H * sizeof(float) >= kMaxBytes) return p;
   p.groups = std::min(stationary_groups(EPI_TREE_INTERNAL, H, 2 * H, ctx->n_cu), packed_groups(EPI_TREE_INTERNAL, H, 2 * H, 0, ctx->n_cu));
@@ -819,10 +823,15 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     // same results.
     const bool one_launch = plan.groups > 0 && !unfused && !stream_is_capturing(stream) && may_wait(ctx, stream);
     // One launch of several levels takes its operands packed, given the room: blocks of 16 nodes, 8 H bytes of split states
-    // and as much of c states for each.
-    // (The leaf kernels on tiles do not know about places: for 36 000 leaves at H = 512 a launch that takes their states there
-    // costs 95 us, which is all that the levels save.)
-    const int64_t blocks = one_launch && plan.leaf && n_off > 0 && s.n_levels - plan.first > 1
+    // and as much of c states for each.  (A leaf level on other tiles knows nothing of places: for 36 000 leaves at H = 512 a
+    // launch that takes their states there costs 95 us, which is all that the levels save.)
+    // Finding the places costs the host 1 to 2 ns a node.  Calls that wait for the host anyway do without: it needs about 26 us
+    // and, places included, 5.5 ns a node, the GPU without them 20 us, 2.5 a level and its fp16 products at 0.5 PFLOP/s (1 000
+    // trees of 2 or 3 leaves, H = 64 40 us without and 47 with places, 3 000, H = 256 99 and 106, but H = 512 197 and 172; 64
+    // trees of 5 to 45 leaves, H = 64 60 and 56, H = 256 86 and 76).
+    const double gpu_us = 20.0 + 2.5 * (s.n_levels - 1) + 3.0 * (20.0 * (N - n_leaf) * H + 6.0 * n_leaf * D) * H / 0.5e9;
+    const bool gpu_bound = gpu_us >= 26.0 + 0.0055 * N;
+    const int64_t blocks = one_launch && gpu_bound && (plan.leaf || plan.dense_leaf) && n_off > 0 && s.n_levels - plan.first > 1
                                ? share_blocks((int64_t)N - s.level_off[plan.first], (int64_t)s.n_levels * plan.groups) : 0;
     const size_t operand_bytes = (size_t)blocks * 128 * H;
     bool packed = blocks > 0 && (double)blocks * 128 * H <= kPackedMaxBytes &&
@@ -906,13 +915,14 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     LaunchTimer timer{ctx, stream, !noalloc};
     // Wide levels run on the split contraction: the weights they use are split first, and the leaves' embedding rows
     // get their scales, in one launch.
-    const bool split_leaf = !plan.leaf && split_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ws);
+    const bool split_leaf = !plan.leaf && !plan.dense_leaf && split_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ws);
     const bool split_internal = (plan.groups == 0 || plan.first > 1) && n_wide > 0 && split_level_wins(EPI_TREE_INTERNAL, n_wide, H, 2 * H, ws);
     struct { unsigned char* w; float* scale; } split_w[2] = {};
     float* leaf_scale = nullptr;
     SplitRowsArgs split_rows{};
-    if (split_leaf || split_internal) {
-      const size_t leaf_bytes = split_leaf ? (size_t)5 * H * D * sizeof(float) : 0;
+    unsigned char* dense_at = nullptr;  // the leaves' embedding rows as operands, then their inverse scales
+    if (split_leaf || split_internal || plan.dense_leaf) {
+      const size_t leaf_bytes = split_leaf ? (size_t)5 * H * D * sizeof(float) : plan.dense_leaf ? dense_scratch_bytes(n_leaf, D) : 0;
       const size_t int_bytes = split_internal ? (size_t)5 * H * 2 * H * sizeof(float) : 0;
       const size_t scale_bytes = ((size_t)10 * H + n_leaf) * sizeof(float);
       const size_t bytes = (leaf_bytes + int_bytes + scale_bytes + 255) / 256 * 256;
@@ -926,6 +936,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
       if (at) {
         SplitRowsArgs sr{};
         float* scale = reinterpret_cast<float*>(at + leaf_bytes + int_bytes);
+        if (plan.dense_leaf) dense_at = at;
         if (split_leaf) {  // the rows of gates i, o, u only
           split_w[0] = {at, scale};
           leaf_scale = scale + (size_t)10 * H;
@@ -994,6 +1005,16 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
         std::swap(first.start, timer.ev.start);
         HIP_TRY(ctx, launch_split_rows(split_rows, stream, first));
       }
+      if (lv == 0 && dense_at) {
+        DenseArgs da{};
+        da.a = a;
+        if (timer.tile()) *timer.tile() = 16;
+        if (timer.ksplit()) *timer.ksplit() = -1;
+        if (packed) da.places = {packed_at, (uint32_t)operand_bytes, reinterpret_cast<float*>(packed_at + operand_bytes), d_idx + at_place};
+        HIP_TRY(ctx, launch_dense_level(EPI_TREE_LEAF, da, dense_at, ws.n_cu, stream, timer.ev));
+        TRY(timer.end());
+        continue;
+      }
       if (lv == 0 && plan.leaf) {
         sa.a[0] = a;
         if (packed) {
@@ -1032,7 +1053,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
             sa.cells = reinterpret_cast<float*>(packed_at + operand_bytes);
             sa.place = d_idx + at_place;
             sa.first_position = off;
-            const int32_t there = plan.leaf ? n_leaf : 0;  // (that kernel has taken the leaves' there)
+            const int32_t there = plan.leaf || dense_at ? n_leaf : 0;  // (those kernels have taken the leaves' there)
             if (off > there) {
               LaunchEvents first;
               std::swap(first.start, timer.ev.start);
@@ -1323,7 +1344,8 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
     TRY(reserve_splitk(ctx, stream));
     TRY(reserve_scratch(ctx, (size_t)R * 4 * (size_t)H, stream));
     const size_t split_bytes = (size_t)4 * H * D * sizeof(float);
-    const bool split = split_level_wins(EPI_STORE_Z, R, H, D, ctx->splitk) &&
+    const bool dense = dense_level_wins(EPI_STORE_Z, R, H, D, ctx->splitk) && reserve_split(ctx, dense_scratch_bytes(R, D), stream);
+    const bool split = !dense && split_level_wins(EPI_STORE_Z, R, H, D, ctx->splitk) &&
                        reserve_split(ctx, split_bytes + ((size_t)4 * H + R) * sizeof(float), stream);
     auto input_transform = [&](LaunchTimer& timer) {  // hoisted: every step of every sequence in one dense batch
       CellLevelArgs a{};
@@ -1332,6 +1354,14 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
       a.W = d_Wx; a.ldw = D; a.bias = d_b;
       a.zout = ctx->d_scratch;
       TRY(timer.begin(ACROBAT_K_LSTM_INPUT, 0, R));
+      if (dense) {
+        if (timer.tile()) *timer.tile() = 16;
+        if (timer.ksplit()) *timer.ksplit() = -1;
+        DenseArgs da{};
+        da.a = a;
+        HIP_TRY(ctx, launch_dense_level(EPI_STORE_Z, da, ctx->d_split, ctx->splitk.n_cu, stream, timer.ev));
+        return timer.end();
+      }
       if (split) {  // (timed with the contraction that follows)
         float* scale = reinterpret_cast<float*>(ctx->d_split + split_bytes);
         a.Wsplit = ctx->d_split;

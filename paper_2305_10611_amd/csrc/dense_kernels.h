@@ -1,0 +1,48 @@
+// Launch interface of the wide products with packed input rows (dense_kernels.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "cell_kernels.h"
+
+namespace acrobat {
+
+// Where the states of tree nodes go besides the arena: the operands of the blocks that read them (packed_kernels.hip).
+struct TreePlaces {
+  void* operand; uint32_t operand_bytes;  // null: nowhere
+  float* cells;
+  const int32_t* place;  // [n] by list position
+};
+
+constexpr int32_t kDenseMaxK = 1024;
+constexpr double kDenseMaxBytes = 4294967296.0 - 131072.0;
+
+// Input rows as matrix operands: blocks of 16 rows, 64 K bytes each, and every row's inverse scale.
+struct PackRowsArgs {
+  int32_t n, K;
+  const float* src; const int32_t* idx;  // row of src by position, null: the position itself
+  void* operand;   // [ceil(n / 16)] blocks
+  float* inverse;  // [16 ceil(n / 16)]
+};
+
+// One level: TREE_LEAF or STORE_Z with one segment of at most kDenseMaxK columns, H a multiple of 32.
+struct DenseArgs {
+  CellLevelArgs a;
+  const void* operand; uint32_t operand_bytes;
+  float* inverse;
+  TreePlaces places;
+  int32_t n_cb, n_groups;  // set by the launcher
+};
+// Whether a level (G gates of H units over K columns) is wide enough for this kernel to win; a forced tile switches it off.
+bool dense_level_wins(CellEpilogue epi, int32_t n, int32_t H, int32_t K, const SplitKWorkspace& ws);
+// Scratch of a level: packed rows, then their inverse scales.
+inline size_t dense_scratch_bytes(int32_t n, int32_t K) {
+  const size_t rows = ((size_t)n + 15) / 16 * 16;
+  return rows * K * sizeof(float) + rows * sizeof(float);
+}
+// Packs the input rows (s.a.src0, gathered by s.a.idx0) into `scratch` and runs the level: two launches.
+hipError_t launch_dense_level(CellEpilogue epi, DenseArgs s, void* scratch, int n_cu, hipStream_t stream,
+                              const LaunchEvents& ev = LaunchEvents());
+
+}  // namespace acrobat

@@ -1,0 +1,92 @@
+"""Wide leaf levels and LSTM input products with packed input rows against the oracle: every instance (columns up to 128, 256,
+384, 512, 768, 1 024), steps that do not divide evenly, rows that do not fill a block, groups that straddle an XCD, inputs that
+are not to be split, the call that allocates nothing.
+
+Tolerance: 1e-6 over the 2-norm, as in test_split_contraction."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import generators as gen
+
+pytestmark = pytest.mark.gpu
+
+NT = oracle.default_threads()
+
+
+def rel(got, want):
+    want = want.astype(np.float64)
+    return float(np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want))
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_2305_10611_amd as A
+    c = A.Context(0)
+    yield c
+    c.close()
+
+
+def takes_it(ctx, run, kind):
+    """The level's launch record says 16-row blocks."""
+    import paper_2305_10611_amd as A
+    ctx.acrobat_set_profiling(True)
+    try:
+        out = run()
+        r = [x for x in ctx.acrobat_last_profile() if x[0] == getattr(A.binding, kind)]
+    finally:
+        ctx.acrobat_set_profiling(False)
+    assert r and r[0][4] == 16 and r[0][5] == -1
+    return out
+
+
+@pytest.mark.parametrize("H,D,n", [(512, 96, 3391), (512, 256, 1270), (320, 352, 1500), (512, 512, 637), (256, 672, 1000),
+                                   (480, 1024, 340), (288, 544, 1073)])
+def test_leaf_levels(ctx, H, D, n):
+    from tests import parity as P
+    w = gen.treelstm_workload(n, 1, 2, H, 50, "uniform", seed=H + D, bias_scale=0.2, D=D)
+    h, c = takes_it(ctx, lambda: P.run_treelstm(ctx, w), "K_TREE_LEAF")
+    oh, oc = oracle.treelstm(w, nthreads=NT)
+    assert rel(h, oh) < 1e-6 and rel(c, oc) < 1e-6
+
+
+@pytest.mark.parametrize("H,D,n", [(256, 128, 1911), (512, 224, 620), (352, 384, 477), (512, 512, 245), (320, 736, 285),
+                                   (256, 992, 263), (1024, 32, 1921)])
+def test_lstm_input_products(ctx, H, D, n):
+    from tests import parity as P
+    w = gen.lstm_workload(n, 2, 2, H, D, seed=H + D, bias_scale=0.2)
+    h, c = takes_it(ctx, lambda: P.run_lstm(ctx, w), "K_LSTM_INPUT")
+    oh, oc = oracle.varlen_lstm(w, nthreads=NT)
+    assert rel(h, oh) < 1e-6 and rel(c, oc) < 1e-6
+
+
+def test_rows_that_are_not_to_be_split(ctx):
+    """A feature of 1e9 with a weight of 1e-9 beside ordinary ones, infinities and NaNs: what fp32 says."""
+    from tests import parity as P
+    w = gen.treelstm_workload(1200, 1, 2, 320, 64, "uniform", seed=5, bias_scale=0.2, D=352)
+    w["emb"][:, 3] *= 1e9
+    w["W_leaf"][:, 3] *= 1e-9
+    h, c = takes_it(ctx, lambda: P.run_treelstm(ctx, w), "K_TREE_LEAF")
+    oh, oc = oracle.treelstm(w, nthreads=NT)
+    assert rel(h, oh) < 1e-6 and rel(c, oc) < 1e-6
+    w["emb"][5, 7], w["emb"][6, 9] = np.inf, np.nan
+    h, c = P.run_treelstm(ctx, w)
+    roots_of = np.repeat(np.arange(1200), np.diff(w["tree_off"]))
+    odd = np.unique(roots_of[np.isin(w["token"], (5, 6)) & (w["left"] < 0)])
+    rest = ~np.isin(roots_of, odd)
+    assert np.isfinite(h[rest]).all()
+    assert rel(h[rest], oh[rest]) < 1e-6
+    assert np.isnan(h[np.flatnonzero((w["token"] == 6) & (w["left"] < 0))]).all()
+
+
+def test_without_allocations(ctx):
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    w = gen.treelstm_workload(1300, 1, 2, 320, 64, "uniform", seed=8, bias_scale=0.2, D=352)
+    h, c = P.run_treelstm(ctx, w)
+    d = {k: P.dev(w[k]) for k in ("emb", "W_leaf", "b_leaf", "U", "b")}
+    h1, c1 = P.nan_filled(*h.shape), P.nan_filled(*c.shape)
+    rc = ctx.acrobat_treelstm_forward_noalloc(w, 320, 352, 64, d["emb"], d["W_leaf"], d["b_leaf"], d["U"], d["b"], h1, c1,
+                                              P.stream_handle())
+    assert rc == A.OK
+    assert np.array_equal(h1.cpu().numpy(), h) and np.array_equal(c1.cpu().numpy(), c)
