@@ -1114,13 +1114,20 @@ SeqPlan plan_recurrence(acrobat_ctx* ctx, CellEpilogue epi, int32_t H, int32_t R
   if (p.groups == 0) return p;
   const int64_t entries = (int64_t)directions * R, blocks = share_blocks(entries, (int64_t)n_steps * p.groups);
   p.n_off = (size_t)n_steps * p.groups + 1;
-  p.n_idx = 3 * (size_t)entries + p.n_off;
+  p.n_idx = (size_t)entries + p.n_off;
   p.operand_bytes = (size_t)blocks * 64 * H;
   // (a captured call that lacks the room does without)
   if ((double)p.operand_bytes > kPackedMaxBytes || !indices_fit(ctx, p.n_idx, stream) ||
       !reserve_packed(ctx, (epi == EPI_LSTM_STEP ? 2 : 1) * p.operand_bytes, stream))
     p.groups = 0;
   return p;
+}
+
+// Room for a plan's lists, at least what a launch per step needs, so that a smaller call with other sizes can be captured
+// afterwards.
+int reserve_recurrence(acrobat_ctx* ctx, const SeqPlan& plan, int32_t directions, int32_t R, hipStream_t stream) {
+  const size_t n_idx = stream_is_capturing(stream) ? plan.n_idx : 2 * (size_t)directions * R + plan.n_off;
+  return reserve_indices(ctx, n_idx, stream);
 }
 
 // The steps of a recurrence, lists and offset table staged and uploaded (sa.off), in one launch or one per step.  step_off[t + 1] - step_off[t]: nodes of step t, per direction.
@@ -1133,6 +1140,7 @@ int run_recurrence(acrobat_ctx* ctx, CellEpilogue epi, StationaryArgs& sa, const
   sa.cells = reinterpret_cast<float*>(ctx->d_packed + plan.operand_bytes);
   sa.n_cb = packed_members(epi, H, plan.variant);
   sa.variant = plan.variant;
+  sa.n_steps = n_steps;
   sa.n_groups = plan.groups;
   sa.counters = ctx->splitk.counters;
   sa.status = ctx->h_status_dev;
@@ -1385,22 +1393,20 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
       const SeqPlan plan = H == 128 && n_live <= kLstmSlots * kLstmMaxBlocks
                                ? SeqPlan() : plan_recurrence(ctx, EPI_LSTM_STEP, H, R, n_live, s.n_levels, 1, stream);
       if (plan.groups > 0) {
-        TRY(reserve_indices(ctx, plan.n_idx, stream));
+        TRY(reserve_recurrence(ctx, plan, 1, R, stream));
         int32_t* st = ctx->h_stage;
-        const size_t at_place = 2 * (size_t)R + plan.n_off;
-        stage_seq_groups(n_seq, len, s.n_levels, plan.groups, 1, st, st + R, st + 2 * (size_t)R, st + at_place);
+        stage_seq_groups(n_seq, len, s.n_levels, plan.groups, 1, st, nullptr, st + R);
         TRY(upload_indices(ctx, plan.n_idx, stream));
         LaunchTimer timer{ctx, stream};
         TRY(input_transform(timer));
         StationaryArgs sa{};
         CellLevelArgs& a = sa.a[0];
         a.n = R; a.H = H; a.nseg = 1; a.kseg = H;
-        a.src0 = d_h; a.ld0 = H; a.idx0 = ctx->d_idx + R; a.out_rows = ctx->d_idx;
+        a.src0 = d_h; a.ld0 = H; a.out_rows = ctx->d_idx;
         a.h = d_h; a.c = d_c; a.cprev_src = d_c;
         a.zadd = ctx->d_scratch;
         a.W = d_Wh; a.ldw = H;
-        sa.off = ctx->d_idx + 2 * (size_t)R;
-        sa.place = ctx->d_idx + at_place;
+        sa.off = ctx->d_idx + R;
         return run_recurrence(ctx, EPI_LSTM_STEP, sa, plan, s.n_levels, s.level_off.data(), 1, R, timer);
       }
     }
@@ -1549,11 +1555,10 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
     const bool preferred = H < 512 || 2 * blocks_per_dir * (H / 16) <= ctx->n_cu;  // (figures in plan_recurrence)
     const SeqPlan plan = may_persist && preferred ? SeqPlan() : plan_recurrence(ctx, EPI_RNN_STEP, H, R, n_live, T, 2, stream);
     const bool persistent = may_persist && plan.groups == 0;
-    const size_t at_place = 4 * (size_t)R + plan.n_off;
     if (plan.groups > 0) {
-      TRY(reserve_indices(ctx, plan.n_idx, stream));
+      TRY(reserve_recurrence(ctx, plan, 2, R, stream));
       int32_t* st = ctx->h_stage;
-      stage_seq_groups(n_seq, len, T, plan.groups, 2, st, st + 2 * (size_t)R, st + 4 * (size_t)R, st + at_place);
+      stage_seq_groups(n_seq, len, T, plan.groups, 2, st, nullptr, st + 2 * (size_t)R);
       TRY(upload_indices(ctx, plan.n_idx, stream));
     } else if (persistent) {
       // (at least what a launch per step needs, so that a smaller call with other sizes can be captured afterwards)
@@ -1629,14 +1634,13 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
       for (int dir = 0; dir < 2; ++dir) {
         CellLevelArgs& a = sa.a[dir];
         a.n = 2 * R; a.H = H; a.nseg = 1; a.kseg = H;
-        a.src0 = hdir[dir]; a.ld0 = H; a.idx0 = ctx->d_idx + 2 * (size_t)R; a.out_rows = ctx->d_idx;
+        a.src0 = hdir[dir]; a.ld0 = H; a.out_rows = ctx->d_idx;
         a.W = par[dir]->Wh; a.ldw = H;
         a.zadd = xp[dir];
         a.h = hdir[dir];
         a.first = par[dir]->h_init;
       }
-      sa.off = ctx->d_idx + 4 * (size_t)R;
-      sa.place = ctx->d_idx + at_place;
+      sa.off = ctx->d_idx + 2 * (size_t)R;
       TRY(run_recurrence(ctx, EPI_RNN_STEP, sa, plan, T, s.fwd_off.data(), 2, R, timer));
     } else if (persistent) {
       RnnPersistentArgs pa{};

@@ -80,7 +80,7 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
   // workgroups of the group bring the first 128 rows of every level's share into their L2.
   int touched = 0;
   if (s.level1 - s.level0 > 1) {
-    const int* const list = cb & 1 ? s.place : a.out_rows;
+    const int* const list = kTree && (cb & 1) ? s.place : a.out_rows;
     for (int l = s.level0 + (tid >> 2); l < s.level1; l += 16 * NW) {
       const int p = s.off[l * s.n_groups + group] + 32 * (tid & 3);
       if (p < s.off[l * s.n_groups + group + 1]) touched |= list[p];
@@ -166,15 +166,15 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
     p0 = offsets[lv * s.n_groups + group];
     p1 = offsets[lv * s.n_groups + group + 1];
   };
-  // rows written and places of this thread's rows; for a recurrence, whose addends they name, a chunk ahead
-  int out[EPT], to[EPT], next_out[EPT], next_place[EPT];
-  auto request_lists = [&](int (&o)[EPT], int (&t)[EPT], int p, int end) {  // tail rows repeat the last node; never stored
+  // rows written, and of tree nodes the places, of this thread's rows; for a recurrence, whose addends they name, a chunk ahead
+  int out[EPT], to[EPT], next_out[EPT];
+  auto request_lists = [&](int (&o)[EPT], int p, int end) {  // tail rows repeat the last node; never stored
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
       int i = p + 16 * (rb0 + e * (NW / 4)) + er;
       i = i < end ? i : end - 1;
       o[e] = at_byte(out_rows, 4u * (unsigned)i);
-      t[e] = at_byte(place, 4u * (unsigned)i);
+      if constexpr (kTree) to[e] = at_byte(place, 4u * (unsigned)i);
     }
   };
 
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
   unsigned arrived = 0;  // levels this group has announced
   share_of(lv, p0, p1);
   if (p0 >= p1) return;  // (nothing in this level: nothing in a later one)
-  if constexpr (!kTree) request_lists(next_out, next_place, p0, p1);
+  if constexpr (!kTree) request_lists(next_out, p0, p1);
   __syncthreads();
 
   // One level; false when there is nothing more to do.  kFirst: step 0 of a recurrence, whose states before it are zero or
@@ -191,15 +191,15 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
     constexpr bool kFirst = decltype(first_level)::value;
     const int n = p1 - p0, nb = (n + 15) >> 4;
     int c0 = 0, c1 = 0;  // the next level's share
-    if (lv + 1 < s.level1) share_of(lv + 1, c0, c1);
-    const unsigned block0 = (unsigned)((p0 - s.first_position) >> 4) + (unsigned)(lv * s.n_groups + group);
+    if (lv + 1 < (kTree ? s.level1 : s.n_steps)) share_of(lv + 1, c0, c1);
+    const auto first_block = [&](int p, int l) { return (unsigned)((p - s.first_position) >> 4) + (unsigned)(l * s.n_groups + group); };
+    const unsigned block0 = first_block(p0, lv);
+    // a share's sequences are a prefix of the step before's: row i of a block is read as row i of the same block of the next
+    const unsigned reader0 = first_block(c0, lv + 1);
     float p[EPT][2], zx[EPT][kTree ? 1 : G];
     auto take_lists = [&]() {
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        out[e] = next_out[e];
-        to[e] = next_place[e];
-      }
+      for (int e = 0; e < EPT; ++e) out[e] = next_out[e];
     };
     auto fetch_addends = [&]() {  // cold memory: requested before the wait
 #pragma unroll
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
     auto chunk = [&](const int b, auto n_blocks) {
       constexpr int blocks = decltype(n_blocks)::value;
       const bool more = b + blocks < nb;
-      if constexpr (kTree) request_lists(out, to, p0 + 16 * b, p1);  // (behind the loads of this chunk: they return in order)
+      if constexpr (kTree) request_lists(out, p0 + 16 * b, p1);  // (behind the loads of this chunk: they return in order)
       float* const zc = zbuf + (S::ZB == 2 ? (b / RB & 1) * (RB * NW * ZQ) : 0);
 #pragma unroll
       for (int r = 0; r < blocks; ++r) {
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
       }
       // what comes next: behind this chunk's own loads, which would otherwise wait (loads return in order)
       if constexpr (!kTree)
-        request_lists(next_out, next_place, more ? p0 + 16 * (b + blocks) : c0 < c1 ? c0 : p0, more ? p1 : c0 < c1 ? c1 : p1);
+        request_lists(next_out, more ? p0 + 16 * (b + blocks) : c0 < c1 ? c0 : p0, more ? p1 : c0 < c1 ? c1 : p1);
       // (one of two buffers has been read two chunks later: its readers have passed the barrier in between)
       __syncthreads();
       float zs[EPT][G];
@@ -339,10 +339,15 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
         if (__builtin_expect(live && finite != 0.0f, 0)) {
           // What is not finite, or not to be split, is computed in fp32 from the arena's rows.  (Through LDS, this thread's
           // own words: indexed registers would cost spills in every block.)
-          const int pos = p0 + 16 * (b + r) + er;
           const __amdgpu_buffer_rsrc_t rsrc = agent_buffer(a.src0, s.src_bytes);
-          const unsigned at0 = kFirst ? 0u : (unsigned)a.idx0[pos] * (unsigned)a.ld0 * 4u;
-          const unsigned at1 = kTree ? (unsigned)a.idx1[pos] * (unsigned)a.ld0 * 4u - 4u * a.kseg : at0;
+          unsigned at0 = 0u, at1 = 0u;
+          if constexpr (kTree) {
+            const int pos = p0 + 16 * (b + r) + er;
+            at0 = (unsigned)a.idx0[pos] * (unsigned)a.ld0 * 4u;
+            at1 = (unsigned)a.idx1[pos] * (unsigned)a.ld0 * 4u - 4u * a.kseg;
+          } else if constexpr (!kFirst) {
+            at0 = at1 = (unsigned)(s.two && (group & 1) ? out[e] + 1 : out[e] - 1) * (unsigned)a.ld0 * 4u;
+          }
           const int k_end = kFirst && EPI == EPI_LSTM_STEP ? 0 : K;  // (no state before the first step: no product)
 #pragma unroll
           for (int g = 0; g < G; ++g) zr[z_at(g)] = zs[e][g];
@@ -372,14 +377,15 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
       for (int e = 0; e < EPT; ++e) {
         const int r = rb0 + e * (NW / 4);
         if (r >= blocks || 16 * (b + r) + er >= n) continue;
-        // place: row + 16 block, for a tree node twice that and the side
-        const unsigned row = (unsigned)(kTree ? to[e] >> 1 : to[e]) & 15u, blk = (unsigned)(kTree ? to[e] >> 5 : to[e] >> 4);
-        const unsigned side_block = kTree ? 2u * blk + ((unsigned)to[e] & 1u) : blk;
-        const unsigned place_at = to[e] < 0 ? kNowhere : side_block * (64u * H) + 16u * row;
+        // a tree node's place: twice row + 16 block, and the side
+        const bool read = kTree ? to[e] >= 0 : 16 * (b + r) + er < c1 - c0;
+        const unsigned row = kTree ? (unsigned)to[e] >> 1 & 15u : (unsigned)er;
+        const unsigned side_block = kTree ? 2u * (unsigned)(to[e] >> 5) + ((unsigned)to[e] & 1u) : reader0 + b + r;
+        const unsigned place_at = side_block * (64u * H) + 16u * row;
         const unsigned row_at = 4u * ((unsigned)out[e] * (unsigned)H + j);
         const auto store_state = [&](float h, int b16, unsigned at) {
           const unsigned word = quad_word(split_state(h), lane);  // (a row's 16 lanes are live together)
-          __builtin_amdgcn_raw_buffer_store_b32(word, operand, (int)(to[e] < 0 ? kNowhere : place_at + in_place(b16)), 0, kAuxAgentScope);
+          __builtin_amdgcn_raw_buffer_store_b32(word, operand, (int)(read ? place_at + in_place(b16) : kNowhere), 0, kAuxAgentScope);
           __hip_atomic_store(&at_byte(h_rows, at), h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         };
         const auto bias = [&](int g) { return s_bias[my_ch][g][eu]; };
@@ -399,7 +405,7 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
           }
           store_state(h, jb, row_at);
           at_byte(c_rows, row_at) = c;
-          if (to[e] >= 0) at_byte(cells, side_block * (64u * H) + 1024u * jb + 64u * row + 4u * eu) = c;
+          if (read) at_byte(cells, side_block * (64u * H) + 1024u * jb + 64u * row + 4u * eu) = c;
         }
       }
     };
@@ -423,7 +429,7 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
       if (tid == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       ++arrived;
     }
-    if (c0 >= c1) return false;
+    if (c0 >= c1 || !announce) return false;
     p0 = c0;
     p1 = c1;
     ++lv;

@@ -319,7 +319,7 @@ void TreeGrouping::places(const TreeSchedule& s, const std::vector<int32_t>& lea
 }
 
 void stage_seq_groups(int32_t n_seq, const int32_t* len, int32_t n_steps, int32_t groups, int32_t directions, int32_t* out,
-                      int32_t* prev, int32_t* off, int32_t* place) {
+                      int32_t* prev, int32_t* off) {
   // ranks by descending length (counting sort), dealt out to groups / directions lists
   const int32_t lists = groups / directions;
   std::vector<int32_t> first((size_t)n_steps + 2, 0), row0;
@@ -349,16 +349,11 @@ void stage_seq_groups(int32_t n_seq, const int32_t* len, int32_t n_steps, int32_
         while (!m.empty() && len[m.back()] <= t) m.pop_back();
       for (const int32_t q : m) {
         out[p] = backward ? row0[q] + len[q] - 1 - t : row0[q] + t;
-        prev[p] = t == 0 ? 0 : backward ? out[p] + 1 : out[p] - 1;
+        if (prev) prev[p] = t == 0 ? 0 : backward ? out[p] + 1 : out[p] - 1;
         ++p;
       }
     }
   off[(size_t)n_steps * groups] = p;
-  for (int32_t share = 0; place && share < n_steps * groups; ++share) {
-    const int32_t p0 = off[share], n = off[share + 1] - p0, next = share + groups;
-    const int32_t kept = next < n_steps * groups ? off[next + 1] - off[next] : 0;  // (a list loses its shortest at the end)
-    for (int32_t i = 0; i < n; ++i) place[p0 + i] = i < kept ? 16 * share_block(off[next], 0, next) + i : -1;
-  }
 }
 
 int schedule_seqs(int32_t n_seq, const int32_t* len, SeqSchedule& out, std::string& err) {

@@ -81,11 +81,11 @@ inline int64_t share_blocks(int64_t n, int64_t n_shares) { return n / 16 + n_sha
 // Deals sequences out to groups that run their recurrences independently of each other (by descending length, back and
 // forth) and lists every step group by group.  Step t of sequence s writes row seq_off[s] + t and reads the row before it
 // (directions == 2: odd groups list the backward direction, which starts at the last row and reads the row behind).
-// out / prev: directions * (sum len) entries; prev of step 0 is 0 (the initial state's row).
+// out / prev (or null): directions * (sum len) entries; prev of step 0 is 0 (the initial state's row).
 // off[t * groups + g]: first position of group g's share of step t, off[n_steps * groups] the end.
-// place[p]: 16 block + row of the same sequence's next step (blocks as share_block(off, 0, t * groups + g)), -1 at its last.
+// A group's share of a step lists the first sequences of its share of the step before, in the same order.
 void stage_seq_groups(int32_t n_seq, const int32_t* len, int32_t n_steps, int32_t groups, int32_t directions, int32_t* out,
-                      int32_t* prev, int32_t* off, int32_t* place = nullptr);
+                      int32_t* prev, int32_t* off);
 
 // Bidirectional RNN with an output phase: levels 0 .. max len - 1 hold step k of both directions
 // (codes: forward row, then R + backward row), the last level holds every output operator (2R + row).

@@ -15,7 +15,8 @@ constexpr int kStationaryMaxStepK = 512;  // the same for the steps of a recurre
 
 // Rows [list positions] of one or more levels.  a: the batch as for a level launch, with idx0 / idx1 / out_rows indexed
 // by absolute list position (null: the position itself) and, if off is null, n rows; both segments of a TREE_INTERNAL
-// contraction are rows of src0.  LSTM_STEP and RNN_STEP (packed_kernels.hip): idx0 names the row of the previous step.
+// contraction are rows of src0.  LSTM_STEP and RNN_STEP (packed_kernels.hip) read the row of src0 before the one they write,
+// the odd groups of two directions the one behind it.
 struct StationaryArgs {
   CellLevelArgs a[2];
   int32_t two;             // != 0: odd groups work with a[1] (the two directions of a bidirectional recurrence)
@@ -31,10 +32,11 @@ struct StationaryArgs {
   int32_t max_polls;
   unsigned long long* stamps;  // [levels * n_groups] 100 MHz clock at the end of a group's share of a level, or null
   // packed_kernels.hip, and the operands that leaves go to: the operands of all blocks, split states and c states, and every list position's place in
-  // them - 16 block + row of the node that reads it, of a tree node 2 (16 block + row) + side; -1: nobody reads it here
+  // them - 16 block + row of the node that reads it, 2 (16 block + row) + side; -1: nobody reads it here
   void* operand; uint32_t operand_bytes;  // at most kPackedMaxBytes
   float* cells;
-  const int32_t* place;
+  const int32_t* place;    // trees only
+  int32_t n_steps;         // of a recurrence, also those behind level1
   int32_t first_position;  // list position from which blocks are counted
   int32_t variant;         // which instance, see packed_variant
 };

@@ -94,8 +94,11 @@ void sequences_round() {
   for (int32_t& v : len) { v = rnd_in(0, 12); R += v; T = T > v ? T : v; }
   if (T < 1) return;
   const int groups = directions * rnd_in(1, 6), E = directions * R;
-  std::vector<int32_t> out(E), prev(E), table((size_t)T * groups + 1), place(E, -7);
-  stage_seq_groups(n_seq, len.data(), T, groups, directions, out.data(), prev.data(), table.data(), place.data());
+  std::vector<int32_t> out(E), prev(E), table((size_t)T * groups + 1);
+  stage_seq_groups(n_seq, len.data(), T, groups, directions, out.data(), prev.data(), table.data());
+  const std::vector<int32_t> listed = out, offsets = table;
+  stage_seq_groups(n_seq, len.data(), T, groups, directions, out.data(), nullptr, table.data());
+  CHECK(listed == out && offsets == table);
   const int64_t blocks = share_blocks(E, (int64_t)T * groups);
   std::set<int32_t> owned;
   for (int t = 0; t < T; ++t)
@@ -103,17 +106,10 @@ void sequences_round() {
       const int share = t * groups + g, p0 = table[share], n = table[share + 1] - p0;
       const int block = share_block(p0, 0, share);
       for (int x = 0; x < (n + 15) / 16; ++x) CHECK(block + x < blocks && owned.insert(block + x).second);
-      std::map<int32_t, int32_t> from;  // row written at the step before -> place
-      if (t > 0)
-        for (int p = table[share - groups]; p < table[share - groups + 1]; ++p) from[out[p]] = place[p];
-      for (int p = p0; p < p0 + n; ++p) CHECK(t == 0 || from.at(prev[p]) == 16 * block + (p - p0));
-      int ended = 0;
-      if (t > 0) {
-        for (int p = table[share - groups]; p < table[share - groups + 1]; ++p) ended += place[p] < 0;
-        CHECK(ended == table[share - groups + 1] - table[share - groups] - n);
+      for (int i = 0; t > 0 && i < n; ++i) {  // row i of the step before left its state for row i, and its row is found from it
+        CHECK(i < table[share - groups + 1] - table[share - groups] && out[table[share - groups] + i] == prev[p0 + i]);
+        CHECK(prev[p0 + i] == out[p0 + i] + (directions == 2 && (g & 1) ? 1 : -1));
       }
-      if (t + 1 == T)
-        for (int p = p0; p < p0 + n; ++p) CHECK(place[p] == -1);
     }
 }
 }  // namespace
