@@ -1624,8 +1624,17 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
         a[dir].zout = xp[dir];
       }
       TRY(timer.begin(ACROBAT_K_RNN_INPUT, 0, 2 * R));
-      HIP_TRY(ctx, launch_cell_level_pair(EPI_STORE_Z1, a[0], a[1], stream, ctx->splitk, timer.tile(), timer.ksplit(),
-                                          timer.ev));
+      if (dense_level_wins(EPI_STORE_Z1, R, H, D, ctx->splitk) && reserve_split(ctx, dense_scratch_bytes(R, D), stream)) {
+        DenseArgs da{};
+        da.a = a[0];
+        da.b = a[1];
+        da.two = 1;
+        if (timer.tile()) *timer.tile() = 16;
+        if (timer.ksplit()) *timer.ksplit() = -1;
+        HIP_TRY(ctx, launch_dense_level(EPI_STORE_Z1, da, ctx->d_split, ctx->splitk.n_cu, stream, timer.ev));
+      } else {
+        HIP_TRY(ctx, launch_cell_level_pair(EPI_STORE_Z1, a[0], a[1], stream, ctx->splitk, timer.tile(), timer.ksplit(), timer.ev));
+      }
       TRY(timer.end());
     }
     if (plan.groups > 0) {

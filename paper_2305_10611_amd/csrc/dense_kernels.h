@@ -26,9 +26,11 @@ struct PackRowsArgs {
   float* inverse;  // [16 ceil(n / 16)]
 };
 
-// One level: TREE_LEAF or STORE_Z with one segment of at most kDenseMaxK columns, H a multiple of 32.
+// One level: TREE_LEAF, STORE_Z or STORE_Z1 with one segment of at most kDenseMaxK columns, H a multiple of 32; `two`: odd
+// groups work with b, another batch of the same sizes over the same input rows.
 struct DenseArgs {
-  CellLevelArgs a;
+  CellLevelArgs a, b;
+  int32_t two;
   const void* operand; uint32_t operand_bytes;
   float* inverse;
   TreePlaces places;

@@ -1,5 +1,5 @@
 // Wide products with input rows on the fp16 matrix cores at fp32 precision (gfx950): leaf levels and hoisted input
-// transforms, with the weights kept in registers.
+// transforms (of a bidirectional recurrence for both directions in one launch), with the weights kept in registers.
 //
 // Two launches.  pack_rows_kernel finds every input row's scale, splits the row (split_fp16.h) and stores blocks of 16
 // rows as matrix operands, in the order in which the lanes of a matrix instruction want them.  cell_dense_kernel then
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const PackRowsArgs p) {
   }
 }
 
-// G gates (column tiles of 16 units for a single gate: TILES), NS steps a wavefront, CH blocks of 16 units a workgroup
+// G column tiles of 16 (the gates, or for a single gate G blocks of units), NS steps a wavefront, CH blocks of units a workgroup
 template <int G, int EPI, int NS, int CH>
 struct DenseShape {
   static constexpr int NW = 8, KS = NW / CH, RB = 2 / CH;  // RB blocks of rows between two barriers: 512 elements
@@ -86,7 +86,8 @@ template <int G, int EPI, int NS, int CH>
 __global__ __launch_bounds__(512, 2) void cell_dense_kernel(const DenseArgs s) {
   using S = DenseShape<G, EPI, NS, CH>;
   constexpr int NW = S::NW, KS = S::KS, RB = S::RB, ZQ = S::ZQ;
-  static_assert(G == 3 || G == 4, "gates of an element are one vector");
+  constexpr bool kTiles = EPI == EPI_STORE_Z1;
+  static_assert(G <= 4, "the tiles of an element are one vector");
   extern __shared__ __attribute__((aligned(16))) float zbuf[];  // [2][RB][NW][ZQ]
   __shared__ __attribute__((aligned(16))) float s_bias[CH][16][4];
   __shared__ __attribute__((aligned(16))) float s_winv[NW][16][4];
@@ -96,22 +97,26 @@ __global__ __launch_bounds__(512, 2) void cell_dense_kernel(const DenseArgs s) {
   const int at = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
   const int group = at / s.n_cb, cb = at % s.n_cb;
   if (group >= s.n_groups) return;
-  const CellLevelArgs& a = s.a;
+  const CellLevelArgs& a = s.two && (group & 1) ? s.b : s.a;
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ks = w % KS, ch = w / KS;
   const int li = lane & 15, kq = lane >> 4;
   const int H = a.H, K = a.kseg, T = K >> 5;  // 32-k steps, at most KS * NS
   const int blocks = (a.n + 15) >> 4;
-  const int b0 = (int)((long)blocks * group / s.n_groups), b1 = (int)((long)blocks * (group + 1) / s.n_groups);
+  const int share = s.two ? group >> 1 : group, shares = s.two ? s.n_groups >> 1 : s.n_groups;
+  const int b0 = (int)((long)blocks * share / shares), b1 = (int)((long)blocks * (share + 1) / shares);
   if (b0 >= b1) return;
+  // first weight row of tile g of unit block c of this workgroup
+  const auto tile_row = [&](int g, int c) {
+    return kTiles ? 16 * ((cb * CH + c) * G + g) : gate_row<EPI>(g) * H + 16 * (cb * CH + c);
+  };
 
   half8 whi[G][NS], wlo[G][NS];
   {
     floatx4 raw[G][NS][2];  // (every load in flight at once)
-    const int unit0 = 16 * (cb * CH + ch);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const float* row = a.W + ((size_t)gate_row<EPI>(g) * H + unit0 + (lane >> 3)) * (size_t)a.ldw + 4 * (lane & 7);
+      const float* row = a.W + (size_t)(tile_row(g, ch) + (lane >> 3)) * (size_t)a.ldw + 4 * (lane & 7);
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
         const int step = ks + KS * t;
@@ -134,7 +139,7 @@ __global__ __launch_bounds__(512, 2) void cell_dense_kernel(const DenseArgs s) {
         sc[h] = scale_for(largest_of_line(m));
         if ((lane & 7) == 0) s_winv[w][(lane >> 3) + 8 * h][g] = inverse_power(sc[h]);
       }
-      if (ks == 0 && lane < 16) s_bias[ch][li][g] = a.bias ? a.bias[gate_row<EPI>(g) * H + unit0 + li] : 0.0f;
+      if (ks == 0 && lane < 16) s_bias[ch][li][g] = a.bias ? a.bias[tile_row(g, ch) + li] : 0.0f;
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
         turn_write(tile, lane, raw[g][t], sc[0], sc[1]);
@@ -240,7 +245,7 @@ __global__ __launch_bounds__(512, 2) void cell_dense_kernel(const DenseArgs s) {
       const float* const x = a.src0 + (size_t)(a.idx0 ? a.idx0[i] : i) * (size_t)a.ld0;
 #pragma unroll 1
       for (int g = 0; g < G; ++g) {
-        const float* const wr = a.W + ((size_t)gate_row<EPI>(g) * H + j) * (size_t)a.ldw;
+        const float* const wr = a.W + (size_t)(tile_row(g, my_ch) + eu) * (size_t)a.ldw;
         float z = 0.0f;
 #pragma unroll 1
         for (int k = 0; k < K; k += 4) {
@@ -256,6 +261,9 @@ __global__ __launch_bounds__(512, 2) void cell_dense_kernel(const DenseArgs s) {
     if constexpr (EPI == EPI_STORE_Z) {
 #pragma unroll
       for (int g = 0; g < G; ++g) a.zout[(size_t)out * (size_t)(G * H) + g * H + j] = zs[g] + bias[g];
+    } else if constexpr (kTiles) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) a.zout[(size_t)out * (size_t)H + tile_row(g, my_ch) + eu] = zs[g] + bias[g];
     } else {
       const float c = fast_sigmoid(zs[0] + bias[0]) * fast_tanh(zs[2] + bias[2]);
       const float h = fast_sigmoid(zs[1] + bias[1]) * fast_tanh(c);
@@ -269,7 +277,7 @@ __global__ __launch_bounds__(512, 2) void cell_dense_kernel(const DenseArgs s) {
 template <int G, int EPI, int NS, int CH>
 struct Dense {
   static constexpr size_t kLdsBytes = DenseShape<G, EPI, NS, CH>::kLdsBytes;
-  static constexpr int kUnits = 16 * CH;
+  static constexpr int kUnits = 16 * CH * (EPI == EPI_STORE_Z1 ? G : 1);
   static hipError_t launch(DenseArgs s, int n_cu, hipStream_t stream, const LaunchEvents& ev) {
     static std::atomic<uint64_t> configured{0};  // (see tree_kernels.hip)
     int dev = 0;
@@ -284,9 +292,10 @@ struct Dense {
     // one workgroup per compute unit in groups of H / kUnits (nobody waits for anybody)
     s.n_cb = s.a.H / kUnits;
     s.n_groups = n_cu / s.n_cb;
-    const int blocks = (s.a.n + 15) / 16;
+    const int blocks = (s.a.n + 15) / 16 * (s.two ? 2 : 1);
     if (s.n_groups > blocks) s.n_groups = blocks;
     if (s.n_groups < 1) s.n_groups = 1;
+    if (s.two) s.n_groups = s.n_groups < 2 ? 2 : s.n_groups & ~1;
     const unsigned grid = 8u * (unsigned)((s.n_groups * s.n_cb + 7) / 8);
     launch_with_events((cell_dense_kernel<G, EPI, NS, CH>), dim3(grid), dim3(512), kLdsBytes, stream, ev.start, ev.stop, s);
     return hipGetLastError();
@@ -307,7 +316,7 @@ hipError_t launch_gates(const DenseArgs& s, int n_cu, hipStream_t stream, const 
 }  // namespace
 
 bool dense_level_wins(CellEpilogue epi, int32_t n, int32_t H, int32_t K, const SplitKWorkspace& ws) {
-  if ((epi != EPI_TREE_LEAF && epi != EPI_STORE_Z) || n <= 0 || K <= 0 || K > kDenseMaxK || ws.force_bm ||
+  if ((epi != EPI_TREE_LEAF && epi != EPI_STORE_Z && epi != EPI_STORE_Z1) || n <= 0 || K <= 0 || K > kDenseMaxK || ws.force_bm ||
       (double)((n + 15) / 16) * 64 * K > kDenseMaxBytes)
     return false;
   // Two launches, and all weights fetched by every group, have to be earned.  Leaf levels, whole calls, stationary kernel
@@ -316,7 +325,12 @@ bool dense_level_wins(CellEpilogue epi, int32_t n, int32_t H, int32_t K, const S
   // (1.0) 50.2 and 48.4, D = 512 (0.5) 37.2 and 42.7; 750, H = D = 320 (0.6) 40.4 and 41.8.  Small models have fewer columns for
   // every packed row: leaves, split tiles against this one, 22 000, H = D = 192 211 and 217; H = 256, D = 544 295 and 294;
   // input products, 10 000 rows, H = 192, D = 160 87 and 90, H = 256 101 and 98.
+  // Both directions of a bidirectional recurrence in one launch, fp32 tiles against this one: 3 000 rows, H = D = 256 (0.8)
+  // 56.8 and 58.3, H = D = 320 (1.2) 65.7 and 66.5, D = 512, H = 256 (1.6) 61.8 and 61.0; 6 000, H = D = 256 (1.6) 76.8 and
+  // 73.3, H = D = 512 (6.3) 137 and 111; 1 200 rows, H = D = 512 (1.3), the product alone, 21 and 23; short rows: 6 000, D = 128,
+  // H = 512 (1.6) 102 and 104; H = 128 loses throughout (18 000 rows 126 and 136).
   if (H < 256) return false;
+  if (epi == EPI_STORE_Z1) return H % 64 == 0 && K >= 256 && 4.0 * n * H * K >= 1.5e9;
   return 2.0 * (epi == EPI_TREE_LEAF ? 3 : 4) * n * H * K >= 1.0e9;
 }
 
@@ -333,6 +347,12 @@ hipError_t launch_dense_level(CellEpilogue epi, DenseArgs s, void* scratch, int 
   if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   LaunchEvents second;
   second.stop = ev.stop;
+  if (epi == EPI_STORE_Z1) {
+    const int K = s.a.kseg;
+    if (K <= 256) return Dense<4, EPI_STORE_Z1, 1, 1>::launch(s, n_cu, stream, second);
+    if (K <= 512) return Dense<4, EPI_STORE_Z1, 2, 1>::launch(s, n_cu, stream, second);
+    return Dense<4, EPI_STORE_Z1, 4, 1>::launch(s, n_cu, stream, second);
+  }
   return epi == EPI_TREE_LEAF ? launch_gates<3, EPI_TREE_LEAF>(s, n_cu, stream, second)
                               : launch_gates<4, EPI_STORE_Z>(s, n_cu, stream, second);
 }

@@ -1,4 +1,4 @@
-"""Wide leaf levels and LSTM input products with packed input rows against the oracle: every instance (columns up to 128, 256,
+"""Wide leaf levels and input products of LSTMs and bidirectional recurrences with packed input rows against the oracle: every instance (columns up to 128, 256,
 384, 512, 768, 1 024), steps that do not divide evenly, rows that do not fill a block, groups that straddle an XCD, inputs that
 are not to be split, the call that allocates nothing.
 
@@ -58,6 +58,27 @@ def test_lstm_input_products(ctx, H, D, n):
     h, c = takes_it(ctx, lambda: P.run_lstm(ctx, w), "K_LSTM_INPUT")
     oh, oc = oracle.varlen_lstm(w, nthreads=NT)
     assert rel(h, oh) < 1e-6 and rel(c, oc) < 1e-6
+
+
+@pytest.mark.parametrize("H,D,n", [(256, 256, 2865), (512, 288, 1273), (320, 352, 1669), (256, 512, 1433), (512, 736, 499),
+                                   (384, 992, 497)])
+def test_birnn_input_products(ctx, H, D, n):
+    """Both directions in one launch; a feature of 1e9 with weights of 1e-9 and a NaN are what fp32 makes of them."""
+    from tests import parity as P
+    w = gen.birnn_workload(n, 2, 2, H, D, 5, seed=H + D)
+    got = takes_it(ctx, lambda: P.run_birnn(ctx, w), "K_RNN_INPUT")
+    for a, b in zip(got, oracle.birnn(w, nthreads=NT)):
+        assert rel(a, b) < 1e-6
+    w["x"][:, 3] *= 1e9
+    w["fWx"][:, 3] *= 1e-9
+    w["bWx"][:, 3] *= 1e-9
+    want = oracle.birnn(w, nthreads=NT)
+    w["x"][9, 7] = np.nan  # of the fifth sequence
+    rest = np.r_[0:8, 10:2 * n]
+    got = P.run_birnn(ctx, w)
+    for a, b in zip(got, want):
+        assert rel(a[rest], b[rest]) < 1e-6
+    assert np.isnan(got[0][9]).all() and np.isnan(got[1][9]).all()
 
 
 def test_rows_that_are_not_to_be_split(ctx):
