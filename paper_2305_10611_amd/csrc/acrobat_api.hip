@@ -131,6 +131,7 @@ struct acrobat_ctx {
   // the entry point that allocates nothing: a staging buffer of fixed size (made by acrobat_create) and
   // this device's address of the library's static scratch array
   int32_t* h_fixed_stage = nullptr;   // kStaticIndexBytes of pinned host memory
+  int32_t* h_fixed_dev = nullptr;     // its address on the device side
   hipEvent_t fixed_done = nullptr;    // the last upload out of h_fixed_stage has finished
   bool fixed_pending = false;
   unsigned char* static_scratch = nullptr;
@@ -249,8 +250,9 @@ int reserve_indices(acrobat_ctx* ctx, size_t n, hipStream_t stream) {
 }
 
 int upload_indices(acrobat_ctx* ctx, size_t n, hipStream_t stream) {
-  HIP_TRY(ctx, hipMemcpyAsync(ctx->d_idx, ctx->h_stage, n * sizeof(int32_t), hipMemcpyHostToDevice, stream));
-  if (stream_is_capturing(stream)) return ACROBAT_OK;
+  const bool capturing = stream_is_capturing(stream);
+  HIP_TRY(ctx, launch_upload(ctx->d_idx, ctx->h_stage, ctx->h_stage_dev, n, capturing, stream));
+  if (capturing) return ACROBAT_OK;
   HIP_TRY(ctx, hipEventRecord(ctx->stage_done, stream));
   ctx->stage_pending = true;
   return ACROBAT_OK;
@@ -537,6 +539,7 @@ int acrobat_create(acrobat_ctx** out, int device) {
   if (hipEventCreateWithFlags(&ctx->stage_done, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&ctx->fixed_done, hipEventDisableTiming) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&ctx->h_fixed_stage), kStaticIndexBytes, hipHostMallocDefault) != hipSuccess ||
+      hipHostGetDevicePointer(reinterpret_cast<void**>(&ctx->h_fixed_dev), ctx->h_fixed_stage, 0) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&ctx->h_status), sizeof(unsigned), hipHostMallocDefault) != hipSuccess ||
       hipHostGetDevicePointer(reinterpret_cast<void**>(&ctx->h_status_dev), ctx->h_status, 0) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&ctx->d_sync), kSyncWordsPadded * sizeof(unsigned)) != hipSuccess ||
@@ -886,9 +889,6 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
       std::memcpy(st + N + n_leaf, s.lrow.data() + n_leaf, n_int * sizeof(int32_t));
       std::memcpy(st + 2 * (size_t)N + n_leaf, s.rrow.data() + n_leaf, n_int * sizeof(int32_t));
     };
-    auto copy_up = [&](size_t first, size_t count) {
-      return hipMemcpyAsync(d_idx + first, st + first, count * sizeof(int32_t), hipMemcpyHostToDevice, stream);
-    };
     auto staging_in_flight = [&]() {  // the staging buffer may be rewritten once these uploads are through
       if (stream_is_capturing(stream)) return hipSuccess;
       const hipError_t e = hipEventRecord(noalloc ? ctx->fixed_done : ctx->stage_done, stream);
@@ -905,7 +905,8 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     if (packed)
       ctx->tree_groups.places(s, ctx->leaf_tokens, plan.groups, plan.first, st, st + N, st + 2 * (size_t)N, st + at_off, st + at_place);
     for (size_t i = 0; i < n_iota; ++i) st[3 * (size_t)N + i] = (int32_t)i;
-    HIP_TRY(ctx, copy_up(0, at_place + (packed ? (size_t)N : 0)));  // one upload (the second operands of level 0 are never read)
+    HIP_TRY(ctx, launch_upload(d_idx, st, noalloc ? ctx->h_fixed_dev : ctx->h_stage_dev, at_place + (packed ? (size_t)N : 0),
+                               stream_is_capturing(stream), stream));  // (the second operands of level 0 are never read)
     HIP_TRY(ctx, staging_in_flight());
     const int32_t* d_out = d_idx;
     const int32_t* d_ia = d_idx + N;

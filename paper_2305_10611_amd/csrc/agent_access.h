@@ -18,6 +18,7 @@ typedef unsigned agent_u4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRsrcFlags = 0x00020000;  // raw buffer resource, 32-bit data format (gfx9)
 constexpr int kAuxAgentScope = 16;      // cache policy sc1: coherent at agent scope
+constexpr int kAuxSystemScope = 17;     // sc0 sc1: coherent at system scope (pinned host memory)
 
 // Buffer resource over [base, base + bytes), bytes < 2^32.  Offsets past the end read zero / store nothing.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t agent_buffer(const void* base, unsigned bytes) {

@@ -150,6 +150,10 @@ struct GatherArgs {
 };
 hipError_t launch_gather_rows(const GatherArgs& g, hipStream_t stream, const LaunchEvents& ev = LaunchEvents());
 
+// n int32 of a pinned host buffer (`host`, and its address on the device side) to device memory, both 16-byte aligned.
+// `capturing`: the stream is being captured, the copy is then always a copy node.
+hipError_t launch_upload(int32_t* dst, const int32_t* host, const int32_t* host_dev, size_t n, bool capturing, hipStream_t stream);
+
 hipError_t launch_mvrnn_level(const MvrnnLevelArgs& a, hipStream_t stream, int32_t* tile,
                               const LaunchEvents& ev = LaunchEvents());
 

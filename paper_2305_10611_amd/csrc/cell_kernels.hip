@@ -1017,6 +1017,16 @@ __global__ __launch_bounds__(kThreads) void gather_rows_kernel(const GatherArgs 
   }
 }
 
+// Index lists out of pinned host memory, read over the bus.
+__global__ __launch_bounds__(kThreads) void upload_kernel(const int* src, int* dst, int n) {
+  const __amdgpu_buffer_rsrc_t rsrc = agent_buffer(src, (unsigned)n * 4u);
+  const int quads = n >> 2, first = (int)blockIdx.x * kThreads + (int)threadIdx.x;
+  for (int i = first; i < quads; i += (int)gridDim.x * kThreads)
+    reinterpret_cast<agent_u4*>(dst)[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, 16 * i, 0, kAuxSystemScope);
+  const int i = 4 * quads + first;
+  if (i < n) dst[i] = (int)__builtin_amdgcn_raw_buffer_load_b32(rsrc, 4 * i, 0, kAuxSystemScope);
+}
+
 template <class F>
 hipError_t dispatch_epilogue(CellEpilogue epi, F&& f) {
   switch (epi) {
@@ -1061,6 +1071,16 @@ hipError_t launch_gather_rows(const GatherArgs& g, hipStream_t stream, const Lau
   const long rows = (long)g.n * g.count;
   const unsigned grid = (unsigned)((rows + 3) / 4 < 4096 ? (rows + 3) / 4 : 4096);
   launch_with_events(gather_rows_kernel, dim3(grid), dim3(kThreads), 0, stream, ev.start, ev.stop, g);
+  return hipGetLastError();
+}
+
+hipError_t launch_upload(int32_t* dst, const int32_t* host, const int32_t* host_dev, size_t n, bool capturing, hipStream_t stream) {
+  // A copy command of up to 16 KB costs as much as a launch, from there on 9 to 12 us more (with four small kernels behind
+  // it, copy command / this kernel: 16 KB 14.3 / 14.3 us, 17 KB 23.6 / 14.5, 256 KB 27.8 / 15.2, 1 MB 42 / 34, 16 MB 316 /
+  // 306; the bus is what bounds it: 56 GB/s.  More than 256 workgroups are slower, 8 MB 188 against 159 us).
+  if (capturing || n <= 4096 || n >= ((size_t)1 << 29)) return hipMemcpyAsync(dst, host, n * sizeof(int32_t), hipMemcpyHostToDevice, stream);
+  const size_t grid = (n / 4 + kThreads - 1) / kThreads;
+  launch_with_events(upload_kernel, dim3((unsigned)(grid < 256 ? grid : 256)), dim3(kThreads), 0, stream, hipEvent_t(nullptr), hipEvent_t(nullptr), host_dev, dst, (int)n);
   return hipGetLastError();
 }
 
