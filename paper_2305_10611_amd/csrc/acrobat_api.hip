@@ -1084,11 +1084,11 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
   }
 }
 
-// Groups a recurrence over sequences is dealt out to for one launch of the stationary kernel; 0: not on that kernel.
+// Groups a recurrence over sequences is dealt out to for one launch of the packed kernel; 0: not on that kernel.
 struct SeqPlan {
   int32_t groups = 0, variant = 0;
   bool whole = false;  // one launch record for all steps (else one per step)
-  size_t n_off = 0, n_idx = 0;  // entries of the offset table; of all lists: rows, previous rows, offsets, places
+  size_t n_off = 0, n_idx = 0;  // entries of the offset table; of both lists: rows, offsets
   size_t operand_bytes = 0;     // of packed states; c states take as much
 };
 
@@ -1099,8 +1099,10 @@ SeqPlan plan_recurrence(acrobat_ctx* ctx, CellEpilogue epi, int32_t H, int32_t R
     return p;
   // The kernels of persistent_kernels.hip step faster at H = 128 and, with a single gate, 256 while a batch has at most 256
   // sequences, and with a single gate at H = 512 while their workgroups have a compute unit each (LSTM, sequences of 1
-  // to 60 steps, H = 128, 8 / 256 sequences 115 / 148 against 128 / 168 us, but H = 256 160 / 201 against 140 / 184.  BiRNN, 1 to 40 steps, H = 128 82 / 100 against 93 / 119, H = 256 91 / 136 against 97 / 143; H = 512,
-  // 64 sequences 138 against 141, 128 200 against 158, 256 354 against 202).  Below H = 128 a step is a launch of 4 us.
+  // to 60 steps, H = 128, 8 / 256 sequences 115 / 148 against 128 / 168 us, but H = 256 160 / 201 against 140 / 184.  BiRNN, 1
+  // to 40 steps, H = 128 82 / 100 against 93 / 119, H = 256 91 / 136 against 97 / 143; H = 512, 64 sequences 138 against 141,
+  // 128 200 against 158, 256 354 against 202; 100 sequences of 1 to 3 steps 37 against 39).  Below H = 128 a step is a launch
+  // of 4 us.
   p.variant = packed_variant(epi, H, n_live, directions, ctx->n_cu);
   const int32_t most = packed_groups(epi, H, H, p.variant, ctx->n_cu) / directions;
   p.groups = directions * std::min({most, (n_live + 15) / 16, (int32_t)((4 * (int64_t)R + 4096) / n_steps)});
@@ -1131,7 +1133,8 @@ int reserve_recurrence(acrobat_ctx* ctx, const SeqPlan& plan, int32_t directions
   return reserve_indices(ctx, n_idx, stream);
 }
 
-// The steps of a recurrence, lists and offset table staged and uploaded (sa.off), in one launch or one per step.  step_off[t + 1] - step_off[t]: nodes of step t, per direction.
+// The steps of a recurrence, lists and offset table staged and uploaded (sa.off), in one launch or one per step.
+// step_off[t + 1] - step_off[t]: nodes of step t, per direction.
 int run_recurrence(acrobat_ctx* ctx, CellEpilogue epi, StationaryArgs& sa, const SeqPlan& plan, int32_t n_steps,
                    const int32_t* step_off, int32_t directions, int32_t R, LaunchTimer& timer) {
   const int32_t H = sa.a[0].H;

@@ -1078,9 +1078,11 @@ hipError_t launch_upload(int32_t* dst, const int32_t* host, const int32_t* host_
   // A copy command of up to 16 KB costs as much as a launch, from there on 9 to 12 us more (with four small kernels behind
   // it, copy command / this kernel: 16 KB 14.3 / 14.3 us, 17 KB 23.6 / 14.5, 256 KB 27.8 / 15.2, 1 MB 42 / 34, 16 MB 316 /
   // 306; the bus is what bounds it: 56 GB/s.  More than 256 workgroups are slower, 8 MB 188 against 159 us).
-  if (capturing || n <= 4096 || n >= ((size_t)1 << 29)) return hipMemcpyAsync(dst, host, n * sizeof(int32_t), hipMemcpyHostToDevice, stream);
+  if (capturing || n <= 4096 || n >= ((size_t)1 << 29))
+    return hipMemcpyAsync(dst, host, n * sizeof(int32_t), hipMemcpyHostToDevice, stream);
   const size_t grid = (n / 4 + kThreads - 1) / kThreads;
-  launch_with_events(upload_kernel, dim3((unsigned)(grid < 256 ? grid : 256)), dim3(kThreads), 0, stream, hipEvent_t(nullptr), hipEvent_t(nullptr), host_dev, dst, (int)n);
+  launch_with_events(upload_kernel, dim3((unsigned)(grid < 256 ? grid : 256)), dim3(kThreads), 0, stream, hipEvent_t(nullptr),
+                     hipEvent_t(nullptr), host_dev, dst, (int)n);
   return hipGetLastError();
 }
 

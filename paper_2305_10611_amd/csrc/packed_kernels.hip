@@ -13,8 +13,9 @@
 // Bound: narrow levels and steps by their chain - announcement 0.9, operand 0.6, matrix instructions and sums 0.5, gates and
 // stores 0.5 us -, wide levels by the matrix cores (7 186 rows, H = 512: 102 us, 1.1 PFLOP/s of fp16 products; a large
 // library product reaches 1.3).  Forward calls against the gathering kernel: 8 trees of 20 leaves, H = 256 50 -> 43 us, 64
-// trees 91 -> 84; LSTM, 256 sequences, H = 512 528 -> 470, 75 sequences, H = 320 229 -> 171; BiRNN, 600 sequences, H = 256
-// 214 -> 175.
+// trees 91 -> 84; LSTM, 256 sequences, H = 512 528 -> 470, 75 sequences, H = 320 229 -> 157; BiRNN, 600 sequences, H = 256
+// 214 -> 175.  A recurrence needs no list of places or previous rows: a share's sequences are the first ones of the share
+// before, so the words that a call uploads are as many as its rows.
 //
 // Operand: blocks of 16 rows; a 32-k step of a block is 64 lanes x 16 bytes of hi terms, then the same of lo terms; lane
 // l holds row l % 16, k = 4 (l / 16) + 0 .. 3 and 16 more.  A tree node has its left child's H columns, then its right

@@ -74,8 +74,8 @@ __global__ void fill_u32_kernel(unsigned* p, unsigned value, int n) {
 // length (the host sorts them), so few of those rows are dead.
 // Blocks whose workgroups have ids 256 apart may share a compute unit and must be different ones - workgroups of one
 // block wait for each other, and as co-residents they were measured to take turns - hence the numbering below.
-// Instances: H = 128 and 256.  At H = 512 the weight-stationary kernel steps faster (393 against 443 us for 256
-// sequences of 1 to 100 steps); here it is slower (262 against 216 us at H = 128, 293 against 283 at H = 256).
+// Instances: H = 128, where a step is faster than on the kernel whose operands arrive packed (256 sequences of 1 to 60 steps
+// 148 against 168 us), and H = 256, which only takes this one where there is no room for packed operands (201 against 184).
 template <int H>
 __global__ __launch_bounds__(kThreads, 2) void lstm_persistent_kernel(const LstmPersistentArgs a) {
   constexpr int CB = H / 16;   // column blocks = workgroups per node block

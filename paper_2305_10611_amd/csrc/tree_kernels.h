@@ -31,8 +31,8 @@ struct StationaryArgs {
   unsigned* status;
   int32_t max_polls;
   unsigned long long* stamps;  // [levels * n_groups] 100 MHz clock at the end of a group's share of a level, or null
-  // packed_kernels.hip, and the operands that leaves go to: the operands of all blocks, split states and c states, and every list position's place in
-  // them - 16 block + row of the node that reads it, 2 (16 block + row) + side; -1: nobody reads it here
+  // packed_kernels.hip, and the operands that leaves go to: the operands of all blocks, split states and c states, and every
+  // list position's place in them, 2 (16 block + row of the node that reads it) + side; -1: nobody reads it here
   void* operand; uint32_t operand_bytes;  // at most kPackedMaxBytes
   float* cells;
   const int32_t* place;    // trees only

@@ -1,5 +1,8 @@
 // Weight-stationary cell kernels for gfx950: a workgroup keeps the weight rows of 16 hidden units (all G gates) in
-// its registers and node rows stream past them, 16 at a time.
+// its registers and node rows stream past them, 16 at a time.  They take small leaf levels and the tree levels whose
+// operands do not arrive packed: level by level under capture, wide levels of a few large trees on the whole chip, calls
+// without room for packed operands.  All levels in one launch otherwise run on packed_kernels.hip, with the same bits, and
+// large leaf levels on dense_kernels.hip.
 //
 // What this is for.  The level kernels fetch weight tiles again for every node tile: 640 KB of weights per 64 nodes at
 // H = 512, which is what bounds a level of a few hundred nodes, and every level of a tree batch is a launch of its own.
@@ -19,12 +22,12 @@
 // finish even blocks and those of the other half odd ones, with four - two workgroups then share a compute unit - all
 // threads finish.
 //
-// Bound: the chain of dependent steps.  A level of one block per group takes 3 us (stores complete, arrival counter,
-// rows, 60 matrix instructions per wavefront, sums, gates), against 5 to 15 us for a launch of its own; a further block
-// of 16 rows 2.4 us at H = 512, of which 0.8 us are matrix instructions.  TreeLSTM forward, 256 trees, H = 512: 672 ->
-// 317 us; 64 trees, H = 256: 143 -> 95 us (with the wide leaf levels on the split tiles).  Tried: handing the buffers
-// from wavefront to wavefront with counters in LDS instead of the barrier (117 instead of 99 us on 2 943 rows),
-// a loop per turn so that the waits are exact (171 registers spilled).
+// Bound: the chain of dependent steps.  A level of one block per group takes 3 us (stores complete, arrival counter, rows,
+// 60 matrix instructions per wavefront, sums, gates), against 5 to 15 us for a launch of its own; a further block of 16
+// rows 2.4 us at H = 512, of which 0.8 us are matrix instructions (operands packed: 1.8).  TreeLSTM forward, 256 trees, H
+// = 512: 672 -> 317 us; 64 trees, H = 256: 143 -> 95 us (with the wide leaf levels on the split tiles; with packed
+// operands and rows 247 and 68).  Tried: handing the buffers from wavefront to wavefront with counters in LDS instead of
+// the barrier (117 instead of 99 us on 2 943 rows), a loop per turn so that the waits are exact (171 registers spilled).
 #include "tree_kernels.h"
 
 #include "cell_epilogue.h"
