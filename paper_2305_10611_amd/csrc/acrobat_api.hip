@@ -274,20 +274,19 @@ bool indices_fit(acrobat_ctx* ctx, size_t n, hipStream_t stream) {
   return (n <= ctx->stage_cap && n <= ctx->idx_cap) || !stream_is_capturing(stream);
 }
 
-// Room for split weights and row scales.  False where there is none - the stream is being captured and no call of this
-// size came before, or the device memory is used up: the level then runs on the fp32 tiles, which need none.
+// Room for split weights and row scales, or packed rows.  False where there is none - the stream is being captured and no
+// call of this size came before, or the device memory is used up; what was there stays then.  The level runs on kernels
+// that need none.
 bool reserve_split(acrobat_ctx* ctx, size_t bytes, hipStream_t stream) {
   if (bytes <= ctx->split_cap) return true;
   if (stream_is_capturing(stream)) return false;
-  if (ctx->d_split) (void)hipFree(ctx->d_split);  // waits for kernels still using it
-  ctx->d_split = nullptr;
-  ctx->split_cap = 0;
   const size_t cap = bytes + bytes / 8;  // (the row scales grow with the batch)
   void* p = nullptr;
   if (hipMalloc(&p, cap) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
+  if (ctx->d_split) (void)hipFree(ctx->d_split);  // waits for kernels still using it
   ctx->d_split = static_cast<unsigned char*>(p);
   ctx->split_cap = cap;
   return true;
@@ -655,16 +654,18 @@ struct TreePlan {
   bool in_order = false;  // groups of consecutive trees
 };
 
-TreePlan plan_tree(const acrobat_ctx* ctx, const TreeSchedule& s, int32_t H, int32_t D, int32_t V, bool noalloc, size_t n_iota) {
+TreePlan plan_tree(acrobat_ctx* ctx, const TreeSchedule& s, int32_t H, int32_t D, int32_t V, bool noalloc, size_t n_iota,
+                   hipStream_t stream) {
   TreePlan p;
   const int32_t N = s.n_nodes;
   constexpr double kMaxBytes = 4294967296.0 - 512.0;  // rows are read through a buffer resource
   if (!ctx->persistent || ctx->splitk.force_bm) return p;
-  // A wide leaf level goes to the packed product, or where that has no room to the split tiles from four rounds of them on;
-  // others stay on the stationary kernel, whose workgroups each convert every row for 48 columns.
+  // A wide leaf level goes to the packed product, or where there is no room for its rows to the split tiles from four rounds
+  // of them on; others stay on the stationary kernel, whose workgroups each convert every row for 48 columns.
   const int32_t n_leaf = s.level_off[1];
+  const size_t dense_bytes = dense_scratch_bytes(n_leaf, D);
   p.dense_leaf = dense_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ctx->splitk) &&
-                 (!noalloc || dense_scratch_bytes(n_leaf, D) <= kStaticScratchBytes / 8);
+                 (noalloc ? dense_bytes <= kStaticScratchBytes / 8 : reserve_split(ctx, dense_bytes, stream));
   const bool tiles = split_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ctx->splitk) && (long)((n_leaf + 63) / 64) * (H / 32) >= 1024 &&
                      (!noalloc || ((size_t)5 * H * D + 10 * (size_t)H + n_leaf) * sizeof(float) < kStaticScratchBytes / 2);
   if (!p.dense_leaf && !tiles && (double)std::max(V, N) * D * sizeof(float) < kMaxBytes)
@@ -817,7 +818,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     for (int32_t lv = 1; lv < s.n_levels; ++lv) n_wide = std::max(n_wide, s.level_off[lv + 1] - s.level_off[lv]);
     const bool unfused = !ctx->gather_fusion && !noalloc;
     const size_t n_iota = unfused ? (size_t)std::max(n_leaf, 2 * n_wide) : 0;
-    TreePlan plan = plan_tree(ctx, s, H, D, V, noalloc, n_iota);
+    TreePlan plan = plan_tree(ctx, s, H, D, V, noalloc, n_iota, stream);
     if (!noalloc && !indices_fit(ctx, 3 * (size_t)N + n_iota + (plan.grouped ? (size_t)s.n_levels * plan.groups + 1 : 0), stream)) plan.groups = 0;
     const size_t n_off = plan.groups > 0 && plan.grouped ? (size_t)s.n_levels * plan.groups + 1 : 0;
     // Stationary launches of the plan: level 0, then the internal levels - in one launch, whose workgroups wait for each
@@ -917,7 +918,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     // Wide levels run on the split contraction: the weights they use are split first, and the leaves' embedding rows
     // get their scales, in one launch.
     const bool split_leaf = !plan.leaf && !plan.dense_leaf && split_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ws);
-    const bool split_internal = (plan.groups == 0 || plan.first > 1) && n_wide > 0 && split_level_wins(EPI_TREE_INTERNAL, n_wide, H, 2 * H, ws);
+    bool split_internal = (plan.groups == 0 || plan.first > 1) && n_wide > 0 && split_level_wins(EPI_TREE_INTERNAL, n_wide, H, 2 * H, ws);
     struct { unsigned char* w; float* scale; } split_w[2] = {};
     float* leaf_scale = nullptr;
     SplitRowsArgs split_rows{};
@@ -929,7 +930,12 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
       const size_t bytes = (leaf_bytes + int_bytes + scale_bytes + 255) / 256 * 256;
       unsigned char* at = nullptr;
       if (!noalloc) {
-        if (reserve_split(ctx, bytes, stream)) at = ctx->d_split;
+        if (reserve_split(ctx, bytes, stream)) {
+          at = ctx->d_split;
+        } else if (plan.dense_leaf) {  // (their room is there)
+          at = ctx->d_split;
+          split_internal = false;
+        }
       } else if (bytes <= ws.partial_floats * sizeof(float)) {  // the end of the partial tiles' region
         ws.partial_floats -= bytes / sizeof(float);
         at = reinterpret_cast<unsigned char*>(ws.partial + ws.partial_floats);

@@ -83,6 +83,18 @@ def run_drnn(ctx, w, mode=2, use_ghosts=True, use_bias=True, max_nodes=None, che
     return rc, trees, stats, tuple(v[:n].cpu().numpy() for v in (a, f, g, y))
 
 
+def kernels_of(call):
+    """Names of the kernels that run while call() is executed (a graph's replay counts), in no order."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    names = [e.key for e in p.key_averages() if "acrobat::" in e.key]
+    assert names, "the profiler saw no kernel of the library"
+    return names
+
+
 from workloads.generators import match_trees, tree_paths  # noqa: E402,F401  (structure helpers, shared with bench.py)
 
 

@@ -1,0 +1,57 @@
+"""Which kernel takes a call, where neither its results nor its launch records tell, and calls at the limits of the room that
+packed operands and packed rows have: against the oracle at 1e-6 over the 2-norm (as in test_split_contraction)."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import generators as gen
+
+pytestmark = pytest.mark.gpu
+
+NT = oracle.default_threads()
+
+
+def rel(got, want):
+    want = want.astype(np.float64)
+    return float(np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want))
+
+
+@pytest.fixture()
+def ctx():
+    """A context of its own for every test: what calls before it have made room for counts."""
+    import paper_2305_10611_amd as A
+    c = A.Context(0)
+    yield c
+    c.close()
+
+
+def test_captured_leaves_without_room_for_packed_rows(ctx):
+    """The call before the capture has leaves too narrow for the packed product: the captured one takes the kernel that
+    needs no room, not the level kernels."""
+    import torch
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    make = lambda D: gen.treelstm_workload(340, 3, 3, 512, 60, "uniform", seed=5, bias_scale=0.2, D=D)
+    P.run_treelstm(ctx, make(32))
+    w = make(512)
+    t = {k: P.dev(w[k]) for k in ("emb", "W_leaf", "b_leaf", "U", "b")}
+    h, c = P.nan_filled(5 * 340, 512), P.nan_filled(5 * 340, 512)
+    st, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=st, capture_error_mode="relaxed"):
+        rc = ctx.acrobat_treelstm_forward(w, 512, 512, 60, t["emb"], t["W_leaf"], t["b_leaf"], t["U"], t["b"], h, c, st.cuda_stream)
+    assert rc == A.OK, ctx.acrobat_last_error()
+    want = oracle.treelstm(w, nthreads=NT)
+    for _ in range(2):
+        h.fill_(float("nan")); c.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert rel(h.cpu().numpy(), want[0]) < 1e-6 and rel(c.cpu().numpy(), want[1]) < 1e-6
+    # the profiler does not see a replay's kernels, but a leaf's bits do not depend on the rest of the batch: 90 leaves
+    few = dict(w, n_trees=30, tree_off=w["tree_off"][:31])
+    few.update({k: w[k][:150] for k in ("left", "right", "token")})
+    got = h.cpu().numpy()[:150]
+    del g
+    names = P.kernels_of(lambda: few.update(h=P.run_treelstm(ctx, few)[0]))
+    assert any("cell_stationary_kernel<3," in k for k in names), names
+    assert np.array_equal(got, few["h"])
