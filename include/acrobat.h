@@ -137,9 +137,10 @@ int acrobat_treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32
 
 /* acrobat_treelstm_forward for callers that cannot allocate: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same arguments, same results (same kernels, same schedule,
- * same choice of kernel variant per level as long as a level's partial tiles fit the fixed workspace; a
- * level whose partial tiles do not fit runs unsplit, which only changes the summation order), but the
- * call allocates and frees nothing on the device or in pinned memory: the index lists are staged in a
+ * same choice of kernel variant per level as long as a level's partial tiles or split weights fit the fixed
+ * workspace; a level whose partial tiles do not fit runs unsplit and one whose split weights do not fit - 40 H^2 bytes
+ * for internal levels that take a launch each, 20 H D for leaf levels with D > 1 024, about 28 MB fit - on fp32 tiles,
+ * which only changes the rounding), but the call allocates and frees nothing on the device or in pinned memory: the index lists are staged in a
  * pinned buffer of fixed size that acrobat_create made, and their device copy and the partial tiles of
  * k-split levels live in one array of ACROBAT_NOALLOC_SCRATCH_MIB MiB that is part of the library's
  * device image.  Each GPU the library is used on holds that array until the process ends.

@@ -665,7 +665,7 @@ TreePlan plan_tree(acrobat_ctx* ctx, const TreeSchedule& s, int32_t H, int32_t D
   const int32_t n_leaf = s.level_off[1];
   const size_t dense_bytes = dense_scratch_bytes(n_leaf, D);
   p.dense_leaf = dense_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ctx->splitk) &&
-                 (noalloc ? dense_bytes <= kStaticScratchBytes / 8 : reserve_split(ctx, dense_bytes, stream));
+                 (noalloc || reserve_split(ctx, dense_bytes, stream));  // (without allocations: in pieces, if need be)
   const bool tiles = split_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ctx->splitk) && (long)((n_leaf + 63) / 64) * (H / 32) >= 1024 &&
                      (!noalloc || ((size_t)5 * H * D + 10 * (size_t)H + n_leaf) * sizeof(float) < kStaticScratchBytes / 2);
   if (!p.dense_leaf && !tiles && (double)std::max(V, N) * D * sizeof(float) < kMaxBytes)
@@ -870,6 +870,61 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
       d_idx = ctx->d_idx;
       ws = ctx->splitk;
     }
+    const int32_t* d_out = d_idx;
+    const int32_t* d_ia = d_idx + N;
+    const int32_t* d_ib = d_idx + 2 * (size_t)N;
+    const int32_t* d_iota = d_idx + 3 * (size_t)N;
+
+    // Wide levels run on the split contraction: the weights they use are split first, and the leaves' embedding rows
+    // get their scales, in one launch.
+    const bool split_leaf = !plan.leaf && !plan.dense_leaf && split_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ws);
+    bool split_internal = (plan.groups == 0 || plan.first > 1) && n_wide > 0 && split_level_wins(EPI_TREE_INTERNAL, n_wide, H, 2 * H, ws);
+    struct { unsigned char* w; float* scale; } split_w[2] = {};
+    float* leaf_scale = nullptr;
+    SplitRowsArgs split_rows{};
+    unsigned char* dense_at = nullptr;  // the leaves' embedding rows as operands, then their inverse scales
+    size_t leaf_bytes = 0;
+    if (split_leaf || split_internal || plan.dense_leaf) {
+      leaf_bytes = split_leaf ? (size_t)5 * H * D * sizeof(float) : plan.dense_leaf ? dense_scratch_bytes(n_leaf, D) : 0;
+      const size_t int_bytes = split_internal ? (size_t)5 * H * 2 * H * sizeof(float) : 0;
+      const size_t scale_bytes = ((size_t)10 * H + n_leaf) * sizeof(float);
+      auto all = [&] { return (leaf_bytes + (split_leaf || split_internal ? int_bytes + scale_bytes : 0) + 255) / 256 * 256; };
+      const size_t region = ws.partial_floats * sizeof(float);
+      if (noalloc && plan.dense_leaf) {  // in pieces of 4 MiB at least; half of the region stays for levels that may be split
+        const size_t least = std::min(leaf_bytes, (size_t)4 << 20), beside = int_bytes + scale_bytes;
+        split_internal = split_internal && least + beside <= region;
+        const size_t kept = (split_internal ? beside : 0) + region / 8 * (plan.groups > 0 ? 1 : 4);
+        leaf_bytes = std::min(leaf_bytes, std::max(least, region > kept ? (region - kept) / 256 * 256 : 0));
+      }
+      unsigned char* at = nullptr;
+      if (!noalloc) {
+        if (reserve_split(ctx, all(), stream)) {
+          at = ctx->d_split;
+        } else if (plan.dense_leaf) {  // (their room is there)
+          at = ctx->d_split;
+          split_internal = false;
+        }
+      } else if (all() <= region) {  // the end of the partial tiles' region
+        ws.partial_floats -= all() / sizeof(float);
+        at = reinterpret_cast<unsigned char*>(ws.partial + ws.partial_floats);
+      }
+      if (at) {
+        SplitRowsArgs sr{};
+        float* scale = reinterpret_cast<float*>(at + leaf_bytes + int_bytes);
+        if (plan.dense_leaf) dense_at = at;
+        if (split_leaf) {  // the rows of gates i, o, u only
+          split_w[0] = {at, scale};
+          leaf_scale = scale + (size_t)10 * H;
+          sr.job[sr.count++] = {d_Wleaf, 3 * H, D, nullptr, H, 2 * H, at, scale};
+          sr.job[sr.count++] = {d_emb, n_leaf, D, d_ia, 0, 0, nullptr, leaf_scale};
+        }
+        if (split_internal) {
+          split_w[1] = {at + leaf_bytes, scale + (size_t)5 * H};
+          sr.job[sr.count++] = {d_U, 5 * H, 2 * H, nullptr, 5 * H, 0, split_w[1].w, split_w[1].scale};
+        }
+        split_rows = sr;
+      }
+    }
     unsigned char* packed_at = ctx->d_packed;
     if (packed && noalloc) {  // the end of the partial tiles' region; a quarter of it stays
       const size_t floats = 2 * operand_bytes / sizeof(float);
@@ -909,54 +964,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     HIP_TRY(ctx, launch_upload(d_idx, st, noalloc ? ctx->h_fixed_dev : ctx->h_stage_dev, at_place + (packed ? (size_t)N : 0),
                                stream_is_capturing(stream), stream));  // (the second operands of level 0 are never read)
     HIP_TRY(ctx, staging_in_flight());
-    const int32_t* d_out = d_idx;
-    const int32_t* d_ia = d_idx + N;
-    const int32_t* d_ib = d_idx + 2 * (size_t)N;
-    const int32_t* d_iota = d_idx + 3 * (size_t)N;
-
     LaunchTimer timer{ctx, stream, !noalloc};
-    // Wide levels run on the split contraction: the weights they use are split first, and the leaves' embedding rows
-    // get their scales, in one launch.
-    const bool split_leaf = !plan.leaf && !plan.dense_leaf && split_level_wins(EPI_TREE_LEAF, n_leaf, H, D, ws);
-    bool split_internal = (plan.groups == 0 || plan.first > 1) && n_wide > 0 && split_level_wins(EPI_TREE_INTERNAL, n_wide, H, 2 * H, ws);
-    struct { unsigned char* w; float* scale; } split_w[2] = {};
-    float* leaf_scale = nullptr;
-    SplitRowsArgs split_rows{};
-    unsigned char* dense_at = nullptr;  // the leaves' embedding rows as operands, then their inverse scales
-    if (split_leaf || split_internal || plan.dense_leaf) {
-      const size_t leaf_bytes = split_leaf ? (size_t)5 * H * D * sizeof(float) : plan.dense_leaf ? dense_scratch_bytes(n_leaf, D) : 0;
-      const size_t int_bytes = split_internal ? (size_t)5 * H * 2 * H * sizeof(float) : 0;
-      const size_t scale_bytes = ((size_t)10 * H + n_leaf) * sizeof(float);
-      const size_t bytes = (leaf_bytes + int_bytes + scale_bytes + 255) / 256 * 256;
-      unsigned char* at = nullptr;
-      if (!noalloc) {
-        if (reserve_split(ctx, bytes, stream)) {
-          at = ctx->d_split;
-        } else if (plan.dense_leaf) {  // (their room is there)
-          at = ctx->d_split;
-          split_internal = false;
-        }
-      } else if (bytes <= ws.partial_floats * sizeof(float)) {  // the end of the partial tiles' region
-        ws.partial_floats -= bytes / sizeof(float);
-        at = reinterpret_cast<unsigned char*>(ws.partial + ws.partial_floats);
-      }
-      if (at) {
-        SplitRowsArgs sr{};
-        float* scale = reinterpret_cast<float*>(at + leaf_bytes + int_bytes);
-        if (plan.dense_leaf) dense_at = at;
-        if (split_leaf) {  // the rows of gates i, o, u only
-          split_w[0] = {at, scale};
-          leaf_scale = scale + (size_t)10 * H;
-          sr.job[sr.count++] = {d_Wleaf, 3 * H, D, nullptr, H, 2 * H, at, scale};
-          sr.job[sr.count++] = {d_emb, n_leaf, D, d_ia, 0, 0, nullptr, leaf_scale};
-        }
-        if (split_internal) {
-          split_w[1] = {at + leaf_bytes, scale + (size_t)5 * H};
-          sr.job[sr.count++] = {d_U, 5 * H, 2 * H, nullptr, 5 * H, 0, split_w[1].w, split_w[1].scale};
-        }
-        split_rows = sr;
-      }
-    }
     StationaryArgs sa{};
     sa.n_cb = H / 16;
     sa.counters = ws.counters;
@@ -1018,7 +1026,7 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
         if (timer.tile()) *timer.tile() = 16;
         if (timer.ksplit()) *timer.ksplit() = -1;
         if (packed) da.places = {packed_at, (uint32_t)operand_bytes, reinterpret_cast<float*>(packed_at + operand_bytes), d_idx + at_place};
-        HIP_TRY(ctx, launch_dense_level(EPI_TREE_LEAF, da, dense_at, ws.n_cu, stream, timer.ev));
+        HIP_TRY(ctx, launch_dense_level(EPI_TREE_LEAF, da, dense_at, leaf_bytes, ws.n_cu, stream, timer.ev));
         TRY(timer.end());
         continue;
       }
@@ -1377,7 +1385,7 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
         if (timer.ksplit()) *timer.ksplit() = -1;
         DenseArgs da{};
         da.a = a;
-        HIP_TRY(ctx, launch_dense_level(EPI_STORE_Z, da, ctx->d_split, ctx->splitk.n_cu, stream, timer.ev));
+        HIP_TRY(ctx, launch_dense_level(EPI_STORE_Z, da, ctx->d_split, dense_scratch_bytes(R, D), ctx->splitk.n_cu, stream, timer.ev));
         return timer.end();
       }
       if (split) {  // (timed with the contraction that follows)
@@ -1641,7 +1649,7 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
         da.two = 1;
         if (timer.tile()) *timer.tile() = 16;
         if (timer.ksplit()) *timer.ksplit() = -1;
-        HIP_TRY(ctx, launch_dense_level(EPI_STORE_Z1, da, ctx->d_split, ctx->splitk.n_cu, stream, timer.ev));
+        HIP_TRY(ctx, launch_dense_level(EPI_STORE_Z1, da, ctx->d_split, dense_scratch_bytes(R, D), ctx->splitk.n_cu, stream, timer.ev));
       } else {
         HIP_TRY(ctx, launch_cell_level_pair(EPI_STORE_Z1, a[0], a[1], stream, ctx->splitk, timer.tile(), timer.ksplit(), timer.ev));
       }

@@ -43,8 +43,9 @@ inline size_t dense_scratch_bytes(int32_t n, int32_t K) {
   const size_t rows = ((size_t)n + 15) / 16 * 16;
   return rows * K * sizeof(float) + rows * sizeof(float);
 }
-// Packs the input rows (s.a.src0, gathered by s.a.idx0) into `scratch` and runs the level: two launches.
-hipError_t launch_dense_level(CellEpilogue epi, DenseArgs s, void* scratch, int n_cu, hipStream_t stream,
-                              const LaunchEvents& ev = LaunchEvents());
+// Packs the input rows (s.a.src0, gathered by s.a.idx0) into `scratch` and runs the level: two launches.  A leaf level (its rows
+// and its results are named by lists) runs in pieces, with the same bits, where not all of its rows fit.
+hipError_t launch_dense_level(CellEpilogue epi, const DenseArgs& s, void* scratch, size_t scratch_bytes, int n_cu,
+                              hipStream_t stream, const LaunchEvents& ev = LaunchEvents());
 
 }  // namespace acrobat

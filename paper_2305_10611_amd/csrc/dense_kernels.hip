@@ -17,6 +17,7 @@
 #include "packed_rows.h"
 #include "split_fp16.h"
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -334,7 +335,9 @@ bool dense_level_wins(CellEpilogue epi, int32_t n, int32_t H, int32_t K, const S
   return 2.0 * (epi == EPI_TREE_LEAF ? 3 : 4) * n * H * K >= 1.0e9;
 }
 
-hipError_t launch_dense_level(CellEpilogue epi, DenseArgs s, void* scratch, int n_cu, hipStream_t stream, const LaunchEvents& ev) {
+namespace {
+
+hipError_t launch_rows(CellEpilogue epi, DenseArgs s, void* scratch, int n_cu, hipStream_t stream, const LaunchEvents& ev) {
   PackRowsArgs p{s.a.n, s.a.kseg, s.a.src0, s.a.idx0, scratch, nullptr};
   const unsigned blocks = (unsigned)((p.n + 15) / 16);
   s.operand = scratch;
@@ -355,6 +358,26 @@ hipError_t launch_dense_level(CellEpilogue epi, DenseArgs s, void* scratch, int 
   }
   return epi == EPI_TREE_LEAF ? launch_gates<3, EPI_TREE_LEAF>(s, n_cu, stream, second)
                               : launch_gates<4, EPI_STORE_Z>(s, n_cu, stream, second);
+}
+
+}  // namespace
+
+hipError_t launch_dense_level(CellEpilogue epi, const DenseArgs& s, void* scratch, size_t scratch_bytes, int n_cu,
+                              hipStream_t stream, const LaunchEvents& ev) {
+  const size_t rows = scratch_bytes / dense_scratch_bytes(16, s.a.kseg) * 16;
+  if (rows >= (size_t)s.a.n) return launch_rows(epi, s, scratch, n_cu, stream, ev);
+  if (epi != EPI_TREE_LEAF || rows == 0 || !s.a.idx0 || !s.a.out_rows) return hipErrorInvalidValue;
+  const int pieces = (int)((s.a.n + rows - 1) / rows), piece = (s.a.n + 16 * pieces - 1) / (16 * pieces) * 16;  // alike, whole blocks
+  for (int at = 0; at < s.a.n; at += piece) {
+    DenseArgs p = s;
+    p.a.n = std::min(piece, s.a.n - at);
+    p.a.idx0 += at;
+    p.a.out_rows += at;
+    if (p.places.place) p.places.place += at;
+    const LaunchEvents some{at == 0 ? ev.start : nullptr, at + piece >= s.a.n ? ev.stop : nullptr};
+    if (const hipError_t e = launch_rows(epi, p, scratch, n_cu, stream, some); e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace acrobat

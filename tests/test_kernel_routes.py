@@ -55,3 +55,24 @@ def test_captured_leaves_without_room_for_packed_rows(ctx):
     names = P.kernels_of(lambda: few.update(h=P.run_treelstm(ctx, few)[0]))
     assert any("cell_stationary_kernel<3," in k for k in names), names
     assert np.array_equal(got, few["h"])
+
+
+@pytest.mark.parametrize("n,leaves,H,D", [(700, 6, 512, 512), (2330, 6, 512, 512), (90, 46, 256, 1024), (2, 2100, 512, 256)])
+def test_leaves_without_allocations_have_the_ordinary_bits(ctx, n, leaves, H, D):
+    """4 200 leaves, whose packed rows take 8.6 MB of the fixed array, 13 980, which run in two pieces, 17 MB of rows at D = 1 024,
+    and two trees whose wide levels run on split weights beside them."""
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    w = gen.treelstm_workload(n, leaves, leaves, H, 500, "uniform", seed=n, bias_scale=0.2, D=D)
+    h, c = P.run_treelstm(ctx, w)
+    d = {k: P.dev(w[k]) for k in ("emb", "W_leaf", "b_leaf", "U", "b")}
+    out = [P.nan_filled(*h.shape) for _ in range(2)]
+    names = P.kernels_of(lambda: ctx.check(ctx.acrobat_treelstm_forward_noalloc(
+        w, H, D, 500, d["emb"], d["W_leaf"], d["b_leaf"], d["U"], d["b"], *out, P.stream_handle())))
+    assert ctx.acrobat_device_status() == A.OK
+    assert any("cell_dense_kernel<3," in k for k in names), names
+    assert np.array_equal(out[0].cpu().numpy(), h) and np.array_equal(out[1].cpu().numpy(), c)
+    few = slice(0, (2 * leaves - 1) * min(n, 60))
+    part = dict(w, n_trees=min(n, 60), tree_off=w["tree_off"][:min(n, 60) + 1], **{k: w[k][few] for k in ("left", "right", "token")})
+    oh, oc = oracle.treelstm(part, nthreads=NT)
+    assert rel(h[few], oh) < 1e-6 and rel(c[few], oc) < 1e-6
