@@ -1103,12 +1103,15 @@ struct SeqPlan {
   int32_t groups = 0, variant = 0;
   bool whole = false;  // one launch record for all steps (else one per step)
   size_t n_off = 0, n_idx = 0;  // entries of the offset table; of both lists: rows, offsets
+  int32_t share_blocks = 0;
   size_t operand_bytes = 0;     // of packed states; c states take as much
 };
 
-SeqPlan plan_recurrence(acrobat_ctx* ctx, CellEpilogue epi, int32_t H, int32_t R, int32_t n_live, int32_t n_steps,
+// step_off[t + 1] - step_off[t]: nodes of step t, per direction.
+SeqPlan plan_recurrence(acrobat_ctx* ctx, CellEpilogue epi, int32_t H, int32_t R, int32_t n_steps, const int32_t* step_off,
                         int32_t directions, hipStream_t stream) {
   SeqPlan p;
+  const int32_t n_live = step_off[1];
   if (!ctx->persistent || ctx->splitk.force_bm || H < 128 || n_steps < 2 || (double)R * H * sizeof(float) >= 4294967296.0 - 512.0)
     return p;
   // The kernels of persistent_kernels.hip step faster at H = 128 and, with a single gate, 256 while a batch has at most 256
@@ -1129,10 +1132,10 @@ SeqPlan plan_recurrence(acrobat_ctx* ctx, CellEpilogue epi, int32_t H, int32_t R
   // against 599, H = 192 234 against 248, H = 128 204 against 180; 64 sequences, H = 384 225 against 179).
   if (!p.whole && stream_is_capturing(stream) && !(epi == EPI_RNN_STEP && n_live > 256 && H >= 192)) p.groups = 0;
   if (p.groups == 0) return p;
-  const int64_t entries = (int64_t)directions * R, blocks = share_blocks(entries, (int64_t)n_steps * p.groups);
   p.n_off = (size_t)n_steps * p.groups + 1;
-  p.n_idx = (size_t)entries + p.n_off;
-  p.operand_bytes = (size_t)blocks * 64 * H;
+  p.n_idx = (size_t)directions * R + p.n_off;
+  p.share_blocks = seq_share_blocks(step_off[2] - step_off[1], p.groups / directions);
+  p.operand_bytes = (size_t)2 * p.groups * p.share_blocks * 64 * H;
   // (a captured call that lacks the room does without)
   if ((double)p.operand_bytes > kPackedMaxBytes || !indices_fit(ctx, p.n_idx, stream) ||
       !reserve_packed(ctx, (epi == EPI_LSTM_STEP ? 2 : 1) * p.operand_bytes, stream))
@@ -1148,7 +1151,6 @@ int reserve_recurrence(acrobat_ctx* ctx, const SeqPlan& plan, int32_t directions
 }
 
 // The steps of a recurrence, lists and offset table staged and uploaded (sa.off), in one launch or one per step.
-// step_off[t + 1] - step_off[t]: nodes of step t, per direction.
 int run_recurrence(acrobat_ctx* ctx, CellEpilogue epi, StationaryArgs& sa, const SeqPlan& plan, int32_t n_steps,
                    const int32_t* step_off, int32_t directions, int32_t R, LaunchTimer& timer) {
   const int32_t H = sa.a[0].H;
@@ -1159,6 +1161,7 @@ int run_recurrence(acrobat_ctx* ctx, CellEpilogue epi, StationaryArgs& sa, const
   sa.n_cb = packed_members(epi, H, plan.variant);
   sa.variant = plan.variant;
   sa.n_steps = n_steps;
+  sa.share_blocks = plan.share_blocks;
   sa.n_groups = plan.groups;
   sa.counters = ctx->splitk.counters;
   sa.status = ctx->h_status_dev;
@@ -1409,7 +1412,7 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
     const int32_t n_live = s.level_off[1];  // sequences with at least one step
     {
       const SeqPlan plan = H == 128 && n_live <= kLstmSlots * kLstmMaxBlocks
-                               ? SeqPlan() : plan_recurrence(ctx, EPI_LSTM_STEP, H, R, n_live, s.n_levels, 1, stream);
+                               ? SeqPlan() : plan_recurrence(ctx, EPI_LSTM_STEP, H, R, s.n_levels, s.level_off.data(), 1, stream);
       if (plan.groups > 0) {
         TRY(reserve_recurrence(ctx, plan, 1, R, stream));
         int32_t* st = ctx->h_stage;
@@ -1571,7 +1574,7 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
                             rnn_persistent_eligible(H, 2 * blocks_per_dir, nullptr);
     const size_t n_slots = (size_t)blocks_per_dir * kRnnSlots;
     const bool preferred = H < 512 || 2 * blocks_per_dir * (H / 16) <= ctx->n_cu;  // (figures in plan_recurrence)
-    const SeqPlan plan = may_persist && preferred ? SeqPlan() : plan_recurrence(ctx, EPI_RNN_STEP, H, R, n_live, T, 2, stream);
+    const SeqPlan plan = may_persist && preferred ? SeqPlan() : plan_recurrence(ctx, EPI_RNN_STEP, H, R, T, s.fwd_off.data(), 2, stream);
     const bool persistent = may_persist && plan.groups == 0;
     if (plan.groups > 0) {
       TRY(reserve_recurrence(ctx, plan, 2, R, stream));

@@ -13,14 +13,18 @@
 // Bound: narrow levels and steps by their chain - announcement 0.9, operand 0.6, matrix instructions and sums 0.5, gates and
 // stores 0.5 us -, wide levels by the matrix cores (7 186 rows, H = 512: 102 us, 1.1 PFLOP/s of fp16 products; a large
 // library product reaches 1.3).  Forward calls against the gathering kernel: 8 trees of 20 leaves, H = 256 50 -> 43 us, 64
-// trees 91 -> 84; LSTM, 256 sequences, H = 512 528 -> 470, 75 sequences, H = 320 229 -> 157; BiRNN, 600 sequences, H = 256
+// trees 91 -> 84; LSTM, 256 sequences, H = 512 528 -> 382 (with packed input rows), 75 sequences, H = 320 229 -> 157; BiRNN, 600 sequences, H = 256
 // 214 -> 175.  A recurrence needs no list of places or previous rows: a share's sequences are the first ones of the share
 // before, so the words that a call uploads are as many as its rows.
 //
 // Operand: blocks of 16 rows; a 32-k step of a block is 64 lanes x 16 bytes of hi terms, then the same of lo terms; lane
 // l holds row l % 16, k = 4 (l / 16) + 0 .. 3 and 16 more.  A tree node has its left child's H columns, then its right
-// child's.  cells: [block][side][workgroup of the group][row][unit].  Share (level, group), list positions p0 ..., has the
-// blocks from (p0 - first_position) / 16 + level * groups + group on (rounded down: no two shares meet).
+// child's.  cells: [block][side][workgroup of the group][row][unit].  Share (level, group) of a tree batch, list positions p0
+// ..., has the blocks from (p0 - first_position) / 16 + level * groups + group on (rounded down: no two shares meet).  A
+// recurrence has two sets of blocks and in each a group those of its widest share: step t reads set t & 1 and leaves its states
+// in the other one, which step t - 1 has read - all of a group has announced that step before it starts on t.  (A set for every
+// step was slower where they outgrew the caches, LSTM, 256 sequences of 1 to 100 steps, H = 512 436 against 382 us, and the same
+// elsewhere, 75 of 1 to 60, H = 320 164 and 165; keeping c states of single blocks in registers changed nothing.)
 // Tree levels: the arithmetic of the gathering kernel, in the same order, so the same bits.
 #include "tree_kernels.h"
 
@@ -181,6 +185,9 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
 
   int lv = s.level0, p0, p1;
   unsigned arrived = 0;  // levels this group has announced
+  // recurrences: first block of the set that this step reads, and of the other one
+  unsigned here = (unsigned)((lv & 1) * s.n_groups + group) * (unsigned)s.share_blocks;
+  unsigned there = (unsigned)((~lv & 1) * s.n_groups + group) * (unsigned)s.share_blocks;
   share_of(lv, p0, p1);
   if (p0 >= p1) return;  // (nothing in this level: nothing in a later one)
   if constexpr (!kTree) request_lists(next_out, p0, p1);
@@ -193,10 +200,9 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
     const int n = p1 - p0, nb = (n + 15) >> 4;
     int c0 = 0, c1 = 0;  // the next level's share
     if (lv + 1 < (kTree ? s.level1 : s.n_steps)) share_of(lv + 1, c0, c1);
-    const auto first_block = [&](int p, int l) { return (unsigned)((p - s.first_position) >> 4) + (unsigned)(l * s.n_groups + group); };
-    const unsigned block0 = first_block(p0, lv);
-    // a share's sequences are a prefix of the step before's: row i of a block is read as row i of the same block of the next
-    const unsigned reader0 = first_block(c0, lv + 1);
+    const unsigned block0 = kTree ? (unsigned)((p0 - s.first_position) >> 4) + (unsigned)(lv * s.n_groups + group) : here;
+    // a share's sequences are a prefix of the step before's: row i of a block is read as row i of the same block of the other set
+    const unsigned reader0 = there;
     float p[EPT][2], zx[EPT][kTree ? 1 : G];
     auto take_lists = [&]() {
 #pragma unroll
@@ -434,6 +440,11 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
     p0 = c0;
     p1 = c1;
     ++lv;
+    if constexpr (!kTree) {
+      const unsigned set = here;
+      here = there;
+      there = set;
+    }
     return true;
   };
   bool on = true;

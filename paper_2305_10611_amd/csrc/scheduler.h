@@ -77,6 +77,9 @@ int schedule_seqs(int32_t n_seq, const int32_t* len, SeqSchedule& out, std::stri
 inline int32_t share_block(int32_t p0, int32_t base, int32_t share) { return (p0 - base) / 16 + share; }
 // Blocks that shares numbered below n_shares of n list positions may take up.
 inline int64_t share_blocks(int64_t n, int64_t n_shares) { return n / 16 + n_shares + 1; }
+// Blocks of 16 rows that hold any share of a step behind the first, n_second nodes in the second step of a direction that is
+// dealt out to `lists` lists.
+inline int32_t seq_share_blocks(int32_t n_second, int32_t lists) { return ((n_second + lists - 1) / lists + 15) / 16; }
 
 // Deals sequences out to groups that run their recurrences independently of each other (by descending length, back and
 // forth) and lists every step group by group.  Step t of sequence s writes row seq_off[s] + t and reads the row before it

@@ -76,3 +76,31 @@ def test_leaves_without_allocations_have_the_ordinary_bits(ctx, n, leaves, H, D)
     part = dict(w, n_trees=min(n, 60), tree_off=w["tree_off"][:min(n, 60) + 1], **{k: w[k][few] for k in ("left", "right", "token")})
     oh, oc = oracle.treelstm(part, nthreads=NT)
     assert rel(h[few], oh) < 1e-6 and rel(c[few], oc) < 1e-6
+
+
+@pytest.mark.parametrize("kind,H,lens", [("lstm", 512, [1000] + [1] * 1999), ("lstm", 320, [9000] * 4 + [1] * 252),
+                                         ("lstm", 512, [9000] * 4 + [1] * 252), ("birnn", 512, [4500] * 4 + [2, 1] * 126)])
+def test_few_long_sequences_among_many_short_ones(ctx, kind, H, lens):
+    """One launch, and no more workspace than a batch of that width needs: a step's packed states last until the next step has
+    read them.  Against a launch per step (2e-6, as in test_split_contraction), which needs none."""
+    import torch
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    lens = gen.make_rng(H).permutation(np.asarray(lens, np.int32))
+    w = gen.lstm_workload(4, 1, 2, H, 32, seed=H, bias_scale=0.2) if kind == "lstm" else gen.birnn_workload(4, 1, 2, H, 32, 5, seed=H)
+    R = int(lens.sum())
+    w.update(len=lens, n_seq=len(lens), x=gen.make_rng(H + 1).standard_normal((R, 32), dtype=np.float32))
+    run = P.run_lstm if kind == "lstm" else P.run_birnn
+    ctx.acrobat_set_persistent(False)
+    steps = run(ctx, w)  # (input products, lists and partial tiles have their room now)
+    ctx.acrobat_set_persistent(True)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    got = []
+    names = P.kernels_of(lambda: got.extend(run(ctx, w)))
+    assert ctx.acrobat_device_status() == A.OK
+    taken = free - torch.cuda.mem_get_info()[0]
+    assert sum("cell_packed_kernel" in k for k in names) == 1 and not any("cell_direct" in k or "cell_tiny" in k for k in names), names
+    assert taken < 64 << 20, taken
+    for a, b in zip(got, steps):
+        assert rel(a, b) < 2e-6
