@@ -296,15 +296,13 @@ bool reserve_split(acrobat_ctx* ctx, size_t bytes, hipStream_t stream) {
 bool reserve_packed(acrobat_ctx* ctx, size_t bytes, hipStream_t stream) {
   if (bytes <= ctx->packed_cap) return true;
   if (stream_is_capturing(stream)) return false;
-  if (ctx->d_packed) (void)hipFree(ctx->d_packed);  // waits for kernels still using it
-  ctx->d_packed = nullptr;
-  ctx->packed_cap = 0;
   const size_t cap = bytes + bytes / 4;  // (batches of one kind differ by a few nodes)
   void* p = nullptr;
   if (hipMalloc(&p, cap) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
+  if (ctx->d_packed) (void)hipFree(ctx->d_packed);  // waits for kernels still using it
   ctx->d_packed = static_cast<unsigned char*>(p);
   ctx->packed_cap = cap;
   return true;
@@ -838,7 +836,11 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     const int64_t blocks = one_launch && gpu_bound && (plan.leaf || plan.dense_leaf) && n_off > 0 && s.n_levels - plan.first > 1
                                ? share_blocks((int64_t)N - s.level_off[plan.first], (int64_t)s.n_levels * plan.groups) : 0;
     const size_t operand_bytes = (size_t)blocks * 128 * H;
-    bool packed = blocks > 0 && (double)blocks * 128 * H <= kPackedMaxBytes &&
+    // (Blocks of a group's narrow levels are mostly empty, and a share may have one more than it fills: one tree of thousands of
+    // levels among small ones takes over 100 times the bytes of its states.  The room stays with the context, so from 256 MiB
+    // on it may be four times the bytes of all states at most; batches of 64 to 1 024 sentences take 1.2 to 3.3 times.)
+    const double packed_most = std::max(268435456.0, 4.0 * 8.0 * N * H);
+    bool packed = blocks > 0 && (double)operand_bytes <= kPackedMaxBytes && 2.0 * operand_bytes <= packed_most &&
                   (!noalloc || (4 * (size_t)N + n_off) * sizeof(int32_t) <= kStaticIndexBytes);
     packed = packed && (noalloc || reserve_packed(ctx, 2 * operand_bytes, stream));
     // (Uploading the leaf lists and launching level 0 before the internal levels are sorted was measured and

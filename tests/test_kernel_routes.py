@@ -104,3 +104,31 @@ def test_few_long_sequences_among_many_short_ones(ctx, kind, H, lens):
     assert taken < 64 << 20, taken
     for a, b in zip(got, steps):
         assert rel(a, b) < 2e-6
+
+
+def test_one_deep_tree_among_small_ones(ctx):
+    """A chain of 3 000 levels beside 255 trees of two leaves: packed operands would take 4 GB for states of 28 MB."""
+    import torch
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    H, deep, few = 512, 3000, 255
+    w = gen.treelstm_workload(few + 1, 2, 2, H, 60, "uniform", seed=4, bias_scale=0.2, D=64)
+    rng = gen.make_rng(6)
+    chain = np.arange(deep, dtype=np.int32)  # node deep + 1 + i has node deep + i (node 0: a leaf) and leaf i + 1 as children
+    left = np.concatenate([np.full(deep + 1, -1, np.int32), [0], deep + 1 + chain[:-1]]).astype(np.int32)
+    right = np.concatenate([np.full(deep + 1, -1, np.int32), 1 + chain]).astype(np.int32)
+    token = np.where(left < 0, rng.integers(0, 60, 2 * deep + 1), -1).astype(np.int32)
+    w = dict(w, tree_off=np.concatenate([w["tree_off"][:-1], [3 * few + 2 * deep + 1]]).astype(np.int32),
+             **{k: np.concatenate([w[k][:3 * few], v]) for k, v in (("left", left), ("right", right), ("token", token))})
+    ctx.acrobat_set_persistent(False)
+    P.run_treelstm(ctx, w)  # (lists and partial tiles have their room now)
+    ctx.acrobat_set_persistent(True)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    got = []
+    names = P.kernels_of(lambda: got.extend(P.run_treelstm(ctx, w)))
+    assert ctx.acrobat_device_status() == A.OK
+    assert free - torch.cuda.mem_get_info()[0] < 384 << 20
+    assert any("cell_stationary_kernel<5," in k for k in names) and not any("cell_packed" in k for k in names), names
+    want = oracle.treelstm(w, nthreads=NT)
+    assert rel(got[0], want[0]) < 1e-6 and rel(got[1], want[1]) < 1e-6
