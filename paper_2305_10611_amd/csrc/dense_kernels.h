@@ -18,12 +18,13 @@ struct TreePlaces {
 constexpr int32_t kDenseMaxK = 1024;
 constexpr double kDenseMaxBytes = 4294967296.0 - 131072.0;
 
-// Input rows as matrix operands: blocks of 16 rows, 64 K bytes each, and every row's inverse scale.
+// Input rows as matrix operands: blocks of 16 rows, 64 K bytes each, every row's inverse scale and the largest of a block.
 struct PackRowsArgs {
   int32_t n, K;
   const float* src; const int32_t* idx;  // row of src by position, null: the position itself
   void* operand;   // [ceil(n / 16)] blocks
   float* inverse;  // [16 ceil(n / 16)]
+  float* largest;  // [ceil(n / 16)]
 };
 
 // One level: TREE_LEAF, STORE_Z or STORE_Z1 with one segment of at most kDenseMaxK columns, H a multiple of 32; `two`: odd
@@ -33,15 +34,16 @@ struct DenseArgs {
   int32_t two;
   const void* operand; uint32_t operand_bytes;
   float* inverse;
+  const float* largest;
   TreePlaces places;
   int32_t n_cb, n_groups;  // set by the launcher
 };
 // Whether a level (G gates of H units over K columns) is wide enough for this kernel to win; a forced tile switches it off.
 bool dense_level_wins(CellEpilogue epi, int32_t n, int32_t H, int32_t K, const SplitKWorkspace& ws);
-// Scratch of a level: packed rows, then their inverse scales.
+// Scratch of a level: packed rows, then their inverse scales, then the largest ones.
 inline size_t dense_scratch_bytes(int32_t n, int32_t K) {
-  const size_t rows = ((size_t)n + 15) / 16 * 16;
-  return rows * K * sizeof(float) + rows * sizeof(float);
+  const size_t blocks = ((size_t)n + 15) / 16;
+  return blocks * (16 * (size_t)K + 17) * sizeof(float);
 }
 // Packs the input rows (s.a.src0, gathered by s.a.idx0) into `scratch` and runs the level: two launches.  A leaf level (its rows
 // and its results are named by lists) runs in pieces, with the same bits, where not all of its rows fit.

@@ -62,6 +62,12 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const PackRowsArgs p) {
     sc[h] = scale_for(fmaxf(fmaxf(s_max[0][r], s_max[1][r]), fmaxf(s_max[2][r], s_max[3][r])));
     if (w == 0 && (lane & 7) == 0) p.inverse[16 * block + r] = inverse_power(sc[h]);
   }
+  if (w == 0) {
+    float m = inverse_power(fminf(sc[0], sc[1]));
+#pragma unroll
+    for (int d = 8; d < 64; d *= 2) m = fmaxf(m, __shfl_xor(m, d));
+    if (lane == 0) p.largest[block] = m;
+  }
   unsigned char* const dst = static_cast<unsigned char*>(p.operand) + (size_t)block * (64u * p.K) + 16 * lane;
 #pragma unroll
   for (int t = 0; t < NS; ++t) {
@@ -169,11 +175,56 @@ __global__ __launch_bounds__(512, 2) void cell_dense_kernel(const DenseArgs s) {
   };
   auto block_at = [&](int b) { return b < b1 ? (unsigned)b * block_bytes : kNowhere - 2048u * KS * NS; };
   __syncthreads();
+  // Rows whose inverse scale is above `limit` (both are positive: compared as integers) are not to be split against some column
+  // of this workgroup.  It does not depend on the other rows of a block, so neither do a row's bits.
+  int limit;
+  {
+    float m = 0.0f;
+#pragma unroll
+    for (int i = lane; i < 16 * NW; i += 64) {
+      const floatx4 u = *reinterpret_cast<const floatx4*>(s_winv[i >> 4][i & 15]);
+#pragma unroll
+      for (int g = 0; g < G; ++g) m = fmaxf(m, u[g]);
+    }
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) m = fmaxf(m, __shfl_xor(m, d));
+    limit = __builtin_amdgcn_readfirstlane(__float_as_int(kLargestUnit / m));
+  }
+  const __attribute__((address_space(4))) int* const largest_of = (const __attribute__((address_space(4))) int*)s.largest;
 #pragma unroll
   for (int t = 0; t < NS; ++t) {
     request(block_at(b0), t);
     hold_order();
   }
+  // This wavefront's partial sums of the rows of a block that are not to be split, on the fp32 matrix cores.  Bound: the weights
+  // that every block fetches again (unscaled features of 1e5, BiRNN, H = D = 512, 300 sequences: 292 us a call on fp32 tiles, 279
+  // with these, 1 815 with a scalar product per element; LSTM, 13 402 rows 870 against 7 785 with scalar products).
+  auto multiply_plain = [&](int b, floatx4 (&sums)[G]) {
+    int i = 16 * b + li;
+    i = i < a.n ? i : a.n - 1;
+    const float* const x = a.src0 + (size_t)(a.idx0 ? a.idx0[i] : i) * (size_t)a.ld0 + 4 * kq;
+    floatx4 acc[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) acc[g] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (int half = 2 * ks; half < 2 * T; half = half & 1 ? half + 2 * KS - 1 : half + 1) {  // 16 k at a time
+      const floatx4 xk = *reinterpret_cast<const floatx4*>(x + 16 * half);
+      floatx4 wk[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+        wk[g] = *reinterpret_cast<const floatx4*>(a.W + (size_t)(tile_row(g, ch) + li) * (size_t)a.ldw + 4 * kq + 16 * half);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(xk[e], wk[g][e], acc[g], 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const bool plain = __float_as_int(at_byte(inverse, 4u * (unsigned)(16 * b + 4 * kq + v))) > limit;
+#pragma unroll
+      for (int g = 0; g < G; ++g) sums[g][v] = plain ? acc[g][v] : sums[g][v];
+    }
+  };
   int parity = 0;
   for (int b = b0; b < b1; b += RB, parity ^= 1) {
     int i = 16 * (b + my_rb) + er;
@@ -204,12 +255,15 @@ __global__ __launch_bounds__(512, 2) void cell_dense_kernel(const DenseArgs s) {
         hold_order();
       }
       const floatx4 unit = *reinterpret_cast<const floatx4*>(s_winv[w][li]);
+#pragma unroll
+      for (int g = 0; g < G; ++g) acc[g] *= unit[g];
+      if (__builtin_expect(b + r < b1 && largest_of[b + r] > limit, 0)) multiply_plain(b + r, acc);
       float* const z = zc + (r * NW + w) * ZQ;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         floatx4 part = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int g = 0; g < G; ++g) part[g] = acc[g][v] * unit[g];
+        for (int g = 0; g < G; ++g) part[g] = acc[g][v];
         *reinterpret_cast<floatx4*>(z + ((4 * kq + v) * 16 + li) * 4) = part;
       }
     }
@@ -224,23 +278,14 @@ __global__ __launch_bounds__(512, 2) void cell_dense_kernel(const DenseArgs s) {
       for (int g = 0; g < G; ++g) sum[g] += part[g];
     }
     if (!live) continue;
-    // scales out again; what is not finite, or not to be split (the slices' weight scales differ: the largest counts), is
-    // computed in fp32
+    // scales out again (of what was split); what is not finite is computed in fp32, term by term
+    const float scale = __float_as_int(rinv) > limit ? 1.0f : rinv;
     float zs[G];
     bool bad = false;
-    {
-      floatx4 unit = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int q = 0; q < KS; ++q) {
-        const floatx4 u = *reinterpret_cast<const floatx4*>(s_winv[my_ch * KS + q][eu]);
-#pragma unroll
-        for (int g = 0; g < G; ++g) unit[g] = fmaxf(unit[g], u[g]);
-      }
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        zs[g] = sum[g] * rinv;
-        bad |= !__builtin_isfinite(zs[g]) || unit[g] * rinv > kLargestUnit;
-      }
+    for (int g = 0; g < G; ++g) {
+      zs[g] = sum[g] * scale;
+      bad |= !__builtin_isfinite(zs[g]);
     }
     if (__builtin_expect(bad, 0)) {
       const float* const x = a.src0 + (size_t)(a.idx0 ? a.idx0[i] : i) * (size_t)a.ld0;
@@ -338,11 +383,12 @@ bool dense_level_wins(CellEpilogue epi, int32_t n, int32_t H, int32_t K, const S
 namespace {
 
 hipError_t launch_rows(CellEpilogue epi, DenseArgs s, void* scratch, int n_cu, hipStream_t stream, const LaunchEvents& ev) {
-  PackRowsArgs p{s.a.n, s.a.kseg, s.a.src0, s.a.idx0, scratch, nullptr};
+  PackRowsArgs p{s.a.n, s.a.kseg, s.a.src0, s.a.idx0, scratch, nullptr, nullptr};
   const unsigned blocks = (unsigned)((p.n + 15) / 16);
   s.operand = scratch;
   s.operand_bytes = 64u * (unsigned)p.K * blocks;
   p.inverse = s.inverse = reinterpret_cast<float*>(static_cast<unsigned char*>(scratch) + (size_t)s.operand_bytes);
+  s.largest = p.largest = p.inverse + (size_t)16 * blocks;
   if (p.K <= 128) launch_with_events((pack_rows_kernel<1>), dim3(blocks), dim3(256), 0, stream, ev.start, hipEvent_t(nullptr), p);
   else if (p.K <= 256) launch_with_events((pack_rows_kernel<2>), dim3(blocks), dim3(256), 0, stream, ev.start, hipEvent_t(nullptr), p);
   else if (p.K <= 512) launch_with_events((pack_rows_kernel<4>), dim3(blocks), dim3(256), 0, stream, ev.start, hipEvent_t(nullptr), p);

@@ -100,6 +100,62 @@ def test_rows_that_are_not_to_be_split(ctx):
     assert np.isnan(h[np.flatnonzero((w["token"] == 6) & (w["left"] < 0))]).all()
 
 
+@pytest.mark.parametrize("kind,H,D,n", [("tree", 512, 512, 1270), ("tree", 256, 992, 1000), ("lstm", 512, 224, 620),
+                                        ("lstm", 320, 736, 285), ("birnn", 512, 288, 1273), ("birnn", 320, 992, 597)])
+def test_some_rows_that_are_not_to_be_split(ctx, kind, H, D, n):
+    """A feature of 1e9 with a weight of 1e-9 in every third row, not in the others: what fp32 says for all of them."""
+    from tests import parity as P
+    if kind == "tree":
+        w = gen.treelstm_workload(n, 1, 2, H, 50, "uniform", seed=H + D, bias_scale=0.2, D=D)
+        x, weights, run, want = "emb", ["W_leaf"], P.run_treelstm, oracle.treelstm
+    elif kind == "lstm":
+        w = gen.lstm_workload(n, 2, 2, H, D, seed=H + D, bias_scale=0.2)
+        x, weights, run, want = "x", ["Wx"], P.run_lstm, oracle.varlen_lstm
+    else:
+        w = gen.birnn_workload(n, 2, 2, H, D, 5, seed=H + D)
+        x, weights, run, want = "x", ["fWx", "bWx"], P.run_birnn, oracle.birnn
+    w[x][::3, 3] *= 1e9
+    for k in weights:
+        w[k][:, 3] *= 1e-9
+    got = takes_it(ctx, lambda: run(ctx, w), {"tree": "K_TREE_LEAF", "lstm": "K_LSTM_INPUT", "birnn": "K_RNN_INPUT"}[kind])
+    for a, b in zip(got, want(w, nthreads=NT)):
+        assert rel(a, b) < 1e-6
+
+
+@pytest.mark.parametrize("kind", ["tree", "lstm", "birnn"])
+def test_unscaled_features_cost_a_few_times_the_product(ctx, kind):
+    """Features of 1e5: no row is to be split, and all products run on the fp32 matrix cores.  A scalar product per element made
+    the launches 44 to 59 times as long as with features of order one (2.6, 3.5 and 1.7 ms); now it is 4 to 5 (0.25, 0.29, 0.16)."""
+    from tests import parity as P
+    import paper_2305_10611_amd as A
+    H, n = 512, 1500
+    ms = []
+    for scale in (1.0, 1e5):
+        if kind == "tree":
+            w = gen.treelstm_workload(n, 4, 4, H, 500, "uniform", seed=1, D=H)
+            w["emb"] *= scale
+            run, record = P.run_treelstm, A.binding.K_TREE_LEAF
+        elif kind == "lstm":
+            w = gen.lstm_workload(n, 4, 4, H, H, seed=1)
+            w["x"] *= scale
+            run, record = P.run_lstm, A.binding.K_LSTM_INPUT
+        else:
+            w = gen.birnn_workload(n, 4, 4, H, H, 5, seed=1)
+            w["x"] *= scale
+            run, record = P.run_birnn, A.binding.K_RNN_INPUT
+        run(ctx, w)
+        ctx.acrobat_set_profiling(True)
+        try:
+            times = []
+            for _ in range(5):
+                run(ctx, w)
+                times += [r[3] for r in ctx.acrobat_last_profile() if r[0] == record]
+        finally:
+            ctx.acrobat_set_profiling(False)
+        ms.append(min(times))
+    assert ms[1] < 15 * ms[0]
+
+
 def test_without_allocations(ctx):
     import paper_2305_10611_amd as A
     from tests import parity as P

@@ -57,13 +57,18 @@ def test_captured_leaves_without_room_for_packed_rows(ctx):
     assert np.array_equal(got, few["h"])
 
 
-@pytest.mark.parametrize("n,leaves,H,D", [(700, 6, 512, 512), (2330, 6, 512, 512), (90, 46, 256, 1024), (2, 2100, 512, 256)])
-def test_leaves_without_allocations_have_the_ordinary_bits(ctx, n, leaves, H, D):
+@pytest.mark.parametrize("n,leaves,H,D,mixed", [(700, 6, 512, 512, False), (2330, 6, 512, 512, False), (90, 46, 256, 1024, False),
+                                                (2, 2100, 512, 256, False), (700, 6, 512, 512, True)])
+def test_leaves_without_allocations_have_the_ordinary_bits(ctx, n, leaves, H, D, mixed):
     """4 200 leaves, whose packed rows take 8.6 MB of the fixed array, 13 980, which run in two pieces, 17 MB of rows at D = 1 024,
-    and two trees whose wide levels run on split weights beside them."""
+    and two trees whose wide levels run on split weights beside them.  mixed: a third of the rows are not to be split, and the
+    calls list the leaves in different orders."""
     import paper_2305_10611_amd as A
     from tests import parity as P
     w = gen.treelstm_workload(n, leaves, leaves, H, 500, "uniform", seed=n, bias_scale=0.2, D=D)
+    if mixed:
+        w["emb"][::3, 3] *= 1e9
+        w["W_leaf"][:, 3] *= 1e-9
     h, c = P.run_treelstm(ctx, w)
     d = {k: P.dev(w[k]) for k in ("emb", "W_leaf", "b_leaf", "U", "b")}
     out = [P.nan_filled(*h.shape) for _ in range(2)]
