@@ -827,8 +827,10 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     // One launch of several levels takes its operands packed, given the room: blocks of 16 nodes, 8 H bytes of split states
     // and as much of c states for each.  (A leaf level on other tiles knows nothing of places: for 36 000 leaves at H = 512 a
     // launch that takes their states there costs 95 us, which is all that the levels save.)
-    // Finding the places costs the host 1 to 2 ns a node.  Calls that wait for the host anyway do without: it needs about 26 us
-    // and, places included, 5.5 ns a node, the GPU without them 20 us, 2.5 a level and its fp16 products at 0.5 PFLOP/s (1 000
+    // Finding the places costs the host 1.3 to 1.5 ns a node, which a call with nothing queued ahead of it pays in full (1 024 trees
+    // that change from call to call, H = 512: alone 1 255 us with places and 1 258 without, queued 897 and 983; 256 trees 356 and
+    // 382, 271 and 321).  Calls that wait for the host anyway do without: it needs about 26 us and, places included, 5.5 ns a
+    // node, the GPU without them 20 us, 2.5 a level and its fp16 products at 0.5 PFLOP/s (1 000
     // trees of 2 or 3 leaves, H = 64 40 us without and 47 with places, 3 000, H = 256 99 and 106, but H = 512 197 and 172; 64
     // trees of 5 to 45 leaves, H = 64 60 and 56, H = 256 86 and 76).
     const double gpu_us = 20.0 + 2.5 * (s.n_levels - 1) + 3.0 * (20.0 * (N - n_leaf) * H + 6.0 * n_leaf * D) * H / 0.5e9;

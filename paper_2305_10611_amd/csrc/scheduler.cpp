@@ -280,11 +280,15 @@ void TreeGrouping::places(const TreeSchedule& s, const std::vector<int32_t>& lea
                           int32_t* out, int32_t* left, const int32_t* right, const int32_t* off, int32_t* place) {
   const int32_t n_leaf = s.level_off[1], p_first = s.level_off[first];
   position_.resize((size_t)s.n_nodes);
-  for (int32_t p = 0; p < n_leaf; ++p) position_[s.level_nodes[p]] = p;
-  for (int32_t p = n_leaf; p < p_first; ++p) {
-    position_[out[p]] = p;
-    place[p] = -1;
-  }
+  int32_t* const position = position_.data();
+  const int32_t* const tokens = leaf_tokens.data();
+  for (int32_t p = 0; p < n_leaf; ++p) position[s.level_nodes[p]] = p;
+  for (int32_t p = n_leaf; p < p_first; ++p) position[out[p]] = p;
+  std::fill(place + n_leaf, place + s.n_nodes, -1);
+  // Every child is written down behind the leaves listed so far and counts if it is one: which children are leaves is as good as
+  // random, and a branch on it would cost more than all else here.  (Entry n_leaf is overwritten once all leaves are listed:
+  // that is after the block which reads it.)
+  const int32_t out_behind = n_leaf < s.n_nodes ? out[n_leaf] : 0, left_behind = n_leaf < s.n_nodes ? left[n_leaf] : 0;
   int32_t k = 0;  // leaves listed
   for (int32_t lv = first; lv < s.n_levels; ++lv)
     for (int32_t g = 0; g < groups; ++g) {
@@ -292,28 +296,29 @@ void TreeGrouping::places(const TreeSchedule& s, const std::vector<int32_t>& lea
       const int32_t at = 32 * share_block(p0, p_first, share);
       for (int32_t b = p0; b < p1; b += 16) {
         const int32_t end = std::min(b + 16, p1);
-        for (int32_t side = 0; side < 2; ++side)
+        for (int32_t side = 0; side < 2; ++side) {
+          const int32_t* const children = side ? right : left;
           for (int32_t p = b; p < end; ++p) {  // (children come at earlier levels)
-            const int32_t child = side ? right[p] : left[p], from = position_[child], to = at + 2 * (p - p0) + side;
-            if (from < n_leaf) {
-              out[k] = child;
-              left[k] = leaf_tokens[from];
-              place[k++] = to;
-              position_[child] = -1;
-            } else {
-              place[from] = to;
-            }
+            const int32_t child = children[p], from = position[child], to = at + 2 * (p - p0) + side;
+            const bool leaf = from < n_leaf;
+            position[child] = -1;
+            out[k] = child;
+            left[k] = tokens[leaf ? from : 0];
+            place[leaf ? k : from] = to;
+            k += leaf;
           }
-        for (int32_t p = b; p < end; ++p) {
-          position_[out[p]] = p;
-          place[p] = -1;
         }
+        for (int32_t p = b; p < end; ++p) position[out[p]] = p;
       }
     }
+  if (n_leaf < s.n_nodes) {
+    out[n_leaf] = out_behind;
+    left[n_leaf] = left_behind;
+  }
   for (int32_t p = 0; k < n_leaf && p < n_leaf; ++p)
-    if (position_[s.level_nodes[p]] >= 0) {
+    if (position[s.level_nodes[p]] >= 0) {
       out[k] = s.level_nodes[p];
-      left[k] = leaf_tokens[p];
+      left[k] = tokens[p];
       place[k++] = -1;
     }
 }
