@@ -301,7 +301,6 @@ void TreeGrouping::places(const TreeSchedule& s, const std::vector<int32_t>& lea
           for (int32_t p = b; p < end; ++p) {  // (children come at earlier levels)
             const int32_t child = children[p], from = position[child], to = at + 2 * (p - p0) + side;
             const bool leaf = from < n_leaf;
-            position[child] = -1;
             out[k] = child;
             left[k] = tokens[leaf ? from : 0];
             place[leaf ? k : from] = to;
@@ -315,6 +314,8 @@ void TreeGrouping::places(const TreeSchedule& s, const std::vector<int32_t>& lea
     out[n_leaf] = out_behind;
     left[n_leaf] = left_behind;
   }
+  if (k == n_leaf) return;  // (else some have no place: of one-leaf trees, and below level `first`)
+  for (int32_t p = 0; p < k; ++p) position[out[p]] = -1;
   for (int32_t p = 0; k < n_leaf && p < n_leaf; ++p)
     if (position[s.level_nodes[p]] >= 0) {
       out[k] = s.level_nodes[p];

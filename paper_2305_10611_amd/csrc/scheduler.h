@@ -58,7 +58,7 @@ class TreeGrouping {
               int32_t* left, const int32_t* right, const int32_t* off, int32_t* place);
 
  private:
-  std::vector<int32_t> position_;  // of every node: of a leaf in level_nodes (-1 once listed), of others in the lists
+  std::vector<int32_t> position_;  // of every node: of a leaf in level_nodes, of others in the lists
   std::vector<int32_t> order_, count_;
   std::vector<uint8_t> group_;  // of every node (at most 256 groups)
 };
