@@ -122,6 +122,26 @@ def test_some_rows_that_are_not_to_be_split(ctx, kind, H, D, n):
         assert rel(a, b) < 1e-6
 
 
+@pytest.mark.parametrize("kind,H,D,n", [("birnn", 256, 512, 1433), ("birnn", 512, 736, 499), ("birnn", 512, 32, 200),
+                                        ("lstm", 320, 736, 285), ("lstm", 256, 992, 263), ("lstm", 256, 32, 200)])
+def test_no_less_exact_than_fp32(ctx, kind, H, D, n):
+    """Input products and (D = 32) steps that were fp32 before they were split: no further from 64 bits than the fp32 tiles
+    (measured: 0.50 to 1.0 of their error)."""
+    from tests import parity as P
+    if kind == "lstm":
+        w, run, want = gen.lstm_workload(n, 2, 9, H, D, seed=H + D, bias_scale=0.2), P.run_lstm, oracle.varlen_lstm
+    else:
+        w, run, want = gen.birnn_workload(n, 2, 9, H, D, 5, seed=H + D), P.run_birnn, oracle.birnn
+    got = run(ctx, w)
+    ctx.check(ctx.acrobat_set_tuning(64, 1, 0))
+    try:
+        plain = run(ctx, w)
+    finally:
+        ctx.check(ctx.acrobat_set_tuning(0, 0, 0))
+    for a, b, r in zip(got, plain, want(w, nthreads=NT)):
+        assert rel(a, r) <= 1.02 * rel(b, r)
+
+
 @pytest.mark.parametrize("kind", ["tree", "lstm", "birnn"])
 def test_unscaled_features_cost_a_few_times_the_product(ctx, kind):
     """Features of 1e5: no row is to be split, and all products run on the fp32 matrix cores.  A scalar product per element made

@@ -137,3 +137,76 @@ def test_one_deep_tree_among_small_ones(ctx):
     assert any("cell_stationary_kernel<5," in k for k in names) and not any("cell_packed" in k for k in names), names
     want = oracle.treelstm(w, nthreads=NT)
     assert rel(got[0], want[0]) < 1e-6 and rel(got[1], want[1]) < 1e-6
+
+
+@pytest.mark.parametrize("kind,H,n,kernel", [("birnn", 512, 70, "cell_packed_kernel"), ("birnn", 512, 256, "cell_packed_kernel"),
+                                             ("birnn", 512, 64, "rnn_persistent_kernel"), ("lstm", 256, 40, "cell_packed_kernel"),
+                                             ("lstm", 128, 40, "lstm_persistent_kernel")])
+def test_captured_recurrences_of_one_launch(ctx, kind, H, n, kernel):
+    """The eager call's kernel and its bits, replay after replay, with other work of the program in between."""
+    import torch
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    w = (gen.lstm_workload(n, 1, 9, H, 32, seed=3, bias_scale=0.2) if kind == "lstm" else gen.birnn_workload(n, 1, 9, H, 32, 5, seed=3))
+    ref = []
+    names = P.kernels_of(lambda: ref.append((P.run_lstm if kind == "lstm" else P.run_birnn)(ctx, w)))
+    assert any(kernel in k for k in names), names
+    g, out, keep = captured(ctx, w, kind)
+    other = torch.zeros(1 << 20, device="cuda")
+    for _ in range(3):
+        for o in out:
+            o.fill_(float("nan"))
+        other.add_(1.0)
+        g.replay()
+        torch.cuda.synchronize()
+        for o, r in zip(out, ref[-1]):
+            assert np.array_equal(o.cpu().numpy(), r)
+    assert ctx.acrobat_device_status() == A.OK
+
+
+def test_captured_lstm_without_room_for_packed_states(ctx):
+    """H = 256: the older kernel, which needs none, takes the call in one launch (recorded once more without polls, it gives up
+    and says so)."""
+    import torch
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    w = gen.lstm_workload(40, 1, 9, 256, 32, seed=3, bias_scale=0.2)
+    ctx.acrobat_set_persistent(False)
+    P.run_lstm(ctx, w)  # (a launch per step)
+    want = oracle.varlen_lstm(w, nthreads=NT)
+    ctx.acrobat_set_persistent(True)
+    g, out, keep = captured(ctx, w, "lstm")
+    for _ in range(3):
+        for o in out:
+            o.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        for o, r in zip(out, want):
+            assert rel(o.cpu().numpy(), r) < 1e-6
+    assert ctx.acrobat_device_status() == A.OK
+    ctx.acrobat_set_persistent(True, 0)
+    g, out, keep = captured(ctx, w, "lstm")
+    g.replay()
+    torch.cuda.synchronize()
+    assert ctx.acrobat_device_status() == A.ETIMEOUT
+
+
+def captured(ctx, w, kind):
+    """A call recorded into a graph -> the graph, its outputs, what it reads."""
+    import torch
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    R, H, D = int(np.sum(w["len"])), int(w["H"]), int(w["D"])
+    st, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    names = ("x", "Wx", "Wh", "b") if kind == "lstm" else ("x", "fWx", "fWh", "fb", "finit", "bWx", "bWh", "bb", "binit", "C", "cb")
+    t = {k: P.dev(np.asarray(w[k], np.float32)) for k in names}
+    out = [P.nan_filled(R, H), P.nan_filled(R, H)] + ([] if kind == "lstm" else [P.nan_filled(R, int(w["n_out"]))])
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=st, capture_error_mode="relaxed"):
+        if kind == "lstm":
+            rc = ctx.acrobat_varlen_lstm_forward(w["len"], H, D, t["x"], t["Wx"], t["Wh"], t["b"], *out, st.cuda_stream)
+        else:
+            rc = ctx.acrobat_birnn_forward(w["len"], H, D, int(w["n_out"]), t["x"], tuple(t["f" + k] for k in ("Wx", "Wh", "b", "init")),
+                                           tuple(t["b" + k] for k in ("Wx", "Wh", "b", "init")), t["C"], t["cb"], *out, st.cuda_stream)
+    assert rc == A.OK, ctx.acrobat_last_error()
+    return g, out, t
