@@ -1420,7 +1420,7 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
       if (plan.groups > 0) {
         TRY(reserve_recurrence(ctx, plan, 1, R, stream));
         int32_t* st = ctx->h_stage;
-        stage_seq_groups(n_seq, len, s.n_levels, plan.groups, 1, st, nullptr, st + R);
+        stage_seq_groups(n_seq, len, s.n_levels, plan.groups, 1, st, st + R);
         TRY(upload_indices(ctx, plan.n_idx, stream));
         LaunchTimer timer{ctx, stream};
         TRY(input_transform(timer));
@@ -1583,7 +1583,7 @@ int acrobat_birnn_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* len, i
     if (plan.groups > 0) {
       TRY(reserve_recurrence(ctx, plan, 2, R, stream));
       int32_t* st = ctx->h_stage;
-      stage_seq_groups(n_seq, len, T, plan.groups, 2, st, nullptr, st + 2 * (size_t)R);
+      stage_seq_groups(n_seq, len, T, plan.groups, 2, st, st + 2 * (size_t)R);
       TRY(upload_indices(ctx, plan.n_idx, stream));
     } else if (persistent) {
       // (at least what a launch per step needs, so that a smaller call with other sizes can be captured afterwards)

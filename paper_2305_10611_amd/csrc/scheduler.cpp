@@ -325,7 +325,7 @@ void TreeGrouping::places(const TreeSchedule& s, const std::vector<int32_t>& lea
 }
 
 void stage_seq_groups(int32_t n_seq, const int32_t* len, int32_t n_steps, int32_t groups, int32_t directions, int32_t* out,
-                      int32_t* prev, int32_t* off) {
+                      int32_t* off) {
   // ranks by descending length (counting sort), dealt out to groups / directions lists
   const int32_t lists = groups / directions;
   std::vector<int32_t> first((size_t)n_steps + 2, 0), row0;
@@ -353,11 +353,7 @@ void stage_seq_groups(int32_t n_seq, const int32_t* len, int32_t n_steps, int32_
       const bool backward = directions == 2 && (g & 1);
       if (!(directions == 2 && backward))
         while (!m.empty() && len[m.back()] <= t) m.pop_back();
-      for (const int32_t q : m) {
-        out[p] = backward ? row0[q] + len[q] - 1 - t : row0[q] + t;
-        if (prev) prev[p] = t == 0 ? 0 : backward ? out[p] + 1 : out[p] - 1;
-        ++p;
-      }
+      for (const int32_t q : m) out[p++] = backward ? row0[q] + len[q] - 1 - t : row0[q] + t;
     }
   off[(size_t)n_steps * groups] = p;
 }

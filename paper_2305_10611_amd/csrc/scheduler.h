@@ -84,11 +84,11 @@ inline int32_t seq_share_blocks(int32_t n_second, int32_t lists) { return ((n_se
 // Deals sequences out to groups that run their recurrences independently of each other (by descending length, back and
 // forth) and lists every step group by group.  Step t of sequence s writes row seq_off[s] + t and reads the row before it
 // (directions == 2: odd groups list the backward direction, which starts at the last row and reads the row behind).
-// out / prev (or null): directions * (sum len) entries; prev of step 0 is 0 (the initial state's row).
+// out: directions * (sum len) entries.
 // off[t * groups + g]: first position of group g's share of step t, off[n_steps * groups] the end.
 // A group's share of a step lists the first sequences of its share of the step before, in the same order.
 void stage_seq_groups(int32_t n_seq, const int32_t* len, int32_t n_steps, int32_t groups, int32_t directions, int32_t* out,
-                      int32_t* prev, int32_t* off);
+                      int32_t* off);
 
 // Bidirectional RNN with an output phase: levels 0 .. max len - 1 hold step k of both directions
 // (codes: forward row, then R + backward row), the last level holds every output operator (2R + row).

@@ -21,7 +21,7 @@ struct StationaryArgs {
   CellLevelArgs a[2];
   int32_t two;             // != 0: odd groups work with a[1] (the two directions of a bidirectional recurrence)
   uint32_t src_bytes;      // of src0, at most 2^32 - 512
-  int32_t n_cb;            // workgroups of a group, H / 16
+  int32_t n_cb;            // workgroups of a group: H / 16, of packed recurrences packed_members
   int32_t n_groups;
   // off[lv * n_groups + g]: first list position of group g's share of level lv; levels follow one another, so the entry
   // behind it is the end of the share.  null: one level of a.n rows, shared evenly.
@@ -52,8 +52,9 @@ constexpr int32_t kPartsMaxRows = 64;
 hipError_t launch_tree_level(const StationaryArgs& s, int32_t p_first, int32_t n, const SplitKWorkspace& ws, hipStream_t stream,
                              const LaunchEvents& ev = LaunchEvents());
 
-// The same for the kernel whose operands arrive packed (packed_kernels.hip): levels [level0, level1) of trees, or steps of a
-// recurrence, always with an offset table; bit for bit the results of the gathering kernel.
+// The same for the kernel whose operands arrive packed (packed_kernels.hip): levels [level0, level1) of trees, bit for bit the
+// results of the gathering kernel, or steps of a recurrence; always with an offset table.  Instances for recurrences cut the
+// contraction into different numbers of slices, so the last bits of a sequence depend on the one that its batch takes.
 constexpr double kPackedMaxBytes = 4294967296.0 - 131072.0;
 // `variant`: instances with more or fewer units a workgroup (0 for trees); packed_variant picks one for a recurrence's batch.
 int packed_groups(CellEpilogue epi, int32_t H, int32_t K, int32_t variant, int32_t n_cu);

@@ -107,8 +107,8 @@ int main() {
     }
     if (T == 0) continue;
     const int groups = directions * rnd_in(1, 20);
-    std::vector<int32_t> out((size_t)directions * R, -1), prev((size_t)directions * R, -1), off((size_t)T * groups + 1, -1);
-    stage_seq_groups(n_seq, len.data(), T, groups, directions, out.data(), prev.data(), off.data());
+    std::vector<int32_t> out((size_t)directions * R, -1), off((size_t)T * groups + 1, -1);
+    stage_seq_groups(n_seq, len.data(), T, groups, directions, out.data(), off.data());
     CHECK(off[0] == 0 && off[(size_t)T * groups] == directions * R);
     std::vector<int> seen((size_t)directions * R, 0);
     std::vector<int> seq_of(R);
@@ -124,7 +124,6 @@ int main() {
           const bool backward = directions == 2 && (g & 1);
           const int row = out[p], q = seq_of[row];
           CHECK(row == (backward ? row0[q] + len[q] - 1 - t : row0[q] + t));
-          CHECK(prev[p] == (t == 0 ? 0 : backward ? row + 1 : row - 1));
           CHECK(t == 0 || at[p - p0] == q);
           CHECK(!seen[(size_t)backward * R + row]++);
           now.push_back(q);
