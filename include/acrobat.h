@@ -23,8 +23,8 @@
  *  - Throughput: two contexts, each fed on a stream of its own with mini-batches in turn, overlap what need not take
  *    turns: uploads, leaf levels and level launches of one batch with another's.  Calls that run as ONE launch whose
  *    workgroups wait for each other (see acrobat_set_persistent) do not overlap one another in that launch: the library
- *    lets them take turns.  For TreeLSTM batches with H <= 512 that is most of the call: 1.09 times the throughput of one
- *    stream for 8 trees (H = 256), 1.38 for 64 trees (H = 256), 1.11 for 256 trees (H = 512).  The first dozen calls of a
+ *    lets them take turns.  For TreeLSTM batches with H <= 512 that is most of the call: 1.04 times the throughput of one
+ *    stream for 8 trees (H = 256), 1.05 for 64 trees (H = 256), 1.02 for 256 trees (H = 512).  The first dozen calls of a
  *    second stream include a one-time 6 ms that the runtime takes to set up copies of two streams side by side.
  *  - Stream capture (hipStreamBeginCapture on the given stream): a forward call may be recorded
  *    into a HIP graph once an uncaptured call of at least the same sizes has run on the context
@@ -125,9 +125,12 @@ int acrobat_schedule_birnn(int32_t n_seq, const int32_t* len, int32_t* n_levels,
  * Products are fp32 in and out.  Wide levels and the launches on resident weights take them on the fp16 matrix cores,
  * every operand split into two terms with a scale per row (22 to 23 bits, less for elements more than 2^17 below the
  * largest of their row), added up in fp32; sums in which that would show in the gates - the largest elements of the
- * two rows have a product of 2^13 or more - and sums that are not finite are computed in fp32.  A forced tile
- * (acrobat_set_tuning) keeps every product in fp32.  The same holds for the LSTM, the BiRNN's steps in one launch and,
- * with a scale per column of the children's matrices, the MV-RNN at d == 128.
+ * two rows have a product of 2^13 or more - and sums that are not finite are computed in fp32, which is slower (features of
+ * 1e5: about twice the time of a call).  A forced tile (acrobat_set_tuning) keeps every product in fp32.  The same holds for
+ * the LSTM (input products of 1 GFLOP or more from H = 256 on, others from the size on at which the split wins; steps, but for
+ * the older kernel of acrobat_set_persistent and launches per step), for the BiRNN (input products of both directions of 1.5
+ * GFLOP or more with H >= 256 and D >= 256, and steps under the same conditions) and, with a scale per column of the
+ * children's matrices, for the MV-RNN at d == 128.  Results are as close to 64 bits as those of fp32 instructions or closer.
  * Device pointers: d_emb [V,D], d_Wleaf [5H,D], d_bleaf [5H] or NULL (= 0), d_U [5H,2H],
  * d_b [5H] or NULL, d_h / d_c [N,H] (written). */
 int acrobat_treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, int32_t D,
@@ -140,8 +143,10 @@ int acrobat_treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32
  * same choice of kernel variant per level as long as a level's partial tiles or split weights fit the fixed
  * workspace; a level whose partial tiles do not fit runs unsplit and one whose split weights do not fit - 40 H^2 bytes
  * for internal levels that take a launch each, 20 H D for leaf levels with D > 1 024, about 28 MB fit - on fp32 tiles,
- * which only changes the rounding), but the call allocates and frees nothing on the device or in pinned memory: the index lists are staged in a
- * pinned buffer of fixed size that acrobat_create made, and their device copy and the partial tiles of
+ * which only changes the rounding; internal levels whose packed operands do not fit gather their rows, more slowly, with the
+ * same bits: what is left for them, at most 24 MB, holds those of 64 sentences of up to 15 levels at H = 256, and of about
+ * 20 at H = 512), but the call allocates and frees nothing on the device or in pinned memory: the index lists are
+ * staged in a pinned buffer of fixed size that acrobat_create made, and their device copy and the partial tiles of
  * k-split levels live in one array of ACROBAT_NOALLOC_SCRATCH_MIB MiB that is part of the library's
  * device image.  Each GPU the library is used on holds that array until the process ends.
  *  - At most ACROBAT_NOALLOC_MAX_NODES nodes per call, else ACROBAT_EINVAL (nothing is launched).
@@ -189,14 +194,15 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
 
 /* Level-launch strategy of the recurrence (the paper's activity breakdown, table 6, and its remark on
  * persistence in Evaluation, "Overall Performance": launch overhead is of the order of the kernel time).
- * Enabled (the default), acrobat_varlen_lstm_forward runs all time steps in ONE launch whenever H is 128
- * or 256, at most 256 sequences have a step to run, and every workgroup of that launch is resident on
- * the GPU at once (an occupancy query), and for other sizes as described further down (otherwise, or when
- * disabled, one launch per step as described above).  The batches are the same - step t over the sequences with len > t - and so is the schedule
- * that acrobat_last_schedule reports; the workgroups keep W_h on chip for all steps and synchronise
+ * Enabled (the default), acrobat_varlen_lstm_forward runs all time steps in ONE launch from H = 128 up to H = 512 (otherwise,
+ * or when disabled, one launch per step as described above): of an older kernel if H is 128, at most 256 sequences have a
+ * step to run and every workgroup of that launch is resident on the GPU at once (an occupancy query), else of the kernel
+ * described further down; at H = 256 the older one remains for calls without room for the newer one's operands.  The batches are
+ * the same - step t over the sequences with len > t - and so is the schedule that acrobat_last_schedule reports; the
+ * workgroups keep W_h on chip for all steps and synchronise
  * among themselves through arrival counters in device memory.  Every wait inside that kernel is bounded
- * by max_polls polls of a counter (max_polls < 0: the kernel's default - about a quarter of a million, sixteen million
- * for the launches of groups of H / 16 workgroups described further down; max_polls == 0 is a
+ * by max_polls polls of a counter (max_polls < 0: the kernel's default - about a quarter of a million for the older kernels,
+ * sixteen million for the launches of groups of workgroups described further down; max_polls == 0 is a
  * test hook: every wait gives up at once, whether or not it would have had to wait, so the error path below runs
  * deterministically): a
  * workgroup whose wait runs out raises a status word (in pinned host memory; nothing touches it otherwise),
@@ -204,25 +210,27 @@ int acrobat_varlen_lstm_forward(acrobat_ctx* ctx, int32_t n_seq, const int32_t* 
  * acrobat_device_status reports that: call it once the stream has been synchronised; it returns ACROBAT_OK
  * or ACROBAT_ETIMEOUT and clears the condition.  Until it has been called the word stays raised and later
  * persistent launches of the context give up at their first long wait too.
- * The same switch covers acrobat_birnn_forward (H in {128, 256, 512}, at most 256 non-empty sequences, every
- * workgroup resident at once): both recurrences then run in one launch, blocks of 16 sequences per direction,
- * H / 16 workgroups per block exchanging h after every step in the same way.
+ * The same switch covers acrobat_birnn_forward: both recurrences run in one launch, of an older kernel for H in {128, 256}
+ * and at most 256 non-empty sequences and for H = 512 and as many as leave every workgroup a compute unit (64), blocks of
+ * 16 sequences per direction, H / 16 workgroups per block exchanging h after every step in the same way; else as below.
  * It also covers acrobat_mvrnn_forward (d == 64 up to a widest internal level of 2 048 nodes; d == 128 with
  * a level of more than 512 nodes reports that launch level by level, as ACROBAT_K_MVRNN_LEVEL):
  * all internal levels then run in ONE launch in which
  * a node waits for its own two children only (flag words per node, polled with the same bound) instead of a
  * whole level waiting for the previous one, provided every workgroup of that launch is resident at once and the
  * call is not being captured into a graph (a captured call keeps one launch per level).
- * Recurrences of other sizes run in one launch of another kernel from H = 128 up to H = 512, with any number of
- * sequences, dealt out to groups of H / 16 workgroups that wait for each other between steps; with profiling on, their
- * steps are timed by clock stamps inside it (records of kind ACROBAT_K_LSTM_STEP / ACROBAT_K_RNN_STEP).
+ * Other recurrences from H = 128 up to H = 512, with any number of sequences, run in one launch of another kernel: dealt
+ * out to groups of H / 16, H / 32 or (BiRNN) H / 64 workgroups, by the size of the batch, that wait for each other between
+ * steps.  With profiling on, at most 256 sequences at H = 512 or (LSTM) H = 256 have one record for all steps; else the
+ * steps are timed by clock stamps inside the launch (records of kind ACROBAT_K_LSTM_STEP / ACROBAT_K_RNN_STEP).
  * And it covers acrobat_treelstm_forward (and its variant that allocates nothing) for H <= 512: whole trees are dealt
  * out to groups of H / 16 workgroups that keep U on chip, and a group runs all internal levels of its trees in ONE
  * launch, its workgroups waiting for each other between levels.
  * A captured tree call, and one with explicit gathers, launches the same arithmetic level by level instead, with the same
  * results bit for bit (one for which no call of its size has made room before the capture takes the kernels of the
  * disabled path where those need none).  A captured LSTM is one launch for H in {128, 256, 512} and at most 256 sequences,
- * a captured BiRNN where its older kernel takes it (above); other sizes take a launch per step, whose results may differ
+ * a captured BiRNN where its older kernel takes it (above) and for H = 512 and at most 256 sequences; other sizes take a
+ * launch per step, whose results may differ
  * from the uncaptured call's in the last bits.  With profiling on, the levels of the one launch are timed by clock stamps
  * inside it.
  * Nothing else may occupy the GPU's compute units for long while such a launch runs (another stream's
