@@ -40,10 +40,11 @@ struct DenseArgs {
 };
 // Whether a level (G gates of H units over K columns) is wide enough for this kernel to win; a forced tile switches it off.
 bool dense_level_wins(CellEpilogue epi, int32_t n, int32_t H, int32_t K, const SplitKWorkspace& ws);
-// Scratch of a level: packed rows, then their inverse scales, then the largest ones.
+// Scratch of a level: packed rows, then their inverse scales, then the largest ones; whole cache lines, so that what lies
+// behind it is aligned.
 inline size_t dense_scratch_bytes(int32_t n, int32_t K) {
   const size_t blocks = ((size_t)n + 15) / 16;
-  return blocks * (16 * (size_t)K + 17) * sizeof(float);
+  return blocks * (16 * (size_t)K + 32) * sizeof(float);
 }
 // Packs the input rows (s.a.src0, gathered by s.a.idx0) into `scratch` and runs the level: two launches.  A leaf level (its rows
 // and its results are named by lists) runs in pieces, with the same bits, where not all of its rows fit.
