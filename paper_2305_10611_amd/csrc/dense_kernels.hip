@@ -175,10 +175,20 @@ __global__ __launch_bounds__(512, 2) void cell_dense_kernel(const DenseArgs s) {
   };
   auto block_at = [&](int b) { return b < b1 ? (unsigned)b * block_bytes : kNowhere - 2048u * KS * NS; };
   __syncthreads();
+#pragma unroll
+  for (int t = 0; t < NS; ++t) {
+    request(block_at(b0), t);
+    hold_order();
+  }
   // Rows whose inverse scale is above `limit` (both are positive: compared as integers) are not to be split against some column
   // of this workgroup.  It does not depend on the other rows of a block, so neither do a row's bits.
+  // `some_plain`: the share has such rows.
+  const __attribute__((address_space(4))) int* const largest_of = (const __attribute__((address_space(4))) int*)s.largest;
   int limit;
+  bool some_plain;
   {
+    int most = 0;
+    for (int b = b0 + lane; b < b1; b += 64) most = max(most, __float_as_int(s.largest[b]));
     float m = 0.0f;
 #pragma unroll
     for (int i = lane; i < 16 * NW; i += 64) {
@@ -189,12 +199,7 @@ __global__ __launch_bounds__(512, 2) void cell_dense_kernel(const DenseArgs s) {
 #pragma unroll
     for (int d = 1; d < 64; d *= 2) m = fmaxf(m, __shfl_xor(m, d));
     limit = __builtin_amdgcn_readfirstlane(__float_as_int(kLargestUnit / m));
-  }
-  const __attribute__((address_space(4))) int* const largest_of = (const __attribute__((address_space(4))) int*)s.largest;
-#pragma unroll
-  for (int t = 0; t < NS; ++t) {
-    request(block_at(b0), t);
-    hold_order();
+    some_plain = __ballot(most > limit) != 0;
   }
   // This wavefront's partial sums of the rows of a block that are not to be split, on the fp32 matrix cores.  Bound: the weights
   // that every block fetches again (unscaled features of 1e5, BiRNN, H = D = 512, 300 sequences: 292 us a call on fp32 tiles, 279
@@ -257,7 +262,7 @@ __global__ __launch_bounds__(512, 2) void cell_dense_kernel(const DenseArgs s) {
       const floatx4 unit = *reinterpret_cast<const floatx4*>(s_winv[w][li]);
 #pragma unroll
       for (int g = 0; g < G; ++g) acc[g] *= unit[g];
-      if (__builtin_expect(b + r < b1 && largest_of[b + r] > limit, 0)) multiply_plain(b + r, acc);
+      if (__builtin_expect(some_plain && b + r < b1 && largest_of[b + r] > limit, 0)) multiply_plain(b + r, acc);
       float* const z = zc + (r * NW + w) * ZQ;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
