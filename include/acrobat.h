@@ -144,8 +144,8 @@ int acrobat_treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32
  * workspace; a level whose partial tiles do not fit runs unsplit and one whose split weights do not fit - 40 H^2 bytes
  * for internal levels that take a launch each, 20 H D for leaf levels with D > 1 024, about 28 MB fit - on fp32 tiles,
  * which only changes the rounding; internal levels whose packed operands do not fit gather their rows, more slowly, with the
- * same bits: what is left for them, at most 24 MB, holds those of 64 sentences of up to 15 levels at H = 256, and of about
- * 20 at H = 512), but the call allocates and frees nothing on the device or in pinned memory: the index lists are
+ * same bits: what is left for them, at most 31 MiB, holds those of 64 sentences of up to 23 levels at H = 256, and of about
+ * 50 of up to 15 at H = 512), but the call allocates and frees nothing on the device or in pinned memory: the index lists are
  * staged in a pinned buffer of fixed size that acrobat_create made, and their device copy and the partial tiles of
  * k-split levels live in one array of ACROBAT_NOALLOC_SCRATCH_MIB MiB that is part of the library's
  * device image.  Each GPU the library is used on holds that array until the process ends.

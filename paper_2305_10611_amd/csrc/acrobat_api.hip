@@ -930,9 +930,9 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
       }
     }
     unsigned char* packed_at = ctx->d_packed;
-    if (packed && noalloc) {  // the end of the partial tiles' region; a quarter of it stays
+    if (packed && noalloc) {  // the end of the partial tiles' region; a quarter of it stays if there are levels besides the launch
       const size_t floats = 2 * operand_bytes / sizeof(float);
-      packed = floats <= ws.partial_floats / 4 * 3;
+      packed = floats <= (plan.first > 1 ? ws.partial_floats / 4 * 3 : ws.partial_floats);
       if (packed) {
         ws.partial_floats -= floats;
         packed_at = reinterpret_cast<unsigned char*>(ws.partial + ws.partial_floats);

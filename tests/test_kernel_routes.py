@@ -83,6 +83,26 @@ def test_leaves_without_allocations_have_the_ordinary_bits(ctx, n, leaves, H, D,
     assert rel(h[few], oh) < 1e-6 and rel(c[few], oc) < 1e-6
 
 
+@pytest.mark.parametrize("n,H,seed,levels", [(64, 256, 6, 16), (40, 512, 7, None), (110, 256, 1, None)])
+def test_sentences_without_allocations_run_on_packed_levels(ctx, n, H, seed, levels):
+    """Also where they are deep, or their leaves' packed rows (110) or 128 KiB a block (H = 512) leave less room for the levels."""
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    w = gen.treelstm_workload(n, 10, 50, H, 500, "uniform", seed=seed, bias_scale=0.2)
+    h, c = P.run_treelstm(ctx, w)
+    if levels:
+        assert len(ctx.acrobat_last_schedule()[0]) - 1 == levels
+    d = {k: P.dev(w[k]) for k in ("emb", "W_leaf", "b_leaf", "U", "b")}
+    out = [P.nan_filled(*h.shape) for _ in range(2)]
+    names = P.kernels_of(lambda: ctx.check(ctx.acrobat_treelstm_forward_noalloc(
+        w, H, H, 500, d["emb"], d["W_leaf"], d["b_leaf"], d["U"], d["b"], *out, P.stream_handle())))
+    assert ctx.acrobat_device_status() == A.OK
+    assert any("cell_packed_kernel<5," in k for k in names), names
+    assert np.array_equal(out[0].cpu().numpy(), h) and np.array_equal(out[1].cpu().numpy(), c)
+    want = oracle.treelstm(w, nthreads=NT)
+    assert rel(h, want[0]) < 1e-6 and rel(c, want[1]) < 1e-6
+
+
 @pytest.mark.parametrize("kind,H,lens", [("lstm", 512, [1000] + [1] * 1999), ("lstm", 320, [9000] * 4 + [1] * 252),
                                          ("lstm", 512, [9000] * 4 + [1] * 252), ("birnn", 512, [4500] * 4 + [2, 1] * 126)])
 def test_few_long_sequences_among_many_short_ones(ctx, kind, H, lens):
