@@ -1107,7 +1107,7 @@ struct SeqPlan {
   int32_t groups = 0, variant = 0;
   bool whole = false;  // one launch record for all steps (else one per step)
   size_t n_off = 0, n_idx = 0;  // entries of the offset table; of both lists: rows, offsets
-  int32_t share_blocks = 0;
+  int32_t share_blocks = 0, sets = 0;
   size_t operand_bytes = 0;     // of packed states; c states take as much
 };
 
@@ -1139,10 +1139,15 @@ SeqPlan plan_recurrence(acrobat_ctx* ctx, CellEpilogue epi, int32_t H, int32_t R
   p.n_off = (size_t)n_steps * p.groups + 1;
   p.n_idx = (size_t)directions * R + p.n_off;
   p.share_blocks = seq_share_blocks(step_off[2] - step_off[1], p.groups / directions);
-  p.operand_bytes = (size_t)2 * p.groups * p.share_blocks * 64 * H;
+  // Two sets of blocks, unless those of all steps are small: a line that the group has just read takes longer to write (75
+  // sequences of 1 to 60 steps, H = 320, 6 MB for all: 162.9 us with two sets, 160.8 with 16, 160.3 with all; 256 of 1 to 100,
+  // H = 512, 52 MB, 386, 384 and 439, 1 500 of 1 to 60 785, 808 and 831).  (A captured call may only have room for two.)
+  const size_t set_bytes = (size_t)p.groups * p.share_blocks * 64 * H, arrays = epi == EPI_LSTM_STEP ? 2 : 1;
+  p.sets = n_steps * set_bytes <= (size_t)8 << 20 && reserve_packed(ctx, arrays * n_steps * set_bytes, stream) ? n_steps : 2;
+  p.operand_bytes = p.sets * set_bytes;
   // (a captured call that lacks the room does without)
   if ((double)p.operand_bytes > kPackedMaxBytes || !indices_fit(ctx, p.n_idx, stream) ||
-      !reserve_packed(ctx, (epi == EPI_LSTM_STEP ? 2 : 1) * p.operand_bytes, stream))
+      !reserve_packed(ctx, arrays * p.operand_bytes, stream))
     p.groups = 0;
   return p;
 }
@@ -1166,6 +1171,7 @@ int run_recurrence(acrobat_ctx* ctx, CellEpilogue epi, StationaryArgs& sa, const
   sa.variant = plan.variant;
   sa.n_steps = n_steps;
   sa.share_blocks = plan.share_blocks;
+  sa.sets = plan.sets;
   sa.n_groups = plan.groups;
   sa.counters = ctx->splitk.counters;
   sa.status = ctx->h_status_dev;

@@ -21,10 +21,11 @@
 // l holds row l % 16, k = 4 (l / 16) + 0 .. 3 and 16 more.  A tree node has its left child's H columns, then its right
 // child's.  cells: [block][side][workgroup of the group][row][unit].  Share (level, group) of a tree batch, list positions p0
 // ..., has the blocks from (p0 - first_position) / 16 + level * groups + group on (rounded down: no two shares meet).  A
-// recurrence has two sets of blocks and in each a group those of its widest share: step t reads set t & 1 and leaves its states
-// in the other one, which step t - 1 has read - all of a group has announced that step before it starts on t.  (A set for every
-// step was slower where they outgrew the caches, LSTM, 256 sequences of 1 to 100 steps, H = 512 436 against 382 us, and the same
-// elsewhere, 75 of 1 to 60, H = 320 164 and 165; keeping c states of single blocks in registers changed nothing.)
+// recurrence has `sets` sets of blocks, at least two, and in each a group those of its widest share: step t reads set t % sets
+// and leaves its states in the next one, which only steps before it have read - all of a group has announced those before it
+// starts on t.  (A set for every step was slower where they outgrew the caches, LSTM, 256 sequences of 1 to 100 steps, H = 512
+// 439 against 386 us, and a little faster where they are small, 75 of 1 to 60, H = 320 160 against 163; keeping c states of single
+// blocks in registers changed nothing.)
 // Tree levels: the arithmetic of the gathering kernel, in the same order, so the same bits.
 #include "tree_kernels.h"
 
@@ -185,9 +186,11 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
 
   int lv = s.level0, p0, p1;
   unsigned arrived = 0;  // levels this group has announced
-  // recurrences: first block of the set that this step reads, and of the other one
-  unsigned here = (unsigned)((lv & 1) * s.n_groups + group) * (unsigned)s.share_blocks;
-  unsigned there = (unsigned)((~lv & 1) * s.n_groups + group) * (unsigned)s.share_blocks;
+  // recurrences: first block of the set that this step reads, and of the one after it
+  const unsigned set_blocks = (unsigned)s.n_groups * (unsigned)s.share_blocks, set0 = (unsigned)group * (unsigned)s.share_blocks;
+  const unsigned sets_end = set0 + (unsigned)s.sets * set_blocks;
+  unsigned here = kTree ? 0u : set0 + (unsigned)(lv % s.sets) * set_blocks, there = here + set_blocks;
+  if (there == sets_end) there = set0;
   share_of(lv, p0, p1);
   if (p0 >= p1) return;  // (nothing in this level: nothing in a later one)
   if constexpr (!kTree) request_lists(next_out, p0, p1);
@@ -441,9 +444,9 @@ __global__ __launch_bounds__(64 * NW, 2) void cell_packed_kernel(const Stationar
     p1 = c1;
     ++lv;
     if constexpr (!kTree) {
-      const unsigned set = here;
       here = there;
-      there = set;
+      there += set_blocks;
+      if (there == sets_end) there = set0;
     }
     return true;
   };

@@ -39,6 +39,7 @@ struct StationaryArgs {
   int32_t n_steps;         // of a recurrence, also those behind level1
   int32_t first_position;  // trees: list position from which blocks are counted
   int32_t share_blocks;    // recurrences: blocks of a group's share of any step but the first
+  int32_t sets;            // and sets of blocks that the steps take in turn
   int32_t variant;         // which instance, see packed_variant
 };
 // Groups of H / 16 workgroups that are resident on the current device at once (eight XCDs, a group never crosses one);

@@ -184,6 +184,27 @@ def test_captured_recurrences_of_one_launch(ctx, kind, H, n, kernel):
     assert ctx.acrobat_device_status() == A.OK
 
 
+def test_captured_lstm_with_room_for_two_steps_states_only(ctx):
+    """The call before the capture is wider and keeps two sets of packed states; this one would keep all steps': same bits."""
+    import torch
+    import paper_2305_10611_amd as A
+    from tests import parity as P
+    w = gen.lstm_workload(40, 30, 40, 512, 32, seed=3, bias_scale=0.2)
+    other = A.Context(0)
+    want = P.run_lstm(other, w)
+    other.close()
+    P.run_lstm(ctx, gen.lstm_workload(256, 60, 100, 512, 32, seed=4, bias_scale=0.2))
+    g, out, keep = captured(ctx, w, "lstm")
+    for _ in range(3):
+        for o in out:
+            o.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        for o, r in zip(out, want):
+            assert np.array_equal(o.cpu().numpy(), r), np.flatnonzero((o.cpu().numpy() != r).any(axis=1))
+    assert ctx.acrobat_device_status() == A.OK
+
+
 def test_captured_lstm_without_room_for_packed_states(ctx):
     """H = 256: the older kernel, which needs none, takes the call in one launch (recorded once more without polls, it gives up
     and says so)."""
