@@ -840,7 +840,9 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     const size_t operand_bytes = (size_t)blocks * 128 * H;
     // (Blocks of a group's narrow levels are mostly empty, and a share may have one more than it fills: one tree of thousands of
     // levels among small ones takes over 100 times the bytes of its states.  The room stays with the context, so from 256 MiB
-    // on it may be four times the bytes of all states at most; batches of 64 to 1 024 sentences take 1.2 to 3.3 times.)
+    // on it may be four times the bytes of all states at most; batches of 64 to 1 024 sentences take 1.2 to 3.3 times.  Mostly empty
+    // blocks are slower than gathered rows there: packed / gathered 20 chains of 300 levels, H = 512 1 390 / 1 182 us, 8 of 1 000
+    // 4 600 / 3 710, 64 of 500, H = 256 1 777 / 1 698.)
     const double packed_most = std::max(268435456.0, 4.0 * 8.0 * N * H);
     bool packed = blocks > 0 && (double)operand_bytes <= kPackedMaxBytes && 2.0 * operand_bytes <= packed_most &&
                   (!noalloc || (4 * (size_t)N + n_off) * sizeof(int32_t) <= kStaticIndexBytes);
