@@ -838,12 +838,14 @@ int treelstm_forward(acrobat_ctx* ctx, const acrobat_trees* trees, int32_t H, in
     const int64_t blocks = one_launch && gpu_bound && (plan.leaf || plan.dense_leaf) && n_off > 0 && s.n_levels - plan.first > 1
                                ? share_blocks((int64_t)N - s.level_off[plan.first], (int64_t)s.n_levels * plan.groups) : 0;
     const size_t operand_bytes = (size_t)blocks * 128 * H;
-    // (Blocks of a group's narrow levels are mostly empty, and a share may have one more than it fills: one tree of thousands of
-    // levels among small ones takes over 100 times the bytes of its states.  The room stays with the context, so from 256 MiB
-    // on it may be four times the bytes of all states at most; batches of 64 to 1 024 sentences take 1.2 to 3.3 times.  Mostly empty
-    // blocks are slower than gathered rows there: packed / gathered 20 chains of 300 levels, H = 512 1 390 / 1 182 us, 8 of 1 000
-    // 4 600 / 3 710, 64 of 500, H = 256 1 777 / 1 698.)
-    const double packed_most = std::max(268435456.0, 4.0 * 8.0 * N * H);
+    // (Blocks of a group's narrow levels are mostly empty, and a share may have one more than it fills: one tree of thousands
+    // of levels among small ones takes over 100 times the bytes of its states, which stay with the context.  And operands that
+    // outgrow the 256 MiB of the last cache by some are slower than gathered rows: chains, packed / gathered, H = 512, 8 of 225
+    // levels (251 MB) 812 / 870 us, of 250 (278) 981 / 962, of 1 000 4 600 / 3 710, 20 of 225 (273) 869 / 900, of 250 (303) 1
+    // 012 / 1 012; H = 256, 16 of 300 (334) 856 / 922, of 330 (368) 1 072 / 1 014, 64 of 250 (327) 831 / 872, of 280 (367) 984
+    // / 973; H = 128, 40 of 260 (362) 742 / 750, of 290 (403) 864 / 835.  Batches of 64 to 1 024 sentences, whose blocks are
+    // full, take 1.2 to 3.3 times their states.)
+    const double packed_most = std::max((H > 256 ? 280.0 : 336.0) * 1048576.0, 32.0 * N * H);
     bool packed = blocks > 0 && (double)operand_bytes <= kPackedMaxBytes && 2.0 * operand_bytes <= packed_most &&
                   (!noalloc || (4 * (size_t)N + n_off) * sizeof(int32_t) <= kStaticIndexBytes);
     packed = packed && (noalloc || reserve_packed(ctx, 2 * operand_bytes, stream));
