@@ -131,12 +131,14 @@ def test_few_long_sequences_among_many_short_ones(ctx, kind, H, lens):
         assert rel(a, b) < 2e-6
 
 
-def test_one_deep_tree_among_small_ones(ctx):
-    """A chain of 3 000 levels beside 255 trees of two leaves: packed operands would take 4 GB for states of 28 MB."""
+@pytest.mark.parametrize("deep,few,kernel", [(3000, 255, "cell_stationary_kernel<5,"), (120, 15, "cell_packed_kernel<5,")])
+def test_one_deep_tree_among_small_ones(ctx, deep, few, kernel):
+    """A chain of 3 000 levels beside 255 trees of two leaves: packed operands would take 4 GB for states of 28 MB, so rows are
+    gathered.  Of 120 beside 15: they take over 100 times the states as well, but fit the caches."""
     import torch
     import paper_2305_10611_amd as A
     from tests import parity as P
-    H, deep, few = 512, 3000, 255
+    H = 512
     w = gen.treelstm_workload(few + 1, 2, 2, H, 60, "uniform", seed=4, bias_scale=0.2, D=64)
     rng = gen.make_rng(6)
     chain = np.arange(deep, dtype=np.int32)  # node deep + 1 + i has node deep + i (node 0: a leaf) and leaf i + 1 as children
@@ -154,7 +156,7 @@ def test_one_deep_tree_among_small_ones(ctx):
     names = P.kernels_of(lambda: got.extend(P.run_treelstm(ctx, w)))
     assert ctx.acrobat_device_status() == A.OK
     assert free - torch.cuda.mem_get_info()[0] < 384 << 20
-    assert any("cell_stationary_kernel<5," in k for k in names) and not any("cell_packed" in k for k in names), names
+    assert any(kernel in k for k in names) and any("cell_packed" in k for k in names) == ("packed" in kernel), names
     want = oracle.treelstm(w, nthreads=NT)
     assert rel(got[0], want[0]) < 1e-6 and rel(got[1], want[1]) < 1e-6
 
